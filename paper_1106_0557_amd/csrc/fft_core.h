@@ -175,6 +175,21 @@ constexpr int first_factor(int R) {
     return R;
 }
 
+// Largest power of the largest odd prime (5, else 3) dividing R; 1 if R is a power of two.
+constexpr int odd_prime_power(int R) {
+    const int p = R % 5 == 0 ? 5 : (R % 3 == 0 ? 3 : 0);
+    int P = 1;
+    while (p && R % (P * p) == 0) P *= p;
+    return P;
+}
+
+// Index with remainder k1 mod P and k2 mod Q, P and Q coprime (Chinese remainder theorem).
+constexpr int crt(int k1, int P, int k2, int Q) {
+    int k = k1;
+    while (k % Q != k2) k += P;
+    return k;
+}
+
 // In-register DFT of length R, natural order in and out:
 // X[k] = sum_j x[j] exp(DIR 2 pi i j k / R).
 template <int R, int DIR, typename T>
@@ -186,14 +201,12 @@ __device__ __forceinline__ void dft(cx<T> *x) {
         x[0] = a + b;
         x[1] = a - b;
     } else if constexpr (R == 3) {
-        constexpr T h = static_cast<T>(0.8660254037844386467637231707529362);  // sin(2 pi / 3)
+        constexpr T h = static_cast<T>(DIR * 0.8660254037844386467637231707529362);  // DIR sin(2 pi / 3)
         const cx<T> s = x[1] + x[2], d = x[1] - x[2];
         const cx<T> m = {x[0].x - static_cast<T>(0.5) * s.x, x[0].y - static_cast<T>(0.5) * s.y};
-        // DIR * i * h * d
-        const cx<T> n = DIR > 0 ? cx<T>{-h * d.y, h * d.x} : cx<T>{h * d.y, -h * d.x};
         x[0] = x[0] + s;
-        x[1] = m + n;
-        x[2] = m - n;
+        x[1] = {m.x - h * d.y, m.y + h * d.x};  // m + DIR i sin(2 pi / 3) d
+        x[2] = {m.x + h * d.y, m.y - h * d.x};
     } else if constexpr (R == 4) {
         const cx<T> t0 = x[0] + x[2], t1 = x[0] - x[2], t2 = x[1] + x[3];
         const cx<T> t3 = rot<4, DIR, 1>(x[1] - x[3]);
@@ -204,20 +217,49 @@ __device__ __forceinline__ void dft(cx<T> *x) {
     } else if constexpr (R == 5) {
         constexpr CosSin w1 = turn(1, 5), w2 = turn(2, 5);
         const T c1 = static_cast<T>(w1.c), c2 = static_cast<T>(w2.c);
-        const T s1 = static_cast<T>(w1.s), s2 = static_cast<T>(w2.s);
+        constexpr double ratio = w2.s / w1.s;
+        const T s1 = static_cast<T>(DIR * w1.s), rs = static_cast<T>(ratio);
         const cx<T> a1 = x[1] + x[4], d1 = x[1] - x[4], a2 = x[2] + x[3], d2 = x[2] - x[3];
         const cx<T> p1 = {x[0].x + c1 * a1.x + c2 * a2.x, x[0].y + c1 * a1.y + c2 * a2.y};
         const cx<T> p2 = {x[0].x + c2 * a1.x + c1 * a2.x, x[0].y + c2 * a1.y + c1 * a2.y};
-        const cx<T> u1 = {s1 * d1.x + s2 * d2.x, s1 * d1.y + s2 * d2.y};
-        const cx<T> u2 = {s2 * d1.x - s1 * d2.x, s2 * d1.y - s1 * d2.y};
-        // q = DIR * i * u
-        const cx<T> q1 = DIR > 0 ? cx<T>{-u1.y, u1.x} : cx<T>{u1.y, -u1.x};
-        const cx<T> q2 = DIR > 0 ? cx<T>{-u2.y, u2.x} : cx<T>{u2.y, -u2.x};
+        // (sin1 d1 + sin2 d2) and (sin2 d1 - sin1 d2) with sin1 taken out, which goes
+        // into the multiply-adds of the outputs
+        const cx<T> u1 = {d1.x + rs * d2.x, d1.y + rs * d2.y};
+        const cx<T> u2 = {rs * d1.x - d2.x, rs * d1.y - d2.y};
         x[0] = x[0] + a1 + a2;
-        x[1] = p1 + q1;
-        x[4] = p1 - q1;
-        x[2] = p2 + q2;
-        x[3] = p2 - q2;
+        x[1] = {p1.x - s1 * u1.y, p1.y + s1 * u1.x};
+        x[4] = {p1.x + s1 * u1.y, p1.y - s1 * u1.x};
+        x[2] = {p2.x - s1 * u2.y, p2.y + s1 * u2.x};
+        x[3] = {p2.x + s1 * u2.y, p2.y - s1 * u2.x};
+    } else if constexpr (odd_prime_power(R) > 1 && odd_prime_power(R) < R) {
+        // Coprime factors, R = P * Q with P odd (Good-Thomas): input index
+        // (Q p + P q) mod R, output index congruent to k1 mod P and k2 mod Q, and
+        // no twiddles between the layers.  The odd factor first: with the upper
+        // half of the input zero its short DFTs have one or two operands.
+        constexpr int P = odd_prime_power(R);
+        constexpr int Q = R / P;
+        cx<T> a[P][Q];
+        sfor<0, Q>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            cx<T> u[P];
+            sfor<0, P>([&](auto pc) {
+                constexpr int p = decltype(pc)::value;
+                u[p] = x[(Q * p + P * q) % R];
+            });
+            dft<P, DIR>(u);
+            sfor<0, P>([&](auto kc) {
+                constexpr int k1 = decltype(kc)::value;
+                a[k1][q] = u[k1];
+            });
+        });
+        sfor<0, P>([&](auto kc) {
+            constexpr int k1 = decltype(kc)::value;
+            dft<Q, DIR>(a[k1]);
+            sfor<0, Q>([&](auto k2c) {
+                constexpr int k2 = decltype(k2c)::value;
+                x[crt(k1, P, k2, Q)] = a[k1][k2];
+            });
+        });
     } else {
         // Cooley-Tukey in registers, R = P * Q, input index q + Q p, output k1 + P k2.
         constexpr int P = first_factor(R);
