@@ -5,6 +5,7 @@ Every call recompiles (the build check compiles each time it is asked to).
 """
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import subprocess
 import sys
@@ -22,8 +23,9 @@ ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-parameter", "-fno-signed-zeros",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-DEVICE_SOURCES = (["green.hip", "line_generic.hip", "noalloc.hip", "pass_f32_e32.hip"]
-                  + [f"pass_{p}_e{e}.hip" for p in ("f32", "f64") for e in (16, 20, 24, 36)])
+DEVICE_SOURCES = ([f"pass_{p}_e{e}.hip" for p in ("f32", "f64") for e in (36, 24, 20, 16)]
+                  + [f"mix_{p}_{c}.hip" for p in ("f32", "f64") for c in "edcba"]
+                  + ["line_generic.hip", "pass_f32_e32.hip", "mix_info.hip", "green.hip", "noalloc.hip"])
 HOST_SOURCES = ["pspfft_runtime.cpp"]
 
 
@@ -34,23 +36,21 @@ def _run(cmd):
 
 def build(verbose: bool = True, jobs: int = 8) -> str:
     out_dir = tempfile.mkdtemp(prefix="pspfft_build_")
-    objs = []
-    procs = []
-    for src in DEVICE_SOURCES:
-        obj = os.path.join(out_dir, src + ".o")
-        cmd = [HIPCC, f"--offload-arch={ARCH}", *COMMON, "-c", os.path.join(CSRC, src), "-o", obj]
-        procs.append((cmd, subprocess.Popen(cmd)))
-        objs.append(obj)
-    for src in HOST_SOURCES:
-        obj = os.path.join(out_dir, src + ".o")
-        cmd = [HIPCC, f"--offload-arch={ARCH}", *COMMON, "-c", os.path.join(CSRC, src), "-o", obj]
-        procs.append((cmd, subprocess.Popen(cmd)))
-        objs.append(obj)
-    for cmd, p in procs:
+    # at most `jobs` compilers at a time (each takes one CPU), the longest first
+    sources = DEVICE_SOURCES + HOST_SOURCES
+    objs = [os.path.join(out_dir, src + ".o") for src in sources]
+    cmds = [[HIPCC, f"--offload-arch={ARCH}", *COMMON, "-c", os.path.join(CSRC, src), "-o", obj]
+            for src, obj in zip(sources, objs)]
+
+    def compile_one(cmd):
         if verbose:
             print("+", " ".join(cmd), flush=True)
-        if p.wait() != 0:
-            raise RuntimeError("compile failed: " + " ".join(cmd))
+        return subprocess.call(cmd)
+
+    with concurrent.futures.ThreadPoolExecutor(jobs) as pool:
+        for cmd, rc in zip(cmds, pool.map(compile_one, cmds)):
+            if rc != 0:
+                raise RuntimeError("compile failed: " + " ".join(cmd))
     tmp = LIB + ".tmp"
     _run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, LIB)

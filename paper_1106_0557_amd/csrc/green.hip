@@ -107,6 +107,10 @@ __device__ __forceinline__ long green_pos(long i, int nx, int ny, int nz, int gz
     nyq = kx == nx;
     if (!gz) return nyq ? row : row * nx + kx;
     const long kz = row / (ny + 1), ky = row - kz * (ny + 1);
+    if (gz == 2) {
+        const long pos = (kz >> 1) + ((kz & 1) ? nz / 2 + 1 : 0), groups = (nx + kGroup - 1) / kGroup;
+        return nyq ? ky * (nz + 1) + pos : ((ky * groups + kx / kGroup) * (nz + 1) + pos) * kGroup + kx % kGroup;
+    }
     return nyq ? ky * (nz + 1) + kz : (ky * nx + kx) * (nz + 1) + kz;
 }
 

@@ -15,9 +15,13 @@
 // y < ny; the inverse x pass reads them.  The upper z half of the doubled mesh
 // is never stored: it is zero on input and discarded on output.
 //
-// Green's-function spectrum (plan precision), octant kx <= nx, ky <= ny, kz <= nz:
-//   G  : [kz][ky][kx < nx]   row stride nx
-//   Gn : [kz][ky]            kx = nx
+// Green's-function spectrum (plan precision), octant kx <= nx, ky <= ny, kz <= nz,
+// by DevPlan::gz:
+//   0  G : [kz][ky][kx < nx]                  Gn : [kz][ky]   (kx = nx)
+//   1  G : [ky][kx][kz]                       Gn : [ky][kz]
+//   2  G : [ky][kx / kGroup][kz'][kx % kGroup]  Gn : [ky][kz']
+// with kz' the even kz first, then the odd ones (a z pass by half-length lines reads
+// one parity at a time).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,6 +30,9 @@
 #include <cstdint>
 
 namespace pspfft {
+
+// Adjacent kx that a blocked spectrum keeps together.
+constexpr int kGroup = 8;
 
 constexpr int kMaxStages = 10;
 constexpr int kMaxProblems = 32;  // problems per grouped launch
@@ -54,12 +61,16 @@ struct AxisPlan {
     int twoff[kMaxStages];      // offset of stage s in the twiddle table
     const void *tw;             // twiddles exp(-2 pi i r k / (Ns R)), k < Ns, 1 <= r < R
     const void *post;           // x only: exp(-i pi k / n), k < n
+    // stage twiddles of the half-length lines of mix_lines.h (null: another
+    // kernel takes the axis): for s = 0, 1 and each stage past the first,
+    // exp(-2 pi i r (k + s/2) / (Ns R)) at [(r - 1)*Ns + k]
+    const void *mtw;
 };
 
 struct DevPlan {
     int nx, ny, nz, prec;  // prec: 0 = FP32, 1 = FP64
     int zb;                // z planes per tile of the workspace
-    int gz;                // spectrum kz-fastest (z pass by wavefront-owned lines)
+    int gz;                // spectrum layout (above)
     AxisPlan ax[3];        // x, y, z
     const void *G;         // spectrum, main part
     const void *Gn;        // spectrum, kx = nx
@@ -359,11 +370,33 @@ inline hipError_t launch_plane(bool fwd, int prec, int E, int K, const LaunchArg
 // gtile * (glmax + 1) complex values, then, with args.gtw, the stage twiddles).
 hipError_t launch_generic(int mode, int prec, const LaunchArgs &args, int grid, size_t lds, hipStream_t stream);
 
+
+// Spectrum layout of a plan whose z lines of n cells are half-length lines:
+// blocked, or kx-fastest for the lengths of the radix families whose plans have
+// always kept it so.
+__host__ __device__ constexpr int mix_spectrum(int prec, int n) {
+    const bool fp32_only = n == 320 || n == 576 || n == 640 || n == 1024 || n == 1152;
+    return n == 144 || n == 160 || n == 192 || (prec != 0 && fp32_only) ? 0 : 2;
+}
+
+// Stage radices of length n on the half-length line kernels (radix[2] = 1: two
+// stages), threads per line, and the lines (by precision) and rows of a
+// workgroup; false if they do not take the length.
+struct MixInfo {
+    int radix[3];
+    int nb;
+    int tile[2];
+    int rows;
+};
+bool mix_info(int n, MixInfo &info);
+// Pass `mode` by half-length lines of n cells (x rows of n) for the problems of
+// args, whose segments count mix_info() tiles or rows.
+hipError_t launch_mix_lines(int mode, int prec, int n, const LaunchArgs &args, hipStream_t stream);
+
 // Green's-function spectrum in FP64: fills the octant (nz+1)(ny+1)(nx+1) of G
 // into `a`, applies the even-extension cosine transform along each axis (using
 // `b` as scratch) and writes the scaled result in plan precision into G / Gn.
-// gz: store kz-fastest, G at (ky*nx + kx)*(nz+1) + kz and Gn at ky*(nz+1) + kz,
-// instead of G at (kz*(ny+1) + ky)*nx + kx and Gn at kz*(ny+1) + ky.
+// gz: the layout of G and Gn (above).
 hipError_t green_spectrum(int nx, int ny, int nz, const double h[3], int prec, int gz, double *a, double *b,
                           const double *cos_x, const double *cos_y, const double *cos_z, void *G, void *Gn,
                           hipStream_t stream);

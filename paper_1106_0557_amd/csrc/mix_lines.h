@@ -1,0 +1,743 @@
+// mix_lines.h -- the five passes for axes of n = R0*R1(*R2) cells with freely
+// mixed radices (Budiardja & Cardall, arXiv:1106.0557, Sec. 2.1 and 2.2.2).
+//
+// Half-length lines.  A doubled line of 2n points whose upper half is zero is
+// two transforms of n points:
+//   Y[2j + s] = sum_{y < n} x[y] exp(-2 pi i y (j + s/2) / n),   s = 0, 1,
+// and the inverse of a doubled line of which only the first half is kept is
+// the sum of their adjoints.  s = 1 shifts the frequency by one half: in a
+// decimation-in-time transform that only replaces k by k + s/2 in the stage
+// twiddles exp(-2 pi i r (k + s/2) / (Ns R)), so the first stage (k = 0)
+// multiplies by constants and the others read a table of their own.  One half
+// of the line is in LDS at a time, half of what the doubled line takes, so a
+// compute unit holds two or more workgroups (one's memory traffic runs under
+// another's transforms) with whole 64- or 128-byte row segments.
+//
+// A line has NB threads; stage R gives thread t the butterflies t, t + NB, ...
+// of its N/R.  The inverse is the adjoint of the forward flow graph: it visits
+// the stages backwards with the same twiddles and the same LDS positions, so
+//  * a z line's spectrum values meet the product in the registers of the last
+//    stage, and the inverse starts from those registers;
+//  * each transform starts by writing the LDS positions that the same thread
+//    read last in the transform before it: no barrier between them.
+//
+// x rows (length n, the packed real form) take the s = 0 transform.
+#pragma once
+
+#include "pass_kernels.h"
+
+namespace pspfft {
+
+// Lengths N = R0*R1*R2 (R2 = 1: two stages).  Up to 256 points two stages, so
+// one LDS exchange per transform; beyond, three stages whose butterflies spread
+// over 32, 64 or 96 threads with at most 20 values per thread and few idle ones.
+// The odd factors go first: N/R0 then keeps the powers of two, which the
+// workspace's z tiles divide.
+template <int N>
+struct MixRadices {
+    static constexpr int R0 = 0, R1 = 0, R2 = 0;
+};
+#define PSPFFT_MIX_A(X)                                                                                       \
+    X(25, 5, 5, 1) X(27, 9, 3, 1) X(30, 5, 6, 1) X(45, 9, 5, 1) X(50, 5, 10, 1) X(54, 9, 6, 1)                \
+    X(60, 6, 10, 1) X(75, 15, 5, 1) X(81, 9, 9, 1) X(90, 9, 10, 1) X(100, 10, 10, 1) X(108, 9, 12, 1)         \
+    X(120, 10, 12, 1) X(125, 25, 5, 1) X(135, 15, 9, 1) X(144, 12, 12, 1)
+#define PSPFFT_MIX_B(X)                                                                                       \
+    X(150, 15, 10, 1) X(160, 10, 16, 1) X(162, 9, 18, 1) X(180, 15, 12, 1) X(192, 12, 16, 1)                  \
+    X(200, 10, 20, 1) X(216, 18, 12, 1) X(225, 15, 15, 1) X(240, 15, 16, 1) X(243, 27, 9, 1)                  \
+    X(250, 25, 10, 1) X(256, 16, 16, 1)
+#define PSPFFT_MIX_C(X)                                                                                       \
+    X(270, 9, 6, 5) X(288, 9, 8, 4) X(300, 5, 10, 6) X(320, 10, 8, 4) X(324, 9, 12, 3) X(360, 15, 6, 4)       \
+    X(375, 15, 5, 5) X(384, 12, 8, 4) X(400, 5, 16, 5) X(405, 15, 9, 3) X(432, 9, 16, 3) X(450, 15, 6, 5)     \
+    X(480, 15, 16, 2) X(486, 9, 18, 3)
+#define PSPFFT_MIX_D(X)                                                                                       \
+    X(500, 5, 10, 10) X(512, 16, 8, 4) X(540, 9, 10, 6) X(576, 9, 16, 4) X(600, 15, 10, 4)                    \
+    X(625, 25, 25, 1) X(640, 10, 16, 4) X(648, 9, 18, 4) X(675, 15, 9, 5) X(720, 15, 12, 4) X(729, 9, 9, 9)   \
+    X(750, 15, 10, 5)
+#define PSPFFT_MIX_E(X)                                                                                       \
+    X(768, 12, 16, 4) X(800, 5, 16, 10) X(810, 15, 9, 6) X(864, 9, 16, 6) X(900, 15, 15, 4)                   \
+    X(960, 15, 16, 4) X(972, 9, 18, 6) X(1000, 5, 20, 10) X(1024, 16, 16, 4) X(1080, 15, 12, 6)               \
+    X(1125, 15, 15, 5) X(1152, 12, 8, 12)
+#define PSPFFT_MIX_ALL(X) PSPFFT_MIX_A(X) PSPFFT_MIX_B(X) PSPFFT_MIX_C(X) PSPFFT_MIX_D(X) PSPFFT_MIX_E(X)
+#define PSPFFT_MIX_RADICES(N, A, B, C)                          \
+    template <>                                                 \
+    struct MixRadices<N> {                                      \
+        static constexpr int R0 = A, R1 = B, R2 = C;            \
+        static_assert(A * B * C == N, "radices of the length"); \
+    };
+PSPFFT_MIX_ALL(PSPFFT_MIX_RADICES)
+#undef PSPFFT_MIX_RADICES
+
+constexpr int mix_max(int a, int b) { return a > b ? a : b; }
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Stage geometry of a length: butterflies n0, n1, nL and rounds d0, d1, dL of
+// the first, second and last stage, values per thread V (any stage).
+template <int N_>
+struct MixLen {
+    using R = MixRadices<N_>;
+    static constexpr int N = N_, R0 = R::R0, R1 = R::R1, R2 = R::R2;
+    static constexpr int ST = R2 > 1 ? 3 : 2;
+    static constexpr int RL = ST == 3 ? R2 : R1;
+    // threads per line
+    static constexpr int NB = ST == 2 ? mix_max(R0, R1) : (N <= 540 ? 32 : (N <= 1024 ? 64 : 96));
+    static constexpr int n0 = N / R0, n1 = N / R1, nL = N / RL;
+    static constexpr int d0 = ceil_div(n0, NB), d1 = ceil_div(n1, NB), dL = ceil_div(nL, NB);
+    static constexpr int V0 = d0 * R0, VL = dL * RL;
+    static constexpr int V = mix_max(mix_max(V0, VL), d1 * R1);
+    static constexpr int NTW = N - R0;  // stage twiddles of one s
+    static constexpr int off_last = ST == 3 ? R0 * (R1 - 1) : 0;
+};
+
+// Column tiles (lines per workgroup): 128-byte row segments (16 lines in FP32,
+// 8 in FP64) where two workgroups share a CU, the workgroup stays at 512
+// threads and, in FP32, the values of a thread fit the registers that leaves;
+// else 64-byte ones.  Measured, z pass of one solve: FP32 384^3 16 lines 0.51
+// ms, 8 lines 0.54; 480^3 (18 values a thread) 16 lines 1.16 ms, 8 lines 1.06.
+template <typename T, int N>
+struct MixTile {
+    using G = MixLen<N>;
+    static constexpr int CSZ = static_cast<int>(sizeof(cx<T>));
+    static constexpr bool F32 = sizeof(T) == 4;
+    static constexpr int lds(int tile) { return (N * tile + 2 * G::NTW) * CSZ; }
+    static constexpr bool fits(int tile) {
+        return 2 * lds(tile) <= 160 * 1024 && tile * G::NB <= 512 && (!F32 || G::ST == 2 || tile < 16 || G::V <= 16);
+    }
+    static constexpr int full = 128 / CSZ;
+    static constexpr int TILE = fits(full) ? full : full / 2;
+    static constexpr int BLOCK = TILE * G::NB;
+    static constexpr size_t LDS = static_cast<size_t>(lds(TILE));
+    static_assert(BLOCK <= 1024 && LDS <= 160 * 1024, "one workgroup fits");
+    // wavefronts per SIMD the z kernel is compiled for
+    static constexpr int WPS = G::ST == 2 ? 1 : (F32 ? (BLOCK == 512 ? 4 : (BLOCK <= 256 ? 3 : 1)) : 2);
+};
+
+// x rows per workgroup: about 256 threads.  LDS row stride: positions P at
+// P + P/R0 for even R0 (consecutive butterflies then start on different banks).
+template <typename T, int N>
+struct MixRow {
+    using G = MixLen<N>;
+    static constexpr int CSZ = static_cast<int>(sizeof(cx<T>));
+    static constexpr int PAD = G::R0 % 2 == 0 ? 1 : 0;
+    static constexpr int RP = G::R0 + PAD;
+    static constexpr int S = (N / G::R0 * RP) | 1;
+    static constexpr int ROWS = mix_max(1, 256 / G::NB);
+    static constexpr int BLOCK = ROWS * G::NB;
+    // rows, stage twiddles (s = 0), split factors
+    static constexpr size_t LDS = static_cast<size_t>(ROWS * S + G::NTW + N) * CSZ;
+    static_assert(LDS <= 160 * 1024, "one workgroup fits");
+};
+
+// The transforms of one line, N = R0*R1(*R2).  LDS position P of the line is at
+// pos(P)*LW from `col`; PAD as in MixRow (0: columns).
+template <typename T, int N, int LW, int PAD>
+struct MixFFT {
+    using G = MixLen<N>;
+    static constexpr int NB = G::NB;
+    static constexpr int RP = G::R0 + PAD;
+
+    // butterflies t, t + NB, ... of a stage of radix R: f(round, butterfly)
+    template <int R, typename F>
+    static __device__ __forceinline__ void each(int t, F &&f) {
+        constexpr int nb = N / R, D = ceil_div(nb, NB);
+        sfor<0, D>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const int b = t + NB * i;
+            if constexpr ((i + 1) * NB <= nb) f(ic, b);
+            else if (b < nb) f(ic, b);
+        });
+    }
+    // positions b*R0 + r (after the first stage)
+    static __device__ __forceinline__ int out0(int b) { return b * RP * LW; }
+    // positions b + r*(N/R): base and step (N/R is a multiple of R0 past the first stage)
+    static __device__ __forceinline__ int in(int b) { return (PAD ? b + b / G::R0 : b) * LW; }
+    template <int R>
+    static constexpr int in_step() { return N / R / G::R0 * RP * LW; }
+    // positions q*R0*R1 + k + r*R0 with b = q*R0 + k (after the second of three stages)
+    static __device__ __forceinline__ int out1(int b) {
+        const int q = b / G::R0, k = b - q * G::R0;
+        return (q * G::R1 * RP + k) * LW;
+    }
+
+    // Forward transform s of x (first-stage positions b + r*n0 in x[i*R0 + r]);
+    // the result is left in v at the last stage's positions b + r*nL.  tw: the
+    // table of s, twiddle r of k at [(r - 1)*Ns + k].
+    template <int SH, typename TP>
+    static __device__ __forceinline__ void fwd(const cx<T> *x, cx<T> *v, cx<T> *col, TP tw, int t) {
+        each<G::R0>(t, [&](auto ic, int b) {
+            constexpr int i = decltype(ic)::value;
+            cx<T> u[G::R0];
+            sfor<0, G::R0>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                u[r] = rot<2 * G::R0, -1, SH * r>(x[i * G::R0 + r]);
+            });
+            dft<G::R0, -1>(u);
+            cx<T> *p = col + out0(b);
+            sfor<0, G::R0>([&](auto rc) { constexpr int r = decltype(rc)::value; p[r * LW] = u[r]; });
+        });
+        __syncthreads();
+        if constexpr (G::ST == 3) {
+            each<G::R1>(t, [&](auto ic, int b) {
+                constexpr int i = decltype(ic)::value;
+                const cx<T> *p = col + in(b);
+                sfor<0, G::R1>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    v[i * G::R1 + r] = p[r * in_step<G::R1>()];
+                });
+            });
+            __syncthreads();
+            each<G::R1>(t, [&](auto ic, int b) {
+                constexpr int i = decltype(ic)::value;
+                const int k = b % G::R0;
+                cx<T> u[G::R1];
+                u[0] = v[i * G::R1];
+                sfor<1, G::R1>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    u[r] = cmul(v[i * G::R1 + r], tw_at(tw, (r - 1) * G::R0 + k));
+                });
+                dft<G::R1, -1>(u);
+                cx<T> *p = col + out1(b);
+                sfor<0, G::R1>([&](auto rc) { constexpr int r = decltype(rc)::value; p[r * RP * LW] = u[r]; });
+            });
+            __syncthreads();
+        }
+        each<G::RL>(t, [&](auto ic, int b) {
+            constexpr int i = decltype(ic)::value;
+            const cx<T> *p = col + in(b);
+            cx<T> u[G::RL];
+            u[0] = p[0];
+            sfor<1, G::RL>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                u[r] = cmul(p[r * in_step<G::RL>()], tw_at(tw, G::off_last + (r - 1) * G::nL + b));
+            });
+            dft<G::RL, -1>(u);
+            sfor<0, G::RL>([&](auto rc) { constexpr int r = decltype(rc)::value; v[i * G::RL + r] = u[r]; });
+        });
+    }
+
+    // Adjoint of fwd: v (last-stage positions, overwritten) to first-stage positions in o,
+    // added to what is there if ADD.
+    template <int SH, bool ADD, typename TP>
+    static __device__ __forceinline__ void inv(cx<T> *v, cx<T> *o, cx<T> *col, TP tw, int t) {
+        each<G::RL>(t, [&](auto ic, int b) {
+            constexpr int i = decltype(ic)::value;
+            cx<T> u[G::RL];
+            sfor<0, G::RL>([&](auto rc) { constexpr int r = decltype(rc)::value; u[r] = v[i * G::RL + r]; });
+            dft<G::RL, 1>(u);
+            cx<T> *p = col + in(b);
+            p[0] = u[0];
+            sfor<1, G::RL>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                p[r * in_step<G::RL>()] = cmulc(u[r], tw_at(tw, G::off_last + (r - 1) * G::nL + b));
+            });
+        });
+        __syncthreads();
+        if constexpr (G::ST == 3) {
+            each<G::R1>(t, [&](auto ic, int b) {
+                constexpr int i = decltype(ic)::value;
+                const cx<T> *p = col + out1(b);
+                sfor<0, G::R1>([&](auto rc) { constexpr int r = decltype(rc)::value; v[i * G::R1 + r] = p[r * RP * LW]; });
+            });
+            __syncthreads();
+            each<G::R1>(t, [&](auto ic, int b) {
+                constexpr int i = decltype(ic)::value;
+                const int k = b % G::R0;
+                cx<T> u[G::R1];
+                sfor<0, G::R1>([&](auto rc) { constexpr int r = decltype(rc)::value; u[r] = v[i * G::R1 + r]; });
+                dft<G::R1, 1>(u);
+                cx<T> *p = col + in(b);
+                p[0] = u[0];
+                sfor<1, G::R1>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    p[r * in_step<G::R1>()] = cmulc(u[r], tw_at(tw, (r - 1) * G::R0 + k));
+                });
+            });
+            __syncthreads();
+        }
+        each<G::R0>(t, [&](auto ic, int b) {
+            constexpr int i = decltype(ic)::value;
+            cx<T> u[G::R0];
+            const cx<T> *p = col + out0(b);
+            sfor<0, G::R0>([&](auto rc) { constexpr int r = decltype(rc)::value; u[r] = p[r * LW]; });
+            dft<G::R0, 1>(u);
+            sfor<0, G::R0>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                const cx<T> w = rot<2 * G::R0, 1, SH * r>(u[r]);
+                if constexpr (ADD) o[i * G::R0 + r] = o[i * G::R0 + r] + w;
+                else o[i * G::R0 + r] = w;
+            });
+        });
+    }
+};
+
+// Problem and tile of a workgroup (segments are numbered tile-major, so that
+// problems sharing a plan read one spectrum slice together).
+struct MixJob {
+    const ProbArg *pa;
+    int local;
+    bool nyq;
+};
+__device__ __forceinline__ MixJob mix_job(const LaunchArgs &args, int bid) {
+    int sgi = 0;
+    while (sgi + 1 < args.nseg && bid >= args.seg[sgi + 1].wg_begin) ++sgi;
+    const Segment &sg = args.seg[sgi];
+    int local = bid - sg.wg_begin;
+    const int member = local % sg.group;
+    local /= sg.group;
+    const bool nyq = local >= sg.wg_main;
+    return MixJob{&args.p[sg.first + member], nyq ? local - sg.wg_main : local, nyq};
+}
+
+// A lane's line: position p at base + p*step + lane bytes, base and step the same for the
+// whole workgroup; the lane's own share (its line and its thread's first position t) in 32 bits.
+template <typename T>
+struct MixLine {
+    char *base;
+    size_t step;     // bytes between positions
+    uint32_t lane;   // bytes: line within the workgroup's base, and position t
+    bool active;
+    __device__ __forceinline__ cx<T> &at(int p) const {
+        return *reinterpret_cast<cx<T> *>(base + static_cast<size_t>(p) * step + lane);
+    }
+};
+
+// z lines.  Rows ky and 2ny - ky read the same spectrum values, so the lines are numbered pair
+// by pair of such rows ((0, ny) first), and within a pair by runs of TILE adjacent kx of the
+// one row, then of the other: tiles that share spectrum values are neighbours.
+template <typename T, int N, int GL>
+struct MixZ {
+    MixLine<T> ln;
+    const gbl<const T> *g;  // this line's spectrum values: unit u between kz of one parity, o1 the odd ones
+    size_t u, o1;
+};
+
+template <typename T, int N, int TILE, int GL>
+__device__ __forceinline__ MixZ<T, N, GL> mix_z_line(const LaunchArgs &args, int bid, int c, int t) {
+    using cplan = const __attribute__((address_space(4))) DevPlan;
+    constexpr size_t CSZ = sizeof(cx<T>);
+    const MixJob job = mix_job(args, bid);
+    const auto &pl = *(cplan *)job.pa->plan;
+    const int nx = pl.nx, ny = pl.ny;
+    const int g = job.local * TILE + c;
+    MixZ<T, N, GL> z;
+    int ky, kx;
+    size_t gb;
+    if (!job.nyq) {
+        z.ln.active = g < 2 * ny * nx;
+        const int gg = z.ln.active ? g : 0;
+        const int pr = gg / (2 * nx), l = gg - pr * 2 * nx;
+        const int j = l / (2 * TILE), rem = l - j * 2 * TILE, w = min(TILE, nx - j * TILE);
+        const bool second = rem >= w;
+        kx = j * TILE + rem - (second ? w : 0);
+        ky = pr == 0 ? (second ? ny : 0) : (second ? 2 * ny - pr : pr);
+        const int zb = pl.zb, sh = __builtin_ctz(static_cast<unsigned>(zb));
+        const size_t plane = static_cast<size_t>(2) * ny * nx;
+        z.ln.base = static_cast<char *>(job.pa->W);
+        z.ln.step = plane * CSZ;  // zb divides NB and n0: whole tiles from one first-stage register to the next
+        z.ln.lane = static_cast<uint32_t>(
+            ((static_cast<size_t>(t >> sh) << sh) * plane + (static_cast<size_t>(ky) * zb + (t & (zb - 1))) * nx + kx) * CSZ);
+    } else {
+        z.ln.active = g < 2 * ny;
+        ky = z.ln.active ? g : 0;
+        kx = nx;
+        z.ln.base = static_cast<char *>(job.pa->Wn);
+        z.ln.step = static_cast<size_t>(2) * ny * CSZ;
+        z.ln.lane = static_cast<uint32_t>((static_cast<size_t>(t) * 2 * ny + ky) * CSZ);
+    }
+    const int kyo = ky <= ny ? ky : 2 * ny - ky;
+    if constexpr (GL == 2) {
+        z.u = job.nyq ? 1 : kGroup;
+        z.o1 = (N / 2 + 1) * z.u;
+        gb = job.nyq ? static_cast<size_t>(kyo) * (N + 1)
+                     : (static_cast<size_t>(kyo) * ((nx + kGroup - 1) / kGroup) + kx / kGroup) * (kGroup * (N + 1)) + kx % kGroup;
+    } else {
+        const size_t s = job.nyq ? ny + 1 : static_cast<size_t>(ny + 1) * nx;
+        z.u = 2 * s;
+        z.o1 = s;
+        gb = job.nyq ? kyo : static_cast<size_t>(kyo) * nx + kx;
+    }
+    z.g = as_global(static_cast<const T *>(job.nyq ? pl.Gn : pl.G)) + gb;
+    return z;
+}
+
+// Spectrum values of transform s at the last stage's positions p = b + r*nL: kz = 2p + s, even about n.
+template <typename T, int N, int GL, int SH>
+__device__ __forceinline__ void mix_load_g(const MixZ<T, N, GL> &z, T *gv, int t) {
+    using G = MixLen<N>;
+    using F = MixFFT<T, N, 1, 0>;
+    F::template each<G::RL>(t, [&](auto ic, int b) {
+        constexpr int i = decltype(ic)::value;
+        const gbl<const T> *up = z.g + SH * z.o1 + b * z.u;
+        const gbl<const T> *dn = z.g + SH * z.o1 - b * z.u;
+        sfor<0, G::RL>([&](auto rc) {
+            constexpr int r = decltype(rc)::value;
+            constexpr int p0 = r * G::nL, p1 = p0 + G::nL - 1;  // positions of the butterflies
+            const gbl<const T> *a = up + p0 * z.u, *m = dn + (N - p0 - SH) * z.u;
+            if constexpr (2 * p1 + SH <= N) gv[i * G::RL + r] = *a;
+            else if constexpr (2 * p0 + SH > N) gv[i * G::RL + r] = *m;
+            else gv[i * G::RL + r] = 2 * (p0 + b) + SH <= N ? *a : *m;
+        });
+    });
+}
+
+// Column passes.  MODE Z_CONV: PERSIST lets one workgroup per CU walk its tiles (lines too long
+// for two): the next tile's line is loaded into the registers of this one's as soon as its second
+// transform has read them, ahead of the stores (loads and stores retire in order, so no wait for
+// the line covers them; lanes without a line store past the buffer's range).
+template <typename T, int N, int MODE, int GL, bool PERSIST>
+__global__ void __launch_bounds__((MixTile<T, N>::BLOCK), (MODE == Z_CONV ? MixTile<T, N>::WPS : 1))
+mix_col_kernel(const LaunchArgs args) {
+    using G = MixLen<N>;
+    using C = MixTile<T, N>;
+    constexpr int TILE = C::TILE, NB = G::NB;
+    using F = MixFFT<T, N, TILE, 0>;
+    extern __shared__ __align__(16) unsigned char smem[];
+    cx<T> *lds = reinterpret_cast<cx<T> *>(smem);
+    TileWalk walk = tile_walk<true>();
+    int bid = walk.tile();
+    if (bid >= args.nwg) return;
+    const int tid = static_cast<int>(threadIdx.x);
+    int c = tid % TILE, t = tid / TILE;  // adjacent lanes on adjacent lines
+    const AxisPlan &ax = args.p[0].plan->ax[MODE == Z_CONV ? 2 : 1];
+    cx<T> *twl = lds + N * TILE;
+    copy_to_lds<T>(twl, ax.mtw, 2 * G::NTW);
+    const cx<T> *tw0 = twl, *tw1 = twl + G::NTW;
+
+    if constexpr (MODE == Z_CONV) {
+        cx<T> x[G::V0], v[G::V], e[G::V0];
+        T gv[G::VL];
+        auto load = [&](const MixZ<T, N, GL> &z) __attribute__((always_inline)) {
+            F::template each<G::R0>(t, [&](auto ic, int) {
+                constexpr int i = decltype(ic)::value;
+                sfor<0, G::R0>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    x[i * G::R0 + r] = z.ln.at(i * NB + r * G::n0);
+                });
+            });
+        };
+        auto multiply = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int m = 0; m < G::VL; ++m) v[m] = scale(v[m], gv[m]);
+        };
+        auto cur = mix_z_line<T, N, TILE, GL>(args, bid, c, t);
+        load(cur);
+        mix_load_g<T, N, GL, 0>(cur, gv, t);
+        if constexpr (PERSIST) __builtin_amdgcn_s_waitcnt(0x0f70);  // nothing outstanding on entry (vmcnt 0)
+        __syncthreads();  // twiddles visible
+        for (;;) {
+            if constexpr (PERSIST) asm volatile("" : "+v"(t), "+v"(c));  // addresses are derived again per tile
+            F::template fwd<0>(x, v, lds + c, tw0, t);
+            multiply();
+            mix_load_g<T, N, GL, 1>(cur, gv, t);
+            F::template inv<0, false>(v, e, lds + c, tw0, t);
+            F::template fwd<1>(x, v, lds + c, tw1, t);
+            multiply();
+            auto nxt = cur;
+            bool more = false;
+            if constexpr (PERSIST) {
+                walk.i += walk.step;
+                const int nb = walk.tile();
+                more = nb < args.nwg;
+                bid = more ? nb : bid;
+                nxt = mix_z_line<T, N, TILE, GL>(args, bid, c, t);
+                load(nxt);
+                mix_load_g<T, N, GL, 0>(nxt, gv, t);
+            }
+            F::template inv<1, true>(v, e, lds + c, tw1, t);
+            if constexpr (PERSIST) {
+                const uint32_t bytes = static_cast<uint32_t>(NB * cur.ln.step);
+                F::template each<G::R0>(t, [&](auto ic, int) {
+                    constexpr int i = decltype(ic)::value;
+                    sfor<0, G::R0>([&](auto rc) {
+                        constexpr int r = decltype(rc)::value;
+                        buffer_store<T>(e[i * G::R0 + r], cur.ln.base + static_cast<size_t>(i * NB + r * G::n0) * cur.ln.step,
+                                        bytes, cur.ln.active ? cur.ln.lane : 0xfffffff0u);
+                    });
+                });
+                if (!more) break;
+                cur = nxt;
+            } else {
+                if (cur.ln.active)
+                    F::template each<G::R0>(t, [&](auto ic, int) {
+                        constexpr int i = decltype(ic)::value;
+                        sfor<0, G::R0>([&](auto rc) {
+                            constexpr int r = decltype(rc)::value;
+                            cur.ln.at(i * NB + r * G::n0) = e[i * G::R0 + r];
+                        });
+                    });
+                break;
+            }
+        }
+    } else {
+        // y lines: line (z, kx) has position y at w_row(z, y) + kx; the Nyquist line of plane z is
+        // contiguous in Wn.  Two lanes' worth of addresses: positions t + ... and 2t + ... (the
+        // doubled side of the transform)
+        using cplan = const __attribute__((address_space(4))) DevPlan;
+        constexpr size_t CSZ = sizeof(cx<T>);
+        const MixJob job = mix_job(args, bid);
+        const auto &pl = *(cplan *)job.pa->plan;
+        const int nx = pl.nx, ny = pl.ny, nz = pl.nz, zb = pl.zb;
+        const int g0 = job.local * TILE, g = g0 + c;
+        MixLine<T> one, two;
+        uint32_t lane;
+        if (!job.nyq) {
+            one.active = g < nz * nx;
+            const int gg = one.active ? g : g0;
+            const int z0 = g0 / nx, z = gg / nx, kx = gg - z * nx;
+            const size_t row0 = w_row(z0, 0, ny, nx, zb);
+            one.base = static_cast<char *>(job.pa->W) + row0 * CSZ;
+            one.step = static_cast<size_t>(zb) * nx * CSZ;
+            lane = static_cast<uint32_t>((w_row(z, 0, ny, nx, zb) - row0 + kx) * CSZ);
+        } else {
+            one.active = g < nz;
+            one.base = static_cast<char *>(job.pa->Wn);
+            one.step = CSZ;
+            lane = static_cast<uint32_t>(static_cast<size_t>(one.active ? g : g0) * 2 * ny * CSZ);
+        }
+        two = one;
+        one.lane = lane + static_cast<uint32_t>(t * one.step);
+        two.lane = lane + static_cast<uint32_t>(2 * t * one.step);
+        cx<T> x[G::V0], v[G::V];
+        auto load2 = [&](cx<T> *q, auto sc) __attribute__((always_inline)) {
+            constexpr int s = decltype(sc)::value;
+            F::template each<G::RL>(t, [&](auto ic, int) {
+                constexpr int i = decltype(ic)::value;
+                sfor<0, G::RL>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    q[i * G::RL + r] = two.at(2 * (i * NB + r * G::nL) + s);
+                });
+            });
+        };
+        auto store2 = [&](auto sc) __attribute__((always_inline)) {
+            constexpr int s = decltype(sc)::value;
+            if (one.active)
+                F::template each<G::RL>(t, [&](auto ic, int) {
+                    constexpr int i = decltype(ic)::value;
+                    sfor<0, G::RL>([&](auto rc) {
+                        constexpr int r = decltype(rc)::value;
+                        two.at(2 * (i * NB + r * G::nL) + s) = v[i * G::RL + r];
+                    });
+                });
+        };
+        constexpr std::integral_constant<int, 0> even{};
+        constexpr std::integral_constant<int, 1> odd{};
+        if constexpr (MODE == Y_FWD) {
+            F::template each<G::R0>(t, [&](auto ic, int) {
+                constexpr int i = decltype(ic)::value;
+                sfor<0, G::R0>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    x[i * G::R0 + r] = one.at(i * NB + r * G::n0);
+                });
+            });
+            __syncthreads();  // twiddles visible
+            F::template fwd<0>(x, v, lds + c, tw0, t);
+            store2(even);  // every row of the line is in registers since the transform's first barrier
+            __syncthreads();
+            F::template fwd<1>(x, v, lds + c, tw1, t);
+            store2(odd);
+        } else {
+            cx<T> w[G::V];
+            load2(v, even);
+            load2(w, odd);
+            __syncthreads();
+            F::template inv<0, false>(v, x, lds + c, tw0, t);
+            __syncthreads();
+            F::template inv<1, true>(w, x, lds + c, tw1, t);
+            if (one.active)
+                F::template each<G::R0>(t, [&](auto ic, int) {
+                    constexpr int i = decltype(ic)::value;
+                    sfor<0, G::R0>([&](auto rc) {
+                        constexpr int r = decltype(rc)::value;
+                        one.at(i * NB + r * G::n0) = x[i * G::R0 + r];
+                    });
+                });
+        }
+    }
+}
+
+// Row passes: rows r = z*ny + y of S / Phi, packed u[j] = s[2j] + i s[2j+1] (zero for 2j >= nx),
+// a transform of N = nx points and the split step with exp(-i pi k / n), as in the other row
+// kernels.  Consecutive lanes walk along a row.
+template <typename T, int N, int MODE>
+__global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const LaunchArgs args) {
+    using G = MixLen<N>;
+    using C = MixRow<T, N>;
+    constexpr int NB = G::NB, ROWS = C::ROWS, S = C::S;
+    constexpr int J = (N + 1) / 2;  // packed values of a source row
+    using F = MixFFT<T, N, 1, C::PAD>;
+    extern __shared__ __align__(16) unsigned char smem[];
+    cx<T> *lds = reinterpret_cast<cx<T> *>(smem);
+    const int bid = tile_walk<true>().tile();
+    if (bid >= args.nwg) return;
+    const int tid = static_cast<int>(threadIdx.x), c = tid / NB, t = tid % NB;
+    const AxisPlan &ax = args.p[0].plan->ax[0];
+    cx<T> *twl = lds + ROWS * S, *post = twl + G::NTW;
+    copy_to_lds<T>(twl, ax.mtw, G::NTW);
+    copy_to_lds<T>(post, ax.post, N);
+    const MixJob job = mix_job(args, bid);
+    const DevPlan &pl = *job.pa->plan;
+    const int ny = pl.ny, nz = pl.nz;
+    const int g = job.local * ROWS + c;
+    const bool active = g < ny * nz;
+    const int z = active ? g / ny : 0, y = active ? g - z * ny : 0;
+    cx<T> *wrow = static_cast<cx<T> *>(job.pa->W) + w_row(z, y, ny, N, pl.zb);
+    cx<T> *wnyq = static_cast<cx<T> *>(job.pa->Wn) + static_cast<size_t>(z) * 2 * ny + y;
+    cx<T> *row = lds + c * S;
+    const size_t f0 = static_cast<size_t>(active ? g : 0) * N;
+    // LDS slot of position P (MixFFT's layout)
+    auto slot = [](int P) { return C::PAD ? P + P / G::R0 : P; };
+    cx<T> x[G::V0], v[G::V];
+    if constexpr (MODE == X_FWD) {
+        const T *s = static_cast<const T *>(job.pa->S) + f0;
+        F::template each<G::R0>(t, [&](auto ic, int b) {
+            constexpr int i = decltype(ic)::value;
+            sfor<0, G::R0>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                const int j = b + r * G::n0;
+                cx<T> u = {T(0), T(0)};
+                if constexpr (r * G::n0 < J) {
+                    if ((r + 1) * G::n0 <= N / 2 || j < J) {
+                        if constexpr (N % 2 == 0) {
+                            u = reinterpret_cast<const cx<T> *>(s)[j];
+                        } else {  // odd rows: single reals, the last value has no partner
+                            u.x = s[2 * j];
+                            if (2 * j + 1 < N) u.y = s[2 * j + 1];
+                        }
+                    }
+                }
+                x[i * G::R0 + r] = u;
+            });
+        });
+        __syncthreads();  // tables visible
+        F::template fwd<0>(x, v, row, static_cast<const cx<T> *>(twl), t);
+        // split: X[k] = (U[k] + U*[n-k])/2 - (i/2) exp(-i pi k/n) (U[k] - U*[n-k])
+        F::template each<G::RL>(t, [&](auto ic, int b) {
+            constexpr int i = decltype(ic)::value;
+            cx<T> *p = row + F::in(b);
+            sfor<0, G::RL>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                p[r * F::template in_step<G::RL>()] = v[i * G::RL + r];
+            });
+        });
+        __syncthreads();
+        if (active)
+            F::template each<G::RL>(t, [&](auto ic, int b) {
+                constexpr int i = decltype(ic)::value;
+                sfor<0, G::RL>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    const int k = b + r * G::nL;
+                    const cx<T> u = v[i * G::RL + r], w = row[slot(k == 0 ? 0 : N - k)];
+                    const cx<T> a = {static_cast<T>(0.5) * (u.x + w.x), static_cast<T>(0.5) * (u.y - w.y)};
+                    const cx<T> d = {static_cast<T>(0.5) * (u.x - w.x), static_cast<T>(0.5) * (u.y + w.y)};
+                    const cx<T> ed = cmul(post[k], d);
+                    wrow[k] = cx<T>{a.x + ed.y, a.y - ed.x};  // a - i e d
+                    if (k == 0) *wnyq = cx<T>{u.x - u.y, T(0)};
+                });
+            });
+    } else {
+        cx<T> xn = {T(0), T(0)};
+        F::template each<G::RL>(t, [&](auto ic, int b) {
+            constexpr int i = decltype(ic)::value;
+            sfor<0, G::RL>([&](auto rc) { constexpr int r = decltype(rc)::value; v[i * G::RL + r] = wrow[b + r * G::nL]; });
+        });
+        if (t == 0) xn = *wnyq;
+        F::template each<G::RL>(t, [&](auto ic, int b) {
+            constexpr int i = decltype(ic)::value;
+            cx<T> *p = row + F::in(b);
+            sfor<0, G::RL>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                p[r * F::template in_step<G::RL>()] = v[i * G::RL + r];
+            });
+        });
+        __syncthreads();  // row values and tables visible
+        // U[k] = (X[k] + X*[n-k]) + i exp(+i pi k/n) (X[k] - X*[n-k]), k < n; X[n] for k = 0
+        F::template each<G::RL>(t, [&](auto ic, int b) {
+            constexpr int i = decltype(ic)::value;
+            sfor<0, G::RL>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                const int k = b + r * G::nL;
+                const cx<T> a = v[i * G::RL + r], m = k == 0 ? xn : row[slot(N - k)];
+                const cx<T> sm = {a.x + m.x, a.y - m.y}, df = {a.x - m.x, a.y + m.y};
+                const cx<T> ed = cmulc(df, post[k]);
+                v[i * G::RL + r] = cx<T>{sm.x - ed.y, sm.y + ed.x};
+            });
+        });
+        __syncthreads();  // partners read
+        F::template inv<0, false>(v, x, row, static_cast<const cx<T> *>(twl), t);
+        if (active) {
+            T *f = static_cast<T *>(job.pa->Phi) + f0;
+            F::template each<G::R0>(t, [&](auto ic, int b) {
+                constexpr int i = decltype(ic)::value;
+                sfor<0, G::R0>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    const int j = b + r * G::n0;
+                    if constexpr (r * G::n0 < J) {
+                        if ((r + 1) * G::n0 <= N / 2 || j < J) {
+                            if constexpr (N % 2 == 0) {
+                                reinterpret_cast<cx<T> *>(f)[j] = x[i * G::R0 + r];
+                            } else {
+                                f[2 * j] = x[i * G::R0 + r].x;
+                                if (2 * j + 1 < N) f[2 * j + 1] = x[i * G::R0 + r].y;
+                            }
+                        }
+                    }
+                });
+            });
+        }
+    }
+}
+
+// z passes that run persistently: lines beyond 1024 points in FP32 (one workgroup per CU).
+// Measured, z pass of 576 x 576 lines of 1152 points: 7.2 ms with two one-tile workgroups of
+// 4 lines per CU, 5.7 ms persistently with 8.
+template <typename T, int N>
+constexpr bool mix_z_persist() { return sizeof(T) == 4 && N > 1024; }
+
+template <typename T, int N>
+hipError_t launch_mix(int mode, const LaunchArgs &args, hipStream_t stream) {
+    constexpr int kMaxDevices = 64;
+    static int cus[kMaxDevices] = {0};
+    constexpr bool PZ = mix_z_persist<T, N>();
+    constexpr int GL = mix_spectrum(sizeof(T) == 4 ? 0 : 1, N);
+    void (*const fn[5])(LaunchArgs) = {mix_row_kernel<T, N, X_FWD>, mix_col_kernel<T, N, Y_FWD, GL, false>,
+                                       mix_col_kernel<T, N, Z_CONV, GL, PZ>, mix_col_kernel<T, N, Y_INV, GL, false>,
+                                       mix_row_kernel<T, N, X_INV>};
+    if (mode < 0 || mode > 4) return hipErrorInvalidValue;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    if (cus[dev] == 0) {
+        for (auto f : fn) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    160 * 1024);
+            if (e != hipSuccess) return e;
+        }
+        int n = 0;
+        e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        cus[dev] = n > 0 ? n : 1;
+    }
+    const bool row = mode == X_FWD || mode == X_INV;
+    const int block = row ? MixRow<T, N>::BLOCK : MixTile<T, N>::BLOCK;
+    const size_t lds = row ? MixRow<T, N>::LDS : MixTile<T, N>::LDS;
+    // whole rounds of the chunked tile order, or one persistent workgroup per CU
+    int grid = (args.nwg + 8 * kTileChunk - 1) / (8 * kTileChunk) * (8 * kTileChunk);
+    if (mode == Z_CONV && PZ && grid > cus[dev]) grid = cus[dev];
+    hipLaunchKernelGGL(fn[mode], dim3(grid), dim3(block), lds, stream, args);
+    return hipGetLastError();
+}
+
+}  // namespace pspfft
+
+// One translation unit per precision and list of lengths keeps compiles parallel.
+#define PSPFFT_MIX_LAUNCH(N, A, B, C) case N: return launch_mix<MixReal, N>(mode, args, stream);
+#define PSPFFT_MIX_UNIT(T, NAME, LIST)                                                   \
+    namespace pspfft {                                                                   \
+    hipError_t NAME(int n, int mode, const LaunchArgs &args, hipStream_t stream) {       \
+        using MixReal = T;                                                               \
+        switch (n) {                                                                     \
+            LIST(PSPFFT_MIX_LAUNCH)                                                      \
+            default: return hipErrorInvalidValue;                                        \
+        }                                                                                \
+    }                                                                                    \
+    }

@@ -17,6 +17,7 @@
 #include <mutex>
 #include <tuple>
 #include <new>
+#include <string>
 #include <utility>
 #include <numeric>
 #include <vector>
@@ -319,6 +320,51 @@ bool build_axis(int axis, int n, pspfft_precision prec, AxisPlan &ax, std::vecto
     return Ns == L;
 }
 
+// The axis of a mesh runs on half-length lines (mix_lines.h): the lengths of
+// mix_info() that no radix family takes, where a lane's share of an address
+// fits 32 bits (z: one first-stage position block of NB planes; y: the planes
+// that a tile's lines span, in tiles of up to 16).  Every such size moves to
+// that kernel: measured, one FP32 solve, against the generic line kernel, 480^3
+// 12.0 -> 4.4 ms, eight 120^3 946 -> 330 us.
+bool mix_axis(int axis, const int n[3], pspfft_precision prec, pspfft::MixInfo &info) {
+    if (!pspfft::mix_info(n[axis], info)) return false;
+    if (family_axis(axis, n[axis], prec)) {
+        const char *e = std::getenv(axis == 0 ? "DEVMIX_X" : axis == 1 ? "DEVMIX_Y" : "DEVMIX_Z");
+        if (!e || n[axis] < std::atoi(e)) return false;
+    }
+    const size_t lim = (size_t(1) << 32) - 64, cs = cplx_size(prec), nx = n[0], ny = n[1];
+    if (axis == 2) return info.nb * 2 * ny * nx * cs < lim;
+    if (axis == 1) return ((16 / nx + 2 + 16) * 2 * ny * nx + size_t(2) * info.nb * 16 * nx) * cs < lim;
+    return true;
+}
+
+// Appends the stage twiddles of half-length lines (AxisPlan::mtw).
+void mix_twiddles(const pspfft::MixInfo &info, std::vector<std::complex<double>> &tw) {
+    for (int s = 0; s < 2; ++s) {
+        int Ns = info.radix[0];
+        for (int st = 1; st < 3 && info.radix[st] > 1; ++st) {
+            const int R = info.radix[st];
+            for (int r = 1; r < R; ++r)
+                for (int k = 0; k < Ns; ++k) {
+                    double c, sn;
+                    turn(-static_cast<long>(r) * (2 * k + s), 2L * Ns * R, c, sn);
+                    tw.emplace_back(c, sn);
+                }
+            Ns *= R;
+        }
+    }
+}
+
+// Spectrum layout (DevPlan::gz 2) and size: values of G and of Gn.
+bool mix_spectrum_blocked(const int n[3], pspfft_precision prec) {
+    pspfft::MixInfo info;
+    return mix_axis(2, n, prec, info) && pspfft::mix_spectrum(prec == PSPFFT_FP32 ? 0 : 1, n[2]) == 2;
+}
+size_t spectrum_main(const int n[3], pspfft_precision prec) {
+    const size_t row = mix_spectrum_blocked(n, prec) ? round_up(n[0], pspfft::kGroup) : n[0];
+    return static_cast<size_t>(n[2] + 1) * (n[1] + 1) * row;
+}
+
 // cos(pi j / n), j < 2n, for the even-extension transform of G.
 std::vector<double> cos_table(int n) {
     std::vector<double> t(2 * n);
@@ -459,6 +505,71 @@ int generic_tile(int L, size_t csz) {
 // per kMaxProblems problems).  The launch's tile follows its longest line; a
 // line's arithmetic does not depend on the tile (each butterfly reads only its
 // own line), so results are the same alone and in any batch.
+// Problems p[c0 .. c1) of `idx` as the launch's problems, those of one plan (neighbours) as a segment.
+void add_problems(LaunchArgs &args, const std::vector<int> &idx, size_t c0, size_t c1, const pspfft_plan_t *plans,
+                  const pspfft_workspace_t *ws, const void *const *S, void *const *Phi) {
+    std::memset(&args, 0, sizeof(args));
+    args.count = static_cast<int>(c1 - c0);
+    for (size_t j = c0; j < c1; ++j) {
+        const int i = idx[j];
+        args.p[j - c0] = ProbArg{plans[i]->dev, S ? S[i] : nullptr, Phi ? Phi[i] : nullptr, ws[i]->W, ws[i]->Wn};
+        if (j > c0 && plans[idx[j - 1]] == plans[i]) {
+            args.seg[args.nseg - 1].group += 1;
+            continue;
+        }
+        pspfft::Segment &sg = args.seg[args.nseg++];
+        sg.first = static_cast<int>(j - c0);
+        sg.group = 1;
+    }
+}
+
+// Numbers the workgroups of a launch: `tile` lines each, main lines, then Nyquist lines.  False if
+// there are too many.
+bool number_tiles(LaunchArgs &args, int mode, int tile, const std::vector<int> &idx, size_t c0,
+                  const pspfft_plan_t *plans) {
+    long wg = 0;
+    for (int k = 0; k < args.nseg; ++k) {
+        pspfft::Segment &sg = args.seg[k];
+        long lm, ln;
+        pass_lines(mode, plans[idx[c0 + sg.first]]->n, lm, ln);
+        const long wm = (lm + tile - 1) / tile, wn = (ln + tile - 1) / tile;
+        sg.wg_begin = static_cast<int>(wg);
+        sg.wg_main = static_cast<int>(wm);
+        wg += (wm + wn) * sg.group;
+        if (wg + 64 > 0x7fffffffL) return false;  // grids are padded to whole rounds of 64
+    }
+    args.nwg = static_cast<int>(wg);
+    return true;
+}
+
+// Grouped launches of a pass by half-length lines: one per precision and length.
+pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_plan_t *plans,
+                         const pspfft_workspace_t *ws, const void *const *S, void *const *Phi, hipStream_t stream) {
+    const int axis = pspfft::pass_axis(mode);
+    std::map<std::pair<int, int>, std::vector<int>> groups;
+    for (int i : all) groups[{plans[i]->host.prec, plans[i]->n[axis]}].push_back(i);
+    for (auto &kv : groups) {
+        const int prec = kv.first.first, n = kv.first.second;
+        std::vector<int> &idx = kv.second;
+        std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) {
+            return reinterpret_cast<uintptr_t>(plans[a]) < reinterpret_cast<uintptr_t>(plans[b]);
+        });
+        pspfft::MixInfo info;
+        if (!pspfft::mix_info(n, info)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
+        const int tile = axis == 0 ? info.rows : info.tile[prec];
+        for (size_t c0 = 0; c0 < idx.size(); c0 += pspfft::kMaxProblems) {
+            const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
+            LaunchArgs args;
+            add_problems(args, idx, c0, c1, plans, ws, S, Phi);
+            if (!number_tiles(args, mode, tile, idx, c0, plans)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
+            PSPFFT_LOG(3, "pass %d prec %d half-length lines of %d: %d problems in %d segments, %d workgroups of %d "
+                          "lines", mode, prec, n, args.count, args.nseg, args.nwg, tile);
+            if (pspfft::launch_mix_lines(mode, prec, n, args, stream) != hipSuccess) return PSPFFT_ERR_DEVICE;
+        }
+    }
+    return PSPFFT_OK;
+}
+
 pspfft_status launch_generic_lines(int mode, const std::vector<int> &all, const pspfft_plan_t *plans,
                                    const pspfft_workspace_t *ws, const void *const *S, void *const *Phi,
                                    hipStream_t stream) {
@@ -475,52 +586,23 @@ pspfft_status launch_generic_lines(int mode, const std::vector<int> &all, const 
         for (size_t c0 = 0; c0 < idx.size(); c0 += pspfft::kMaxProblems) {
             const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
             LaunchArgs args;
-            std::memset(&args, 0, sizeof(args));
-            args.count = static_cast<int>(c1 - c0);
+            add_problems(args, idx, c0, c1, plans, ws, S, Phi);
             int lmax = 1;
             for (size_t j = c0; j < c1; ++j) lmax = std::max(lmax, plans[idx[j]]->host.ax[axis].L);
-            for (size_t j = c0; j < c1; ++j) {
-                const int i = idx[j];
-                ProbArg &a = args.p[j - c0];
-                a.plan = plans[i]->dev;
-                a.S = S ? S[i] : nullptr;
-                a.Phi = Phi ? Phi[i] : nullptr;
-                a.W = ws[i]->W;
-                a.Wn = ws[i]->Wn;
-                if (j > c0 && plans[idx[j - 1]] == plans[i]) {
-                    args.seg[args.nseg - 1].group += 1;
-                    continue;
-                }
-                pspfft::Segment &sg = args.seg[args.nseg++];
-                sg.first = static_cast<int>(j - c0);
-                sg.group = 1;
-            }
             args.gtile = generic_tile(lmax, csz);
             args.glmax = lmax;
             int ntw = 0;
             for (size_t j = c0; j < c1; ++j) ntw = std::max(ntw, plans[idx[j]]->host.ax[axis].ntw);
             const size_t bufs = static_cast<size_t>(2) * args.gtile * (lmax + 1) * csz;
             args.gtw = bufs + ntw * csz <= 160 * 1024 ? 1 : 0;
-            long wg = 0;
-            for (int k = 0; k < args.nseg; ++k) {
-                pspfft::Segment &sg = args.seg[k];
-                const pspfft_plan_t pl = plans[idx[c0 + sg.first]];
-                long lm, ln;
-                pass_lines(mode, pl->n, lm, ln);
-                const long wm = (lm + args.gtile - 1) / args.gtile, wn = (ln + args.gtile - 1) / args.gtile;
-                sg.wg_begin = static_cast<int>(wg);
-                sg.wg_main = static_cast<int>(wm);
-                wg += (wm + wn) * sg.group;
-            }
-            if (wg > 0x7fffffffL) return PSPFFT_ERR_UNSUPPORTED_SIZE;
-            args.nwg = static_cast<int>(wg);
+            if (!number_tiles(args, mode, args.gtile, idx, c0, plans)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
             const size_t lds = bufs + (args.gtw ? ntw * csz : 0);
             PSPFFT_LOG(3, "pass %d prec %d generic: %d problems in %d segments, %ld workgroups of 256 threads, "
-                          "%d lines each, %zu B LDS", mode, prec, args.count, args.nseg, wg, args.gtile, lds);
+                          "%d lines each, %zu B LDS", mode, prec, args.count, args.nseg, static_cast<long>(args.nwg),
+                       args.gtile, lds);
             // a whole number of rounds of 64 workgroups: the kernel deals its tiles to the XCDs in chunks
-            const long grid = (wg + 63) / 64 * 64;
-            if (grid > 0x7fffffffL) return PSPFFT_ERR_UNSUPPORTED_SIZE;
-            if (pspfft::launch_generic(mode, prec, args, static_cast<int>(grid), lds, stream) != hipSuccess)
+            const int grid = (args.nwg + 63) / 64 * 64;
+            if (pspfft::launch_generic(mode, prec, args, grid, lds, stream) != hipSuccess)
                 return PSPFFT_ERR_DEVICE;
         }
     }
@@ -533,9 +615,16 @@ pspfft_status launch_lines(int mode, const std::vector<int> &all_in, const pspff
                            hipStream_t stream) {
     const int axis = pspfft::pass_axis(mode);
     const bool row = axis == 0;
-    // axes outside the radix families go to the generic kernel
-    std::vector<int> all, gen;
-    for (int i : all_in) (plans[i]->host.ax[axis].E ? all : gen).push_back(i);
+    // axes of half-length lines, and those outside the radix families (the generic kernel)
+    std::vector<int> all, gen, mix;
+    for (int i : all_in) {
+        const AxisPlan &ax = plans[i]->host.ax[axis];
+        (ax.mtw ? mix : ax.E ? all : gen).push_back(i);
+    }
+    if (!mix.empty()) {
+        const pspfft_status st = launch_mix(mode, mix, plans, ws, S, Phi, stream);
+        if (st != PSPFFT_OK) return st;
+    }
     if (!gen.empty()) {
         const pspfft_status st = launch_generic_lines(mode, gen, plans, ws, S, Phi, stream);
         if (st != PSPFFT_OK) return st;
@@ -840,7 +929,11 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
 
     // stage plans and twiddle tables (FP64, rounded once to the plan precision)
     std::vector<std::complex<double>> tws[3];
+    pspfft::MixInfo mix[3];
+    bool mixed[3];
+    size_t mix_at[3];
     for (int a = 0; a < 3; ++a) {
+        mixed[a] = mix_axis(a, p->n, prec, mix[a]);
         if (!build_axis(a, p->n[a], prec, p->host.ax[a], tws[a]))
             return fail(PSPFFT_ERR_UNSUPPORTED_SIZE, vlevel, "%s: no stage plan for axis %d (n = %d)", who, a,
                         p->n[a]);
@@ -859,13 +952,19 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
             off += std::snprintf(radices + off, sizeof(radices) - off, s2 ? " x %d" : "%d", ax.R[s2]);
         PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_INFO_2, "  axis %c: n = %d, line of %d points, stages %s, %s", "xyz"[a],
                    ax.n, ax.L, ax.nst ? radices : "none", ax.E ? "radix-family kernels" : "generic line kernel");
-        if (!ax.E)
+        if (mixed[a])
+            PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_INFO_2, "  axis %c: half-length lines, stages %d x %d%s", "xyz"[a],
+                       mix[a].radix[0], mix[a].radix[1],
+                       mix[a].radix[2] > 1 ? (" x " + std::to_string(mix[a].radix[2])).c_str() : "");
+        else if (!ax.E)
             PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_WARNING,
                        "plan %d x %d x %d %s: axis %c (n = %d) runs on the generic line kernel, slower than the "
                        "radix families (n = 2^a times 1, 3, 5 or 9)", nx, ny, nz, pname, "xyz"[a], ax.n);
     }
     if (hipGetDevice(&p->device) != hipSuccess) return fail(PSPFFT_ERR_DEVICE, vlevel, "%s: hipGetDevice", who);
     for (int a = 0; a < 3; ++a) {
+        mix_at[a] = tws[a].size();
+        if (mixed[a]) mix_twiddles(mix[a], tws[a]);
         const std::vector<std::complex<double>> &tw = tws[a];
         const size_t tb = tw.size() * cs;
         pspfft_status st = alloc(&p->tw[a], tb);
@@ -884,6 +983,7 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
             return fail(PSPFFT_ERR_DEVICE, vlevel, "%s: twiddle upload", who);
         p->host.ax[a].tw = p->tw[a];
         p->host.ax[a].post = a == 0 ? static_cast<char *>(p->tw[a]) + p->host.ax[a].ntw * cs : nullptr;
+        p->host.ax[a].mtw = mixed[a] ? static_cast<char *>(p->tw[a]) + mix_at[a] * cs : nullptr;
         bytes += tb;
     }
     // Workspace z tiles.  Only meshes whose z planes span 4 MB or more are
@@ -898,14 +998,20 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
             const int v = std::atoi(e);
             if (v >= 1 && v <= 16 && (v & (v - 1)) == 0) cap = v;
         }
-        const int nbz = p->host.ax[2].NB;
+        int nbz = p->host.ax[2].NB;
+        if (mixed[2]) {  // whole tiles between a thread's first-stage positions t + NB*i + r*n0
+            const int n0 = nz / mix[2].radix[0];
+            nbz = n0 <= mix[2].nb ? n0 : std::gcd(n0, mix[2].nb);
+        }
         int zb = 1;  // generic z lines (NB = 0): no tiling, nz need not be a multiple of anything
         while (nbz > 0 && zb < cap && nbz % (2 * zb) == 0) zb *= 2;
         p->host.zb = zb;
     }
     // kz-fastest spectrum for wavefront-owned z lines and for z lines on the
-    // generic kernel (whose lanes of a line walk consecutive kz)
-    p->host.gz = z_wave_lines(p) || p->host.ax[2].E == 0 ? 1 : 0;
+    // generic kernel (whose lanes of a line walk consecutive kz); in blocks of
+    // kGroup kx for half-length z lines (whose lanes take kGroup kx or more)
+    p->host.gz = mixed[2] ? pspfft::mix_spectrum(p->host.prec, nz)
+                          : (z_wave_lines(p) || p->host.ax[2].E == 0 ? 1 : 0);
     // fused x-y plane kernels: nx == ny = E*K (at most two stages) and the plane fits in LDS
     {
         const AxisPlan &ax = p->host.ax[0];
@@ -920,7 +1026,7 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
 
     // Green's-function spectrum, computed once in FP64 and kept (Sec. 2.2.2)
     const size_t oct = static_cast<size_t>(nx + 1) * (ny + 1) * (nz + 1);
-    const size_t gmain = static_cast<size_t>(nz + 1) * (ny + 1) * nx * rs;
+    const size_t gmain = spectrum_main(p->n, prec) * rs;
     const size_t gnyq = static_cast<size_t>(nz + 1) * (ny + 1) * rs;
     pspfft_status st;
     if ((st = alloc(&p->G, gmain)) != PSPFFT_OK || (st = alloc(&p->Gn, gnyq)) != PSPFFT_OK)
@@ -1198,10 +1304,12 @@ size_t pspfft_plan_resident_bytes(int nx, int ny, int nz, pspfft_precision prec)
         AxisPlan ax;
         std::vector<std::complex<double>> tw;
         if (!build_axis(a, n[a], prec, ax, tw)) return 0;
+        pspfft::MixInfo info;
+        if (mix_axis(a, n, prec, info)) mix_twiddles(info, tw);
         bytes += tw.size() * cplx_size(prec);
     }
     // spectrum octant: main part and the kx = nx column
-    bytes += static_cast<size_t>(nz + 1) * (ny + 1) * (nx + 1) * real_size(prec);
+    bytes += (spectrum_main(n, prec) + static_cast<size_t>(nz + 1) * (ny + 1)) * real_size(prec);
     return bytes;
 }
 
