@@ -376,19 +376,17 @@ hipError_t launch_generic(int mode, int prec, const LaunchArgs &args, int grid, 
 // always kept it so.
 __host__ __device__ constexpr int mix_spectrum(int prec, int n) {
     const bool fp32_only = n == 320 || n == 576 || n == 640 || n == 1024 || n == 1152;
-    return n == 144 || n == 160 || n == 192 || (prec != 0 && fp32_only) ? 0 : 2;
+    return n == 80 || n == 96 || n == 128 || n == 144 || n == 160 || n == 192 || (prec != 0 && fp32_only) ? 0 : 2;
 }
 
 // Stage radices of length n on the half-length line kernels (radix[2] = 1: two
-// stages), threads per line, and the lines (by precision) and rows of a
-// workgroup; false if they do not take the length.
+// stages), threads per line, and the z lines, y lines and rows of a workgroup;
+// false if they do not take the length.
 struct MixInfo {
     int radix[3];
-    int nb;
-    int tile[2];
-    int rows;
+    int nb, tile_z, tile_y, rows;
 };
-bool mix_info(int n, MixInfo &info);
+bool mix_info(int prec, int n, MixInfo &info);
 // Pass `mode` by half-length lines of n cells (x rows of n) for the problems of
 // args, whose segments count mix_info() tiles or rows.
 hipError_t launch_mix_lines(int mode, int prec, int n, const LaunchArgs &args, hipStream_t stream);

@@ -1,4 +1,4 @@
-// Half-length line kernels, float: the lengths of PSPFFT_MIX_B.
+// Half-length line kernels, float: the lengths of PSPFFT_MIX_F32_B.
 #include "mix_lines.h"
 
-PSPFFT_MIX_UNIT(float, mix_f32_b, PSPFFT_MIX_B)
+PSPFFT_MIX_UNIT(float, mix_f32_b, PSPFFT_MIX_F32_B)

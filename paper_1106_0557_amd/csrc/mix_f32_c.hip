@@ -1,4 +1,4 @@
-// Half-length line kernels, float: the lengths of PSPFFT_MIX_C.
+// Half-length line kernels, float: the lengths of PSPFFT_MIX_F32_C.
 #include "mix_lines.h"
 
-PSPFFT_MIX_UNIT(float, mix_f32_c, PSPFFT_MIX_C)
+PSPFFT_MIX_UNIT(float, mix_f32_c, PSPFFT_MIX_F32_C)

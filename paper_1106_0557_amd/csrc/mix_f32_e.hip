@@ -1,4 +1,4 @@
-// Half-length line kernels, float: the lengths of PSPFFT_MIX_E.
+// Half-length line kernels, float: the lengths of PSPFFT_MIX_F32_E.
 #include "mix_lines.h"
 
-PSPFFT_MIX_UNIT(float, mix_f32_e, PSPFFT_MIX_E)
+PSPFFT_MIX_UNIT(float, mix_f32_e, PSPFFT_MIX_F32_E)

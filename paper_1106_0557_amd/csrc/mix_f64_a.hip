@@ -1,4 +1,4 @@
-// Half-length line kernels, double: the lengths of PSPFFT_MIX_A.
+// Half-length line kernels, double: the lengths of PSPFFT_MIX_F64_A.
 #include "mix_lines.h"
 
-PSPFFT_MIX_UNIT(double, mix_f64_a, PSPFFT_MIX_A)
+PSPFFT_MIX_UNIT(double, mix_f64_a, PSPFFT_MIX_F64_A)

@@ -1,4 +1,4 @@
-// Half-length line kernels, double: the lengths of PSPFFT_MIX_B.
+// Half-length line kernels, double: the lengths of PSPFFT_MIX_F64_B.
 #include "mix_lines.h"
 
-PSPFFT_MIX_UNIT(double, mix_f64_b, PSPFFT_MIX_B)
+PSPFFT_MIX_UNIT(double, mix_f64_b, PSPFFT_MIX_F64_B)

@@ -1,4 +1,4 @@
-// Half-length line kernels, double: the lengths of PSPFFT_MIX_E.
+// Half-length line kernels, double: the lengths of PSPFFT_MIX_F64_E.
 #include "mix_lines.h"
 
-PSPFFT_MIX_UNIT(double, mix_f64_e, PSPFFT_MIX_E)
+PSPFFT_MIX_UNIT(double, mix_f64_e, PSPFFT_MIX_F64_E)

@@ -3,51 +3,38 @@
 
 namespace pspfft {
 
-bool mix_info(int n, MixInfo &info) {
-    switch (n) {
-#define PSPFFT_MIX_CASE(N, A, B, C)                                                                     \
-    case N:                                                                                             \
-        info = MixInfo{{A, B, C}, MixLen<N>::NB, {MixTile<float, N>::TILE, MixTile<double, N>::TILE}, \
-                       MixRow<float, N>::ROWS};                                                         \
-        return true;
-        PSPFFT_MIX_ALL(PSPFFT_MIX_CASE)
-#undef PSPFFT_MIX_CASE
+namespace {
+template <typename T, int N>
+MixInfo info_of() {
+    using G = MixLen<T, N>;
+    return MixInfo{{G::R0, G::R1, G::R2}, G::NB, MixTile<T, N, true>::TILE, MixTile<T, N, false>::TILE,
+                   MixRow<T, N>::ROWS};
+}
+}  // namespace
+
+bool mix_info(int prec, int n, MixInfo &info) {
+    switch (n + (prec << 16)) {
+#define PSPFFT_MIX_CASE_F32(N, A, B, C, D, E) case N: info = info_of<float, N>(); return true;
+#define PSPFFT_MIX_CASE_F64(N, A, B, C, D, E) case N + (1 << 16): info = info_of<double, N>(); return true;
+        PSPFFT_MIX_ALL(PSPFFT_MIX_CASE_F32, PSPFFT_MIX_F32)
+        PSPFFT_MIX_ALL(PSPFFT_MIX_CASE_F64, PSPFFT_MIX_F64)
         default: return false;
     }
 }
 
-#undef PSPFFT_MIX_UNIT
-#define PSPFFT_MIX_UNIT(NAME) hipError_t NAME(int n, int mode, const LaunchArgs &args, hipStream_t stream);
-PSPFFT_MIX_UNIT(mix_f32_a)
-PSPFFT_MIX_UNIT(mix_f32_b)
-PSPFFT_MIX_UNIT(mix_f32_c)
-PSPFFT_MIX_UNIT(mix_f32_d)
-PSPFFT_MIX_UNIT(mix_f32_e)
-PSPFFT_MIX_UNIT(mix_f64_a)
-PSPFFT_MIX_UNIT(mix_f64_b)
-PSPFFT_MIX_UNIT(mix_f64_c)
-PSPFFT_MIX_UNIT(mix_f64_d)
-PSPFFT_MIX_UNIT(mix_f64_e)
-#undef PSPFFT_MIX_UNIT
+using MixUnit = hipError_t(int n, int mode, const LaunchArgs &args, hipStream_t stream);
+MixUnit mix_f32_a, mix_f32_b, mix_f32_c, mix_f32_d, mix_f32_e;
+MixUnit mix_f64_a, mix_f64_b, mix_f64_c, mix_f64_d, mix_f64_e;
 
 hipError_t launch_mix_lines(int mode, int prec, int n, const LaunchArgs &args, hipStream_t stream) {
     if (args.nwg <= 0) return hipSuccess;
-    using Unit = hipError_t (*)(int, int, const LaunchArgs &, hipStream_t);
-    static constexpr Unit units[2][5] = {{mix_f32_a, mix_f32_b, mix_f32_c, mix_f32_d, mix_f32_e},
-                                         {mix_f64_a, mix_f64_b, mix_f64_c, mix_f64_d, mix_f64_e}};
-    switch (n) {
-#define PSPFFT_MIX_CASE_0(N, A, B, C) case N: return units[prec][0](n, mode, args, stream);
-#define PSPFFT_MIX_CASE_1(N, A, B, C) case N: return units[prec][1](n, mode, args, stream);
-#define PSPFFT_MIX_CASE_2(N, A, B, C) case N: return units[prec][2](n, mode, args, stream);
-#define PSPFFT_MIX_CASE_3(N, A, B, C) case N: return units[prec][3](n, mode, args, stream);
-#define PSPFFT_MIX_CASE_4(N, A, B, C) case N: return units[prec][4](n, mode, args, stream);
-        PSPFFT_MIX_A(PSPFFT_MIX_CASE_0)
-        PSPFFT_MIX_B(PSPFFT_MIX_CASE_1)
-        PSPFFT_MIX_C(PSPFFT_MIX_CASE_2)
-        PSPFFT_MIX_D(PSPFFT_MIX_CASE_3)
-        PSPFFT_MIX_E(PSPFFT_MIX_CASE_4)
-        default: return hipErrorInvalidValue;
-    }
+    MixInfo info;
+    if (prec < 0 || prec > 1 || !mix_info(prec, n, info)) return hipErrorInvalidValue;
+    // the lists hold ascending lengths
+    static constexpr MixUnit *units[2][5] = {{mix_f32_a, mix_f32_b, mix_f32_c, mix_f32_d, mix_f32_e},
+                                             {mix_f64_a, mix_f64_b, mix_f64_c, mix_f64_d, mix_f64_e}};
+    const int list = n <= 144 ? 0 : n <= 256 ? 1 : n <= 486 ? 2 : n <= 750 ? 3 : 4;
+    return units[prec][list](n, mode, args, stream);
 }
 
 }  // namespace pspfft

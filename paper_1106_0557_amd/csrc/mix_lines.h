@@ -28,58 +28,85 @@
 
 namespace pspfft {
 
-// Lengths N = R0*R1*R2 (R2 = 1: two stages).  Up to 256 points two stages, so
-// one LDS exchange per transform; beyond, three stages whose butterflies spread
-// over 32, 64 or 96 threads with at most 20 values per thread and few idle ones.
-// The odd factors go first: N/R0 then keeps the powers of two, which the
-// workspace's z tiles divide.
-template <int N>
-struct MixRadices {
-    static constexpr int R0 = 0, R1 = 0, R2 = 0;
-};
-#define PSPFFT_MIX_A(X)                                                                                       \
-    X(25, 5, 5, 1) X(27, 9, 3, 1) X(30, 5, 6, 1) X(45, 9, 5, 1) X(50, 5, 10, 1) X(54, 9, 6, 1)                \
-    X(60, 6, 10, 1) X(75, 15, 5, 1) X(81, 9, 9, 1) X(90, 9, 10, 1) X(100, 10, 10, 1) X(108, 9, 12, 1)         \
-    X(120, 10, 12, 1) X(125, 25, 5, 1) X(135, 15, 9, 1) X(144, 12, 12, 1)
-#define PSPFFT_MIX_B(X)                                                                                       \
-    X(150, 15, 10, 1) X(160, 10, 16, 1) X(162, 9, 18, 1) X(180, 15, 12, 1) X(192, 12, 16, 1)                  \
-    X(200, 10, 20, 1) X(216, 18, 12, 1) X(225, 15, 15, 1) X(240, 15, 16, 1) X(243, 27, 9, 1)                  \
-    X(250, 25, 10, 1) X(256, 16, 16, 1)
-#define PSPFFT_MIX_C(X)                                                                                       \
-    X(270, 9, 6, 5) X(288, 9, 8, 4) X(300, 5, 10, 6) X(320, 10, 8, 4) X(324, 9, 12, 3) X(360, 15, 6, 4)       \
-    X(375, 15, 5, 5) X(384, 12, 8, 4) X(400, 5, 16, 5) X(405, 15, 9, 3) X(432, 9, 16, 3) X(450, 15, 6, 5)     \
-    X(480, 15, 16, 2) X(486, 9, 18, 3)
-#define PSPFFT_MIX_D(X)                                                                                       \
-    X(500, 5, 10, 10) X(512, 16, 8, 4) X(540, 9, 10, 6) X(576, 9, 16, 4) X(600, 15, 10, 4)                    \
-    X(625, 25, 25, 1) X(640, 10, 16, 4) X(648, 9, 18, 4) X(675, 15, 9, 5) X(720, 15, 12, 4) X(729, 9, 9, 9)   \
-    X(750, 15, 10, 5)
-#define PSPFFT_MIX_E(X)                                                                                       \
-    X(768, 12, 16, 4) X(800, 5, 16, 10) X(810, 15, 9, 6) X(864, 9, 16, 6) X(900, 15, 15, 4)                   \
-    X(960, 15, 16, 4) X(972, 9, 18, 6) X(1000, 5, 20, 10) X(1024, 16, 16, 4) X(1080, 15, 12, 6)               \
-    X(1125, 15, 15, 5) X(1152, 12, 8, 12)
-#define PSPFFT_MIX_ALL(X) PSPFFT_MIX_A(X) PSPFFT_MIX_B(X) PSPFFT_MIX_C(X) PSPFFT_MIX_D(X) PSPFFT_MIX_E(X)
-#define PSPFFT_MIX_RADICES(N, A, B, C)                          \
-    template <>                                                 \
-    struct MixRadices<N> {                                      \
-        static constexpr int R0 = A, R1 = B, R2 = C;            \
-        static_assert(A * B * C == N, "radices of the length"); \
+// Lengths N = R0*R1*R2 (R2 = 1: two stages) with the threads per line NB and the z lines per
+// workgroup: X(N, R0, R1, R2, NB, TILE), by precision.  Measured choices among the splits whose
+// stages keep most threads busy (all five passes of one n^3 solve): what counts is that two or
+// more workgroups share a CU (their registers, up to about 24 values per thread in FP32 and 16 in
+// FP64, and their LDS), then few stages, then whole 128-byte row segments, then an N/R0 with a
+// power of two in it, which the workspace's z tiles divide.  For example, one FP32 solve, ms: 480
+// as 5*6*16 with 32 threads 2.73, 8*10*6 with 80 threads 3.9; 432 as 24*18 2.00, 9*16*3 2.3; 1024 as
+// 8*8*16 35.2, 16*16*4 38; FP64 512 as 8*8*8 6.81, 4*8*16 6.83, 16*8*4 6.9.
+template <typename T, int N>
+struct MixRadices;
+#define PSPFFT_MIX_F32_A(X)                                                                                   \
+    X(25, 5, 5, 1, 5, 16) X(27, 9, 3, 1, 9, 16) X(30, 5, 6, 1, 6, 16) X(45, 9, 5, 1, 9, 16)                   \
+    X(50, 5, 10, 1, 10, 16) X(54, 9, 6, 1, 9, 16) X(60, 10, 6, 1, 10, 16) X(75, 15, 5, 1, 15, 16)             \
+    X(80, 10, 8, 1, 10, 16) X(81, 9, 9, 1, 9, 16) X(90, 9, 10, 1, 10, 16) X(96, 12, 8, 1, 12, 16)             \
+    X(100, 10, 10, 1, 10, 16) X(108, 9, 12, 1, 12, 16) X(120, 12, 10, 1, 12, 16) X(125, 5, 5, 5, 25, 16)      \
+    X(135, 9, 15, 1, 15, 16) X(144, 12, 12, 1, 12, 16)
+#define PSPFFT_MIX_F32_B(X)                                                                                   \
+    X(150, 5, 5, 6, 30, 16) X(160, 10, 16, 1, 16, 16) X(162, 18, 9, 1, 9, 16) X(180, 15, 12, 1, 15, 16)       \
+    X(192, 16, 12, 1, 16, 16) X(200, 10, 20, 1, 10, 16) X(216, 12, 18, 1, 12, 16) X(225, 15, 15, 1, 15, 16)   \
+    X(240, 15, 16, 1, 16, 16) X(243, 3, 9, 9, 27, 16) X(250, 5, 10, 5, 25, 16) X(256, 16, 16, 1, 16, 16)
+#define PSPFFT_MIX_F32_C(X)                                                                                   \
+    X(270, 9, 6, 5, 32, 16) X(288, 4, 6, 12, 24, 8) X(300, 5, 10, 6, 32, 16) X(320, 20, 4, 4, 16, 16)         \
+    X(324, 9, 12, 3, 32, 16) X(360, 20, 18, 1, 20, 8) X(375, 15, 5, 5, 32, 16) X(384, 24, 16, 1, 24, 8)       \
+    X(400, 5, 16, 5, 32, 16) X(405, 15, 9, 3, 32, 16) X(432, 24, 18, 1, 24, 8) X(450, 15, 6, 5, 32, 16)       \
+    X(480, 5, 6, 16, 32, 8) X(486, 9, 18, 3, 32, 8)
+#define PSPFFT_MIX_F32_D(X)                                                                                   \
+    X(500, 5, 10, 10, 32, 8) X(512, 8, 8, 8, 32, 8) X(540, 9, 10, 6, 32, 8) X(576, 9, 16, 4, 64, 8)           \
+    X(600, 6, 10, 10, 60, 8) X(625, 25, 25, 1, 25, 8) X(640, 20, 8, 4, 32, 8) X(648, 6, 9, 12, 54, 8)         \
+    X(675, 15, 9, 5, 64, 8) X(720, 12, 5, 12, 60, 8) X(729, 27, 27, 1, 27, 8) X(750, 25, 30, 1, 30, 8)
+#define PSPFFT_MIX_F32_E(X)                                                                                   \
+    X(768, 12, 8, 8, 64, 8) X(800, 5, 8, 20, 64, 8) X(810, 15, 9, 6, 64, 8) X(864, 6, 8, 18, 64, 8)           \
+    X(900, 15, 15, 4, 64, 8) X(960, 4, 15, 16, 64, 8) X(972, 6, 18, 9, 54, 8) X(1000, 10, 10, 10, 64, 8)      \
+    X(1024, 8, 8, 16, 64, 8) X(1080, 12, 9, 10, 90, 8) X(1125, 15, 15, 5, 75, 8) X(1152, 8, 12, 12, 96, 8)
+#define PSPFFT_MIX_F64_A(X)                                                                                   \
+    X(25, 5, 5, 1, 5, 8) X(27, 9, 3, 1, 9, 8) X(30, 5, 6, 1, 6, 8) X(45, 9, 5, 1, 9, 8)                       \
+    X(50, 5, 10, 1, 10, 8) X(54, 9, 6, 1, 9, 8) X(60, 10, 6, 1, 10, 8) X(75, 15, 5, 1, 15, 8)                 \
+    X(80, 10, 8, 1, 10, 8) X(81, 9, 9, 1, 9, 8) X(90, 9, 10, 1, 10, 8) X(96, 12, 8, 1, 12, 8)                 \
+    X(100, 10, 10, 1, 10, 8) X(108, 9, 12, 1, 12, 8) X(120, 15, 8, 1, 8, 8) X(125, 5, 5, 5, 25, 8)            \
+    X(128, 16, 8, 1, 16, 8) X(135, 15, 9, 1, 15, 8) X(144, 12, 12, 1, 12, 8)
+#define PSPFFT_MIX_F64_B(X)                                                                                   \
+    X(150, 5, 5, 6, 30, 4) X(160, 10, 16, 1, 16, 8) X(162, 9, 6, 3, 27, 8) X(180, 15, 12, 1, 15, 8)           \
+    X(192, 16, 12, 1, 16, 8) X(200, 5, 5, 8, 25, 8) X(216, 3, 8, 9, 27, 8) X(225, 5, 5, 9, 25, 8)             \
+    X(240, 16, 15, 1, 16, 8) X(243, 3, 9, 9, 27, 8) X(250, 5, 10, 5, 25, 8) X(256, 8, 8, 4, 32, 8)
+#define PSPFFT_MIX_F64_C(X)                                                                                   \
+    X(270, 3, 10, 9, 30, 8) X(288, 18, 16, 1, 18, 8) X(300, 5, 10, 6, 32, 8) X(320, 20, 16, 1, 20, 8)         \
+    X(324, 9, 12, 3, 32, 8) X(360, 5, 6, 12, 30, 8) X(375, 15, 5, 5, 32, 8) X(384, 12, 8, 4, 32, 8)           \
+    X(400, 5, 16, 5, 32, 8) X(405, 3, 9, 15, 32, 8) X(432, 9, 16, 3, 32, 8) X(450, 15, 6, 5, 30, 8)           \
+    X(480, 15, 16, 2, 32, 8) X(486, 9, 6, 9, 54, 4)
+#define PSPFFT_MIX_F64_D(X)                                                                                   \
+    X(500, 5, 10, 10, 50, 4) X(512, 8, 8, 8, 32, 8) X(540, 9, 6, 10, 60, 4) X(576, 12, 4, 12, 48, 4)          \
+    X(600, 5, 12, 10, 60, 4) X(640, 4, 16, 10, 64, 4) X(648, 6, 9, 12, 54, 4) X(675, 15, 15, 3, 45, 4)        \
+    X(720, 15, 12, 4, 64, 4) X(729, 9, 9, 9, 81, 4) X(750, 15, 10, 5, 64, 4)
+#define PSPFFT_MIX_F64_E(X)                                                                                   \
+    X(768, 8, 8, 12, 64, 4) X(800, 5, 16, 10, 64, 4) X(810, 15, 9, 6, 64, 4) X(864, 12, 8, 9, 96, 4)          \
+    X(900, 15, 15, 4, 64, 4) X(960, 12, 10, 8, 96, 4) X(972, 9, 12, 9, 108, 4) X(1000, 10, 10, 10, 100, 4)    \
+    X(1024, 8, 16, 8, 128, 4) X(1080, 12, 10, 9, 108, 4) X(1125, 15, 15, 5, 75, 4)                            \
+    X(1152, 12, 8, 12, 96, 4)
+#define PSPFFT_MIX_ALL(X, P) P##_A(X) P##_B(X) P##_C(X) P##_D(X) P##_E(X)
+#define PSPFFT_MIX_RADICES(T, N, A, B, C, THREADS, LINES)                        \
+    template <>                                                                  \
+    struct MixRadices<T, N> {                                                    \
+        static constexpr int R0 = A, R1 = B, R2 = C, NB = THREADS, TILE = LINES; \
     };
-PSPFFT_MIX_ALL(PSPFFT_MIX_RADICES)
-#undef PSPFFT_MIX_RADICES
+#define PSPFFT_MIX_RADICES_F32(N, A, B, C, D, E) PSPFFT_MIX_RADICES(float, N, A, B, C, D, E)
+#define PSPFFT_MIX_RADICES_F64(N, A, B, C, D, E) PSPFFT_MIX_RADICES(double, N, A, B, C, D, E)
+PSPFFT_MIX_ALL(PSPFFT_MIX_RADICES_F32, PSPFFT_MIX_F32)
+PSPFFT_MIX_ALL(PSPFFT_MIX_RADICES_F64, PSPFFT_MIX_F64)
 
 constexpr int mix_max(int a, int b) { return a > b ? a : b; }
 constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Stage geometry of a length: butterflies n0, n1, nL and rounds d0, d1, dL of
 // the first, second and last stage, values per thread V (any stage).
-template <int N_>
-struct MixLen {
-    using R = MixRadices<N_>;
-    static constexpr int N = N_, R0 = R::R0, R1 = R::R1, R2 = R::R2;
+template <int N_, int R0_, int R1_, int R2_, int NB_>
+struct MixGeo {
+    static constexpr int N = N_, R0 = R0_, R1 = R1_, R2 = R2_, NB = NB_;
+    static_assert(R0 * R1 * R2 == N, "radices of the length");
     static constexpr int ST = R2 > 1 ? 3 : 2;
     static constexpr int RL = ST == 3 ? R2 : R1;
-    // threads per line
-    static constexpr int NB = ST == 2 ? mix_max(R0, R1) : (N <= 540 ? 32 : (N <= 1024 ? 64 : 96));
     static constexpr int n0 = N / R0, n1 = N / R1, nL = N / RL;
     static constexpr int d0 = ceil_div(n0, NB), d1 = ceil_div(n1, NB), dL = ceil_div(nL, NB);
     static constexpr int V0 = d0 * R0, VL = dL * RL;
@@ -87,35 +114,36 @@ struct MixLen {
     static constexpr int NTW = N - R0;  // stage twiddles of one s
     static constexpr int off_last = ST == 3 ? R0 * (R1 - 1) : 0;
 };
-
-// Column tiles (lines per workgroup): 128-byte row segments (16 lines in FP32,
-// 8 in FP64) where two workgroups share a CU, the workgroup stays at 512
-// threads and, in FP32, the values of a thread fit the registers that leaves;
-// else 64-byte ones.  Measured, z pass of one solve: FP32 384^3 16 lines 0.51
-// ms, 8 lines 0.54; 480^3 (18 values a thread) 16 lines 1.16 ms, 8 lines 1.06.
 template <typename T, int N>
+using MixLen = MixGeo<N, MixRadices<T, N>::R0, MixRadices<T, N>::R1, MixRadices<T, N>::R2, MixRadices<T, N>::NB>;
+
+// Column tiles (lines per workgroup).  z: the table's.  y (fewer values per thread): 128-byte row
+// segments (16 lines in FP32, 8 in FP64) where two workgroups share a CU and stay at 512 threads,
+// else 64-byte ones.
+template <typename T, int N, bool Z>
 struct MixTile {
-    using G = MixLen<N>;
+    using G = MixLen<T, N>;
     static constexpr int CSZ = static_cast<int>(sizeof(cx<T>));
-    static constexpr bool F32 = sizeof(T) == 4;
     static constexpr int lds(int tile) { return (N * tile + 2 * G::NTW) * CSZ; }
-    static constexpr bool fits(int tile) {
-        return 2 * lds(tile) <= 160 * 1024 && tile * G::NB <= 512 && (!F32 || G::ST == 2 || tile < 16 || G::V <= 16);
-    }
     static constexpr int full = 128 / CSZ;
-    static constexpr int TILE = fits(full) ? full : full / 2;
+    static constexpr int TILE =
+        Z ? MixRadices<T, N>::TILE : (2 * lds(full) <= 160 * 1024 && full * G::NB <= 512 ? full : full / 2);
     static constexpr int BLOCK = TILE * G::NB;
     static constexpr size_t LDS = static_cast<size_t>(lds(TILE));
     static_assert(BLOCK <= 1024 && LDS <= 160 * 1024, "one workgroup fits");
-    // wavefronts per SIMD the z kernel is compiled for
-    static constexpr int WPS = G::ST == 2 ? 1 : (F32 ? (BLOCK == 512 ? 4 : (BLOCK <= 256 ? 3 : 1)) : 2);
+    // wavefronts per SIMD the z kernel is compiled for: two workgroups of 384 to 512 threads per
+    // CU, three of 128 to 320; FP64 and the longest registers, what they leave
+    static constexpr int WPS = !Z ? 1
+                               : sizeof(T) == 8 || G::V > 24
+                                   ? 2
+                                   : (BLOCK > 512 ? 1 : (BLOCK >= 384 ? 4 : (BLOCK >= 128 ? 3 : 1)));
 };
 
 // x rows per workgroup: about 256 threads.  LDS row stride: positions P at
 // P + P/R0 for even R0 (consecutive butterflies then start on different banks).
 template <typename T, int N>
 struct MixRow {
-    using G = MixLen<N>;
+    using G = MixLen<T, N>;
     static constexpr int CSZ = static_cast<int>(sizeof(cx<T>));
     static constexpr int PAD = G::R0 % 2 == 0 ? 1 : 0;
     static constexpr int RP = G::R0 + PAD;
@@ -129,10 +157,9 @@ struct MixRow {
 
 // The transforms of one line, N = R0*R1(*R2).  LDS position P of the line is at
 // pos(P)*LW from `col`; PAD as in MixRow (0: columns).
-template <typename T, int N, int LW, int PAD>
+template <typename T, typename G, int LW, int PAD>
 struct MixFFT {
-    using G = MixLen<N>;
-    static constexpr int NB = G::NB;
+    static constexpr int N = G::N, NB = G::NB;
     static constexpr int RP = G::R0 + PAD;
 
     // butterflies t, t + NB, ... of a stage of radix R: f(round, butterfly)
@@ -269,6 +296,15 @@ struct MixFFT {
     }
 };
 
+// A value that is the same for the whole workgroup, kept in a scalar register (divisions leave
+// theirs in a vector register, and addresses built on it would follow).
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+
 // Problem and tile of a workgroup (segments are numbered tile-major, so that
 // problems sharing a plan read one spectrum slice together).
 struct MixJob {
@@ -281,8 +317,8 @@ __device__ __forceinline__ MixJob mix_job(const LaunchArgs &args, int bid) {
     while (sgi + 1 < args.nseg && bid >= args.seg[sgi + 1].wg_begin) ++sgi;
     const Segment &sg = args.seg[sgi];
     int local = bid - sg.wg_begin;
-    const int member = local % sg.group;
-    local /= sg.group;
+    const int member = uniform(local % sg.group);
+    local = uniform(local / sg.group);
     const bool nyq = local >= sg.wg_main;
     return MixJob{&args.p[sg.first + member], nyq ? local - sg.wg_main : local, nyq};
 }
@@ -300,81 +336,112 @@ struct MixLine {
     }
 };
 
-// z lines.  Rows ky and 2ny - ky read the same spectrum values, so the lines are numbered pair
-// by pair of such rows ((0, ny) first), and within a pair by runs of TILE adjacent kx of the
-// one row, then of the other: tiles that share spectrum values are neighbours.
-template <typename T, int N, int GL>
+// z lines.  Rows ky and 2ny - ky read the same spectrum values, so the lines are numbered row 0,
+// then pair by pair of such rows (within a pair by runs of TILE adjacent kx of the one, then of the
+// other), then row ny: tiles that share spectrum values are neighbours, and the octant rows of a
+// tile's lines follow one another.
+// Spectrum values: for one parity of kz, unit `u` bytes apart; addresses are a base that is the same
+// for the whole workgroup plus 32 bits per lane, at its first position t (up) and at NB - t (dn).
+template <typename T>
 struct MixZ {
     MixLine<T> ln;
-    const gbl<const T> *g;  // this line's spectrum values: unit u between kz of one parity, o1 the odd ones
-    size_t u, o1;
+    uint64_t g;
+    size_t u, odd;  // bytes between kz of one parity; the first odd kz
+    uint32_t up, dn;
 };
 
+struct MixRowKx {
+    int ky, kx;
+};
+template <int TILE>
+__device__ __forceinline__ MixRowKx mix_z_row(int g, int nx, int ny) {
+    const int gg = g - nx, pr = gg / (2 * nx), l = gg - pr * 2 * nx;
+    const int j = l / (2 * TILE), rem = l - j * 2 * TILE, w = min(TILE, nx - j * TILE);
+    const bool second = rem >= w;
+    if (g < nx) return MixRowKx{0, g};
+    if (g >= (2 * ny - 1) * nx) return MixRowKx{ny, g - (2 * ny - 1) * nx};
+    return MixRowKx{second ? 2 * ny - 1 - pr : 1 + pr, j * TILE + rem - (second ? w : 0)};
+}
+
 template <typename T, int N, int TILE, int GL>
-__device__ __forceinline__ MixZ<T, N, GL> mix_z_line(const LaunchArgs &args, int bid, int c, int t) {
+__device__ __forceinline__ MixZ<T> mix_z_line(const LaunchArgs &args, int bid, int c, int t) {
     using cplan = const __attribute__((address_space(4))) DevPlan;
     constexpr size_t CSZ = sizeof(cx<T>);
+    constexpr int NB = MixLen<T, N>::NB;
     const MixJob job = mix_job(args, bid);
     const auto &pl = *(cplan *)job.pa->plan;
     const int nx = pl.nx, ny = pl.ny;
-    const int g = job.local * TILE + c;
-    MixZ<T, N, GL> z;
-    int ky, kx;
-    size_t gb;
+    const int g0 = job.local * TILE, g = g0 + c;
+    MixZ<T> z;
+    size_t base = 0, line;  // values of the octant: before the tile's first row, and the lane's own
     if (!job.nyq) {
         z.ln.active = g < 2 * ny * nx;
-        const int gg = z.ln.active ? g : 0;
-        const int pr = gg / (2 * nx), l = gg - pr * 2 * nx;
-        const int j = l / (2 * TILE), rem = l - j * 2 * TILE, w = min(TILE, nx - j * TILE);
-        const bool second = rem >= w;
-        kx = j * TILE + rem - (second ? w : 0);
-        ky = pr == 0 ? (second ? ny : 0) : (second ? 2 * ny - pr : pr);
+        const MixRowKx f = mix_z_row<TILE>(g0, nx, ny), q = mix_z_row<TILE>(z.ln.active ? g : g0, nx, ny);
         const int zb = pl.zb, sh = __builtin_ctz(static_cast<unsigned>(zb));
         const size_t plane = static_cast<size_t>(2) * ny * nx;
         z.ln.base = static_cast<char *>(job.pa->W);
         z.ln.step = plane * CSZ;  // zb divides NB and n0: whole tiles from one first-stage register to the next
         z.ln.lane = static_cast<uint32_t>(
-            ((static_cast<size_t>(t >> sh) << sh) * plane + (static_cast<size_t>(ky) * zb + (t & (zb - 1))) * nx + kx) * CSZ);
+            ((static_cast<size_t>(t >> sh) << sh) * plane + (static_cast<size_t>(q.ky) * zb + (t & (zb - 1))) * nx + q.kx) * CSZ);
+        const int k0 = uniform(f.ky <= ny ? f.ky : 2 * ny - f.ky), kyo = q.ky <= ny ? q.ky : 2 * ny - q.ky;
+        if constexpr (GL == 2) {
+            const int row = (nx + kGroup - 1) / kGroup * kGroup * (N + 1);
+            base = static_cast<size_t>(k0) * row;
+            line = static_cast<uint32_t>((kyo - k0) * row + q.kx / kGroup * (kGroup * (N + 1)) + q.kx % kGroup);
+            z.u = kGroup * sizeof(T);
+            z.odd = (N / 2 + 1) * z.u;
+        } else {
+            base = static_cast<size_t>(k0) * nx;
+            line = static_cast<uint32_t>((kyo - k0) * nx + q.kx);
+            z.odd = static_cast<size_t>(ny + 1) * nx * sizeof(T);
+            z.u = 2 * z.odd;
+        }
     } else {
         z.ln.active = g < 2 * ny;
-        ky = z.ln.active ? g : 0;
-        kx = nx;
+        const int ky = z.ln.active ? g : g0;
         z.ln.base = static_cast<char *>(job.pa->Wn);
         z.ln.step = static_cast<size_t>(2) * ny * CSZ;
         z.ln.lane = static_cast<uint32_t>((static_cast<size_t>(t) * 2 * ny + ky) * CSZ);
+        line = static_cast<uint32_t>((ky <= ny ? ky : 2 * ny - ky) * (GL == 2 ? N + 1 : 1));
+        z.u = (GL == 2 ? 1 : 2 * (ny + 1)) * sizeof(T);
+        z.odd = (GL == 2 ? N / 2 + 1 : ny + 1) * sizeof(T);
     }
-    const int kyo = ky <= ny ? ky : 2 * ny - ky;
-    if constexpr (GL == 2) {
-        z.u = job.nyq ? 1 : kGroup;
-        z.o1 = (N / 2 + 1) * z.u;
-        gb = job.nyq ? static_cast<size_t>(kyo) * (N + 1)
-                     : (static_cast<size_t>(kyo) * ((nx + kGroup - 1) / kGroup) + kx / kGroup) * (kGroup * (N + 1)) + kx % kGroup;
-    } else {
-        const size_t s = job.nyq ? ny + 1 : static_cast<size_t>(ny + 1) * nx;
-        z.u = 2 * s;
-        z.o1 = s;
-        gb = job.nyq ? kyo : static_cast<size_t>(kyo) * nx + kx;
-    }
-    z.g = as_global(static_cast<const T *>(job.nyq ? pl.Gn : pl.G)) + gb;
+    z.g = uniform(reinterpret_cast<uint64_t>(job.nyq ? pl.Gn : pl.G) + base * sizeof(T));
+    z.u = uniform(static_cast<uint64_t>(z.u));
+    z.odd = uniform(static_cast<uint64_t>(z.odd));
+    z.up = static_cast<uint32_t>(line * sizeof(T) + t * z.u);
+    z.dn = static_cast<uint32_t>(line * sizeof(T) + (NB - t) * z.u);
     return z;
 }
 
+// Load at a workgroup-uniform address plus 32 bits per lane.  The empty asm keeps the uniform part
+// whole in scalar registers: where it is a constant distance from another one, the compiler would
+// otherwise form 64-bit vector addresses (two registers and an add per load).
+template <typename T>
+__device__ __forceinline__ T load_from(uint64_t base, uint32_t lane) {
+    asm("" : "+s"(base));
+    return *reinterpret_cast<const gbl<T> *>(reinterpret_cast<const gbl<char> *>(base) + lane);
+}
+
 // Spectrum values of transform s at the last stage's positions p = b + r*nL: kz = 2p + s, even about n.
-template <typename T, int N, int GL, int SH>
-__device__ __forceinline__ void mix_load_g(const MixZ<T, N, GL> &z, T *gv, int t) {
-    using G = MixLen<N>;
-    using F = MixFFT<T, N, 1, 0>;
-    F::template each<G::RL>(t, [&](auto ic, int b) {
+template <typename T, int N, int SH>
+__device__ __forceinline__ void mix_load_g(const MixZ<T> &z, T *gv, int t) {
+    using G = MixLen<T, N>;
+    using F = MixFFT<T, G, 1, 0>;
+    F::template each<G::RL>(t, [&](auto ic, int) {
         constexpr int i = decltype(ic)::value;
-        const gbl<const T> *up = z.g + SH * z.o1 + b * z.u;
-        const gbl<const T> *dn = z.g + SH * z.o1 - b * z.u;
         sfor<0, G::RL>([&](auto rc) {
             constexpr int r = decltype(rc)::value;
-            constexpr int p0 = r * G::nL, p1 = p0 + G::nL - 1;  // positions of the butterflies
-            const gbl<const T> *a = up + p0 * z.u, *m = dn + (N - p0 - SH) * z.u;
-            if constexpr (2 * p1 + SH <= N) gv[i * G::RL + r] = *a;
-            else if constexpr (2 * p0 + SH > N) gv[i * G::RL + r] = *m;
-            else gv[i * G::RL + r] = 2 * (p0 + b) + SH <= N ? *a : *m;
+            constexpr int p0 = G::NB * i + r * G::nL;                                   // position for t = 0
+            constexpr int p1 = p0 + (G::NB < G::nL - G::NB * i ? G::NB : G::nL - G::NB * i) - 1;  // and the last t
+            const uint64_t a = z.g + (SH ? z.odd : 0);
+            // (at kz = n both sides name the same value)
+            const uint64_t up = a + p0 * z.u;
+            const uint64_t dn = a + static_cast<uint64_t>(static_cast<int64_t>(N - p0 - SH - G::NB)) * z.u;
+            T &o = gv[i * G::RL + r];
+            if constexpr (2 * p1 + SH <= N) o = load_from<T>(up, z.up);
+            else if constexpr (2 * p0 + SH >= N) o = load_from<T>(dn, z.dn);
+            else o = *reinterpret_cast<const gbl<T> *>(2 * (p0 + t) + SH <= N ? up + z.up : dn + z.dn);
         });
     });
 }
@@ -384,12 +451,11 @@ __device__ __forceinline__ void mix_load_g(const MixZ<T, N, GL> &z, T *gv, int t
 // transform has read them, ahead of the stores (loads and stores retire in order, so no wait for
 // the line covers them; lanes without a line store past the buffer's range).
 template <typename T, int N, int MODE, int GL, bool PERSIST>
-__global__ void __launch_bounds__((MixTile<T, N>::BLOCK), (MODE == Z_CONV ? MixTile<T, N>::WPS : 1))
+__global__ void __launch_bounds__((MixTile<T, N, MODE == Z_CONV>::BLOCK), (MixTile<T, N, MODE == Z_CONV>::WPS))
 mix_col_kernel(const LaunchArgs args) {
-    using G = MixLen<N>;
-    using C = MixTile<T, N>;
-    constexpr int TILE = C::TILE, NB = G::NB;
-    using F = MixFFT<T, N, TILE, 0>;
+    using G = MixLen<T, N>;
+    constexpr int TILE = MixTile<T, N, MODE == Z_CONV>::TILE, NB = G::NB;
+    using F = MixFFT<T, G, TILE, 0>;
     extern __shared__ __align__(16) unsigned char smem[];
     cx<T> *lds = reinterpret_cast<cx<T> *>(smem);
     TileWalk walk = tile_walk<true>();
@@ -405,7 +471,7 @@ mix_col_kernel(const LaunchArgs args) {
     if constexpr (MODE == Z_CONV) {
         cx<T> x[G::V0], v[G::V], e[G::V0];
         T gv[G::VL];
-        auto load = [&](const MixZ<T, N, GL> &z) __attribute__((always_inline)) {
+        auto load = [&](const MixZ<T> &z) __attribute__((always_inline)) {
             F::template each<G::R0>(t, [&](auto ic, int) {
                 constexpr int i = decltype(ic)::value;
                 sfor<0, G::R0>([&](auto rc) {
@@ -420,14 +486,14 @@ mix_col_kernel(const LaunchArgs args) {
         };
         auto cur = mix_z_line<T, N, TILE, GL>(args, bid, c, t);
         load(cur);
-        mix_load_g<T, N, GL, 0>(cur, gv, t);
+        mix_load_g<T, N, 0>(cur, gv, t);
         if constexpr (PERSIST) __builtin_amdgcn_s_waitcnt(0x0f70);  // nothing outstanding on entry (vmcnt 0)
         __syncthreads();  // twiddles visible
         for (;;) {
             if constexpr (PERSIST) asm volatile("" : "+v"(t), "+v"(c));  // addresses are derived again per tile
             F::template fwd<0>(x, v, lds + c, tw0, t);
             multiply();
-            mix_load_g<T, N, GL, 1>(cur, gv, t);
+            mix_load_g<T, N, 1>(cur, gv, t);
             F::template inv<0, false>(v, e, lds + c, tw0, t);
             F::template fwd<1>(x, v, lds + c, tw1, t);
             multiply();
@@ -440,7 +506,7 @@ mix_col_kernel(const LaunchArgs args) {
                 bid = more ? nb : bid;
                 nxt = mix_z_line<T, N, TILE, GL>(args, bid, c, t);
                 load(nxt);
-                mix_load_g<T, N, GL, 0>(nxt, gv, t);
+                mix_load_g<T, N, 0>(nxt, gv, t);
             }
             F::template inv<1, true>(v, e, lds + c, tw1, t);
             if constexpr (PERSIST) {
@@ -482,7 +548,7 @@ mix_col_kernel(const LaunchArgs args) {
         if (!job.nyq) {
             one.active = g < nz * nx;
             const int gg = one.active ? g : g0;
-            const int z0 = g0 / nx, z = gg / nx, kx = gg - z * nx;
+            const int z0 = uniform(g0 / nx), z = gg / nx, kx = gg - z * nx;
             const size_t row0 = w_row(z0, 0, ny, nx, zb);
             one.base = static_cast<char *>(job.pa->W) + row0 * CSZ;
             one.step = static_cast<size_t>(zb) * nx * CSZ;
@@ -554,16 +620,65 @@ mix_col_kernel(const LaunchArgs args) {
     }
 }
 
+// Packed value j of a source row s of N reals (zero padding past the row): P0 <= j < P0 + COUNT.
+// Odd rows are read as single reals, the last one without a partner.
+template <typename T, int N, int P0, int COUNT>
+__device__ __forceinline__ cx<T> mix_source(const T *s, int j) {
+    constexpr int J = (N + 1) / 2;
+    cx<T> u = {T(0), T(0)};
+    if constexpr (P0 < J) {
+        if (P0 + COUNT <= J || j < J) {
+            if constexpr (N % 2 == 0) {
+                u = reinterpret_cast<const cx<T> *>(s)[j];
+            } else {
+                u.x = s[2 * j];
+                if (2 * j + 1 < N) u.y = s[2 * j + 1];
+            }
+        }
+    }
+    return u;
+}
+// The same for the potential row f.
+template <typename T, int N, int P0, int COUNT>
+__device__ __forceinline__ void mix_potential(T *f, int j, cx<T> u) {
+    constexpr int J = (N + 1) / 2;
+    if constexpr (P0 < J) {
+        if (P0 + COUNT <= J || j < J) {
+            if constexpr (N % 2 == 0) {
+                reinterpret_cast<cx<T> *>(f)[j] = u;
+            } else {
+                f[2 * j] = u.x;
+                if (2 * j + 1 < N) f[2 * j + 1] = u.y;
+            }
+        }
+    }
+}
+// Split step of the packed real transform, X[k] from u = U[k], w = U[n-k] and e = exp(-i pi k/n):
+// (u + w*)/2 - (i/2) e (u - w*); and the inverse one, U[k] from a = X[k], m = X[n-k]:
+// (a + m*) + i conj(e) (a - m*).
+template <typename T>
+__device__ __forceinline__ cx<T> mix_split(cx<T> u, cx<T> w, cx<T> e) {
+    const cx<T> a = {static_cast<T>(0.5) * (u.x + w.x), static_cast<T>(0.5) * (u.y - w.y)};
+    const cx<T> d = {static_cast<T>(0.5) * (u.x - w.x), static_cast<T>(0.5) * (u.y + w.y)};
+    const cx<T> ed = cmul(e, d);
+    return cx<T>{a.x + ed.y, a.y - ed.x};
+}
+template <typename T>
+__device__ __forceinline__ cx<T> mix_unsplit(cx<T> a, cx<T> m, cx<T> e) {
+    const cx<T> sm = {a.x + m.x, a.y - m.y}, df = {a.x - m.x, a.y + m.y};
+    const cx<T> ed = cmulc(df, e);
+    return cx<T>{sm.x - ed.y, sm.y + ed.x};
+}
+
 // Row passes: rows r = z*ny + y of S / Phi, packed u[j] = s[2j] + i s[2j+1] (zero for 2j >= nx),
 // a transform of N = nx points and the split step with exp(-i pi k / n), as in the other row
 // kernels.  Consecutive lanes walk along a row.
 template <typename T, int N, int MODE>
 __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const LaunchArgs args) {
-    using G = MixLen<N>;
+    using G = MixLen<T, N>;
     using C = MixRow<T, N>;
     constexpr int NB = G::NB, ROWS = C::ROWS, S = C::S;
-    constexpr int J = (N + 1) / 2;  // packed values of a source row
-    using F = MixFFT<T, N, 1, C::PAD>;
+    using F = MixFFT<T, G, 1, C::PAD>;
     extern __shared__ __align__(16) unsigned char smem[];
     cx<T> *lds = reinterpret_cast<cx<T> *>(smem);
     const int bid = tile_walk<true>().tile();
@@ -592,19 +707,7 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
             constexpr int i = decltype(ic)::value;
             sfor<0, G::R0>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
-                const int j = b + r * G::n0;
-                cx<T> u = {T(0), T(0)};
-                if constexpr (r * G::n0 < J) {
-                    if ((r + 1) * G::n0 <= N / 2 || j < J) {
-                        if constexpr (N % 2 == 0) {
-                            u = reinterpret_cast<const cx<T> *>(s)[j];
-                        } else {  // odd rows: single reals, the last value has no partner
-                            u.x = s[2 * j];
-                            if (2 * j + 1 < N) u.y = s[2 * j + 1];
-                        }
-                    }
-                }
-                x[i * G::R0 + r] = u;
+                x[i * G::R0 + r] = mix_source<T, N, r * G::n0, G::n0>(s, b + r * G::n0);
             });
         });
         __syncthreads();  // tables visible
@@ -626,10 +729,7 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
                     constexpr int r = decltype(rc)::value;
                     const int k = b + r * G::nL;
                     const cx<T> u = v[i * G::RL + r], w = row[slot(k == 0 ? 0 : N - k)];
-                    const cx<T> a = {static_cast<T>(0.5) * (u.x + w.x), static_cast<T>(0.5) * (u.y - w.y)};
-                    const cx<T> d = {static_cast<T>(0.5) * (u.x - w.x), static_cast<T>(0.5) * (u.y + w.y)};
-                    const cx<T> ed = cmul(post[k], d);
-                    wrow[k] = cx<T>{a.x + ed.y, a.y - ed.x};  // a - i e d
+                    wrow[k] = mix_split(u, w, post[k]);
                     if (k == 0) *wnyq = cx<T>{u.x - u.y, T(0)};
                 });
             });
@@ -656,9 +756,7 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
                 constexpr int r = decltype(rc)::value;
                 const int k = b + r * G::nL;
                 const cx<T> a = v[i * G::RL + r], m = k == 0 ? xn : row[slot(N - k)];
-                const cx<T> sm = {a.x + m.x, a.y - m.y}, df = {a.x - m.x, a.y + m.y};
-                const cx<T> ed = cmulc(df, post[k]);
-                v[i * G::RL + r] = cx<T>{sm.x - ed.y, sm.y + ed.x};
+                v[i * G::RL + r] = mix_unsplit(a, m, post[k]);
             });
         });
         __syncthreads();  // partners read
@@ -669,28 +767,18 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
                 constexpr int i = decltype(ic)::value;
                 sfor<0, G::R0>([&](auto rc) {
                     constexpr int r = decltype(rc)::value;
-                    const int j = b + r * G::n0;
-                    if constexpr (r * G::n0 < J) {
-                        if ((r + 1) * G::n0 <= N / 2 || j < J) {
-                            if constexpr (N % 2 == 0) {
-                                reinterpret_cast<cx<T> *>(f)[j] = x[i * G::R0 + r];
-                            } else {
-                                f[2 * j] = x[i * G::R0 + r].x;
-                                if (2 * j + 1 < N) f[2 * j + 1] = x[i * G::R0 + r].y;
-                            }
-                        }
-                    }
+                    mix_potential<T, N, r * G::n0, G::n0>(f, b + r * G::n0, x[i * G::R0 + r]);
                 });
             });
         }
     }
 }
 
-// z passes that run persistently: lines beyond 1024 points in FP32 (one workgroup per CU).
-// Measured, z pass of 576 x 576 lines of 1152 points: 7.2 ms with two one-tile workgroups of
-// 4 lines per CU, 5.7 ms persistently with 8.
+// z passes that run persistently: FP32 lines whose workgroup of 8 lines exceeds 512 threads, so that
+// one fills a CU.  Measured, z pass of 576 x 576 lines of 1152 points: 7.2 ms with two one-tile
+// workgroups of 4 lines per CU, 6.1 ms with 8 lines and one tile, 5.7 ms persistently.
 template <typename T, int N>
-constexpr bool mix_z_persist() { return sizeof(T) == 4 && N > 1024; }
+constexpr bool mix_z_persist() { return sizeof(T) == 4 && MixTile<T, N, true>::BLOCK > 512; }
 
 template <typename T, int N>
 hipError_t launch_mix(int mode, const LaunchArgs &args, hipStream_t stream) {
@@ -718,8 +806,10 @@ hipError_t launch_mix(int mode, const LaunchArgs &args, hipStream_t stream) {
         cus[dev] = n > 0 ? n : 1;
     }
     const bool row = mode == X_FWD || mode == X_INV;
-    const int block = row ? MixRow<T, N>::BLOCK : MixTile<T, N>::BLOCK;
-    const size_t lds = row ? MixRow<T, N>::LDS : MixTile<T, N>::LDS;
+    using CZ = MixTile<T, N, true>;
+    using CY = MixTile<T, N, false>;
+    const int block = row ? MixRow<T, N>::BLOCK : (mode == Z_CONV ? CZ::BLOCK : CY::BLOCK);
+    const size_t lds = row ? MixRow<T, N>::LDS : (mode == Z_CONV ? CZ::LDS : CY::LDS);
     // whole rounds of the chunked tile order, or one persistent workgroup per CU
     int grid = (args.nwg + 8 * kTileChunk - 1) / (8 * kTileChunk) * (8 * kTileChunk);
     if (mode == Z_CONV && PZ && grid > cus[dev]) grid = cus[dev];
@@ -730,7 +820,7 @@ hipError_t launch_mix(int mode, const LaunchArgs &args, hipStream_t stream) {
 }  // namespace pspfft
 
 // One translation unit per precision and list of lengths keeps compiles parallel.
-#define PSPFFT_MIX_LAUNCH(N, A, B, C) case N: return launch_mix<MixReal, N>(mode, args, stream);
+#define PSPFFT_MIX_LAUNCH(N, A, B, C, D, E) case N: return launch_mix<MixReal, N>(mode, args, stream);
 #define PSPFFT_MIX_UNIT(T, NAME, LIST)                                                   \
     namespace pspfft {                                                                   \
     hipError_t NAME(int n, int mode, const LaunchArgs &args, hipStream_t stream) {       \

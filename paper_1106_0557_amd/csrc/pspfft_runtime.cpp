@@ -320,26 +320,27 @@ bool build_axis(int axis, int n, pspfft_precision prec, AxisPlan &ax, std::vecto
     return Ns == L;
 }
 
-// The axis of a mesh runs on half-length lines (mix_lines.h): the lengths of
-// mix_info() that no radix family takes, where a lane's share of an address
-// fits 32 bits (z: one first-stage position block of NB planes; y: the planes
-// that a tile's lines span, in tiles of up to 16).  Every such size moves to
-// that kernel: measured, one FP32 solve, against the generic line kernel, 480^3
-// 12.0 -> 4.4 ms, eight 120^3 946 -> 330 us.
+// The axis of a mesh runs on half-length lines (mix_lines.h): every length of
+// mix_info(), where a lane's share of an address fits 32 bits (z: one
+// first-stage position block of NB planes; y: the planes that a tile's lines
+// span, in tiles of up to 16).  Measured against the kernels that took the
+// lengths before, one solve: FP32 480^3 12.0 -> 2.7 ms, 512^3 3.46 -> 3.2, 768^3
+// 16.9 -> 14.4, 1024^3 46.6 -> 35.2, 1152^3 71.5 -> 57; 192^3 173 -> 147 us; FP64 512^3
+// 7.75 -> 6.8 ms, 288 x 144 x 144 423 -> 290 us.  Lines of 128 stay with the radix
+// families (twelve FP32 128^3 z passes 0.203 ms there, 0.207 here), except FP64
+// rows (four x passes 0.056 / 0.043 ms there, 0.053 / 0.040 here).
 bool mix_axis(int axis, const int n[3], pspfft_precision prec, pspfft::MixInfo &info) {
-    if (!pspfft::mix_info(n[axis], info)) return false;
-    if (family_axis(axis, n[axis], prec)) {
-        const char *e = std::getenv(axis == 0 ? "DEVMIX_X" : axis == 1 ? "DEVMIX_Y" : "DEVMIX_Z");
-        if (!e || n[axis] < std::atoi(e)) return false;
-    }
+    if (n[axis] == 128 && (axis == 2 || prec == PSPFFT_FP32)) return false;
+    if (!pspfft::mix_info(prec == PSPFFT_FP32 ? 0 : 1, n[axis], info)) return false;
     const size_t lim = (size_t(1) << 32) - 64, cs = cplx_size(prec), nx = n[0], ny = n[1];
     if (axis == 2) return info.nb * 2 * ny * nx * cs < lim;
     if (axis == 1) return ((16 / nx + 2 + 16) * 2 * ny * nx + size_t(2) * info.nb * 16 * nx) * cs < lim;
     return true;
 }
 
-// Appends the stage twiddles of half-length lines (AxisPlan::mtw).
-void mix_twiddles(const pspfft::MixInfo &info, std::vector<std::complex<double>> &tw) {
+// Appends the stage twiddles of half-length lines (AxisPlan::mtw) of n points: 2n values, whatever the stages.
+void mix_twiddles(int n, const pspfft::MixInfo &info, std::vector<std::complex<double>> &tw) {
+    const size_t end = tw.size() + 2 * static_cast<size_t>(n);
     for (int s = 0; s < 2; ++s) {
         int Ns = info.radix[0];
         for (int st = 1; st < 3 && info.radix[st] > 1; ++st) {
@@ -353,6 +354,7 @@ void mix_twiddles(const pspfft::MixInfo &info, std::vector<std::complex<double>>
             Ns *= R;
         }
     }
+    tw.resize(end, std::complex<double>(1.0, 0.0));
 }
 
 // Spectrum layout (DevPlan::gz 2) and size: values of G and of Gn.
@@ -555,8 +557,8 @@ pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_pla
             return reinterpret_cast<uintptr_t>(plans[a]) < reinterpret_cast<uintptr_t>(plans[b]);
         });
         pspfft::MixInfo info;
-        if (!pspfft::mix_info(n, info)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
-        const int tile = axis == 0 ? info.rows : info.tile[prec];
+        if (!pspfft::mix_info(prec, n, info)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
+        const int tile = axis == 0 ? info.rows : (axis == 1 ? info.tile_y : info.tile_z);
         for (size_t c0 = 0; c0 < idx.size(); c0 += pspfft::kMaxProblems) {
             const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
             LaunchArgs args;
@@ -779,25 +781,8 @@ pspfft_status launch_planes(bool fwd, const std::vector<int> &all, const pspfft_
         for (size_t c0 = 0; c0 < idx.size(); c0 += pspfft::kMaxProblems) {
             const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
             LaunchArgs args;
-            std::memset(&args, 0, sizeof(args));
-            args.count = static_cast<int>(c1 - c0);
+            add_problems(args, idx, c0, c1, plans, ws, S, Phi);
             args.nt = streaming_launch(plans, idx, c0, c1) ? 1 : 0;
-            for (size_t j = c0; j < c1; ++j) {
-                const int i = idx[j];
-                ProbArg &a = args.p[j - c0];
-                a.plan = plans[i]->dev;
-                a.S = S ? S[i] : nullptr;
-                a.Phi = Phi ? Phi[i] : nullptr;
-                a.W = ws[i]->W;
-                a.Wn = ws[i]->Wn;
-                if (j > c0 && plans[idx[j - 1]] == plans[i]) {
-                    args.seg[args.nseg - 1].group += 1;
-                    continue;
-                }
-                pspfft::Segment &sg = args.seg[args.nseg++];
-                sg.first = static_cast<int>(j - c0);
-                sg.group = 1;
-            }
             long wg = 0;
             for (int k = 0; k < args.nseg; ++k) {  // one workgroup per z plane
                 pspfft::Segment &sg = args.seg[k];
@@ -964,7 +949,7 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
     if (hipGetDevice(&p->device) != hipSuccess) return fail(PSPFFT_ERR_DEVICE, vlevel, "%s: hipGetDevice", who);
     for (int a = 0; a < 3; ++a) {
         mix_at[a] = tws[a].size();
-        if (mixed[a]) mix_twiddles(mix[a], tws[a]);
+        if (mixed[a]) mix_twiddles(p->n[a], mix[a], tws[a]);
         const std::vector<std::complex<double>> &tw = tws[a];
         const size_t tb = tw.size() * cs;
         pspfft_status st = alloc(&p->tw[a], tb);
@@ -994,6 +979,7 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
     {
         const size_t plane = static_cast<size_t>(2) * ny * nx * cs;
         int cap = plane >= (size_t(4) << 20) ? 16 : 1;
+        if (mixed[2]) cap = plane < (size_t(1) << 20) ? 1 : (nz > 512 && plane >= (size_t(4) << 20) ? 16 : 4);
         if (const char *e = std::getenv("PSPFFT_ZTILE")) {
             const int v = std::atoi(e);
             if (v >= 1 && v <= 16 && (v & (v - 1)) == 0) cap = v;
@@ -1305,7 +1291,7 @@ size_t pspfft_plan_resident_bytes(int nx, int ny, int nz, pspfft_precision prec)
         std::vector<std::complex<double>> tw;
         if (!build_axis(a, n[a], prec, ax, tw)) return 0;
         pspfft::MixInfo info;
-        if (mix_axis(a, n, prec, info)) mix_twiddles(info, tw);
+        if (mix_axis(a, n, prec, info)) mix_twiddles(n[a], info, tw);
         bytes += tw.size() * cplx_size(prec);
     }
     // spectrum octant: main part and the kx = nx column

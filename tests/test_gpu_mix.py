@@ -22,9 +22,15 @@ pytestmark = pytest.mark.gpu
 FP64_TOL = 1e-12
 FP32_TOL = 1e-5
 
-_HEADER = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1106_0557_amd", "csrc",
-                       "mix_lines.h")
-LENGTHS = sorted(int(m) for m in re.findall(r"\bX\((\d+), \d+, \d+, \d+\)", open(_HEADER).read()))
+_CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1106_0557_amd", "csrc")
+
+
+def _lengths(header, fields):
+    with open(os.path.join(_CSRC, header)) as f:
+        return sorted({int(m) for m in re.findall(r"\bX\((\d+)(?:, \d+){%d}\)" % fields, f.read())})
+
+
+LENGTHS = _lengths("mix_lines.h", 5)
 
 
 @pytest.fixture(scope="module", autouse=True)
