@@ -387,9 +387,15 @@ struct MixInfo {
     int nb, tile_z, tile_y, rows;
 };
 bool mix_info(int prec, int n, MixInfo &info);
+// The same for the plane kernels on these line transforms (mix_plane.h): the
+// x and y transforms of planes with nx = ny = n.
+bool mix_plane_info(int prec, int n, MixInfo &info);
 // Pass `mode` by half-length lines of n cells (x rows of n) for the problems of
 // args, whose segments count mix_info() tiles or rows.
 hipError_t launch_mix_lines(int mode, int prec, int n, const LaunchArgs &args, hipStream_t stream);
+
+// Plane kernels (mix_plane.h) for the planes of args (one workgroup each).
+hipError_t launch_mix_plane(bool fwd, int prec, int n, const LaunchArgs &args, hipStream_t stream);
 
 // Green's-function spectrum in FP64: fills the octant (nz+1)(ny+1)(nx+1) of G
 // into `a`, applies the even-extension cosine transform along each axis (using

@@ -1,5 +1,5 @@
 // Lengths of the half-length line kernels and the dispatch to their translation units.
-#include "mix_lines.h"
+#include "mix_plane.h"
 
 namespace pspfft {
 
@@ -20,6 +20,24 @@ bool mix_info(int prec, int n, MixInfo &info) {
         PSPFFT_MIX_ALL(PSPFFT_MIX_CASE_F64, PSPFFT_MIX_F64)
         default: return false;
     }
+}
+
+bool mix_plane_info(int prec, int n, MixInfo &info) {
+    switch (n + (prec << 16)) {
+#define PSPFFT_PLANE_CASE_F32(N, A, B, C, D) case N: info = MixInfo{{A, B, C}, D, 0, 0, N}; return true;
+#define PSPFFT_PLANE_CASE_F64(N, A, B, C, D) case N + (1 << 16): info = MixInfo{{A, B, C}, D, 0, 0, N}; return true;
+        PSPFFT_PLANE_F32(PSPFFT_PLANE_CASE_F32)
+        PSPFFT_PLANE_F64(PSPFFT_PLANE_CASE_F64)
+        default: return false;
+    }
+}
+
+hipError_t mix_plane_f32(int n, bool fwd, const LaunchArgs &args, hipStream_t stream);
+hipError_t mix_plane_f64(int n, bool fwd, const LaunchArgs &args, hipStream_t stream);
+
+hipError_t launch_mix_plane(bool fwd, int prec, int n, const LaunchArgs &args, hipStream_t stream) {
+    if (args.nwg <= 0) return hipSuccess;
+    return prec == 0 ? mix_plane_f32(n, fwd, args, stream) : mix_plane_f64(n, fwd, args, stream);
 }
 
 using MixUnit = hipError_t(int n, int mode, const LaunchArgs &args, hipStream_t stream);

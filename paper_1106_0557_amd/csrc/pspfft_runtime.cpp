@@ -42,7 +42,7 @@ struct pspfft_plan_s {
     size_t bytes = 0;        // resident bytes (without the default workspace)
     int device = 0;
     bool fused = false;      // x and y transforms of a z plane in one kernel
-    int pE = 0, pK = 0;      // radix family and last radix of those kernels
+    int pE = 0, pK = 0;      // radix family and last radix of those kernels; pE 0: mix_plane.h, n = pK
     int verbosity = -1;      // the plan's own message level (Sec. 3.2, VerbosityOption); -1: the process's
     std::mutex mu;           // guards the creation of the default workspace
 };
@@ -327,8 +327,8 @@ bool build_axis(int axis, int n, pspfft_precision prec, AxisPlan &ax, std::vecto
 // lengths before, one solve: FP32 480^3 12.0 -> 2.7 ms, 512^3 3.46 -> 3.2, 768^3
 // 16.9 -> 14.4, 1024^3 46.6 -> 35.2, 1152^3 71.5 -> 57; 192^3 173 -> 147 us; FP64 512^3
 // 7.75 -> 6.8 ms, 288 x 144 x 144 423 -> 290 us.  Lines of 128 stay with the radix
-// families (twelve FP32 128^3 z passes 0.203 ms there, 0.207 here), except FP64
-// rows (four x passes 0.056 / 0.043 ms there, 0.053 / 0.040 here).
+// families (twelve FP32 128^3 z passes 0.203 ms there, 0.207 here; four FP64 ones
+// 0.147 and 0.156), except FP64 rows and y lines (a single 128^3 solve 108 -> 105 us).
 bool mix_axis(int axis, const int n[3], pspfft_precision prec, pspfft::MixInfo &info) {
     if (n[axis] == 128 && (axis == 2 || prec == PSPFFT_FP32)) return false;
     if (!pspfft::mix_info(prec == PSPFFT_FP32 ? 0 : 1, n[axis], info)) return false;
@@ -336,6 +336,17 @@ bool mix_axis(int axis, const int n[3], pspfft_precision prec, pspfft::MixInfo &
     if (axis == 2) return info.nb * 2 * ny * nx * cs < lim;
     if (axis == 1) return ((16 / nx + 2 + 16) * 2 * ny * nx + size_t(2) * info.nb * 16 * nx) * cs < lim;
     return true;
+}
+
+// x and y transforms of a plane by the plane kernels on half-length lines
+// (mix_plane.h): the lengths outside the radix families, and up to 64 the others
+// too, where the threads of a plane are few and each solve waits for its chain
+// of stages.  Measured, us per sequential solve: FP64 24^3 26.0 -> 17.4, 32^3 22.2 ->
+// 17.0, 36^3 36.5 -> 20.8; FP32 48^3 27.0 -> 20.8, 64^3 26.2 -> 22.9 (32 of them
+// 156 -> 154 us).
+bool mix_plane(const int n[3], pspfft_precision prec, pspfft::MixInfo &info) {
+    if (n[0] != n[1] || !pspfft::mix_plane_info(prec == PSPFFT_FP32 ? 0 : 1, n[0], info)) return false;
+    return n[0] <= 64 || !family_axis(0, n[0], prec);
 }
 
 // Appends the stage twiddles of half-length lines (AxisPlan::mtw) of n points: 2n values, whatever the stages.
@@ -777,7 +788,7 @@ pspfft_status launch_planes(bool fwd, const std::vector<int> &all, const pspfft_
         std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) {
             return reinterpret_cast<uintptr_t>(plans[a]) < reinterpret_cast<uintptr_t>(plans[b]);
         });
-        const size_t lds = pspfft::plane_lds_bytes(prec, E, K);
+        const size_t lds = E ? pspfft::plane_lds_bytes(prec, E, K) : 0;
         for (size_t c0 = 0; c0 < idx.size(); c0 += pspfft::kMaxProblems) {
             const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
             LaunchArgs args;
@@ -794,7 +805,8 @@ pspfft_status launch_planes(bool fwd, const std::vector<int> &all, const pspfft_
             args.nwg = static_cast<int>(wg);
             PSPFFT_LOG(3, "plane %s prec %d E %d K %d: %d problems, %ld workgroups of %d threads, %zu B LDS, "
                           "streaming %d", fwd ? "fwd" : "inv", prec, E, K, args.count, wg, E * K * K, lds, args.nt);
-            if (pspfft::launch_plane(fwd, prec, E, K, args, static_cast<int>(wg), lds, stream) != hipSuccess)
+            if ((E ? pspfft::launch_plane(fwd, prec, E, K, args, static_cast<int>(wg), lds, stream)
+                   : pspfft::launch_mix_plane(fwd, prec, K, args, stream)) != hipSuccess)
                 return PSPFFT_ERR_DEVICE;
         }
     }
@@ -915,10 +927,11 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
     // stage plans and twiddle tables (FP64, rounded once to the plan precision)
     std::vector<std::complex<double>> tws[3];
     pspfft::MixInfo mix[3];
-    bool mixed[3];
+    bool mixed[3], planes = false;
     size_t mix_at[3];
     for (int a = 0; a < 3; ++a) {
         mixed[a] = mix_axis(a, p->n, prec, mix[a]);
+        if (a == 0 && !(flags & PSPFFT_PLAN_FIVE_PASS) && mix_plane(p->n, prec, mix[0])) mixed[0] = planes = true;
         if (!build_axis(a, p->n[a], prec, p->host.ax[a], tws[a]))
             return fail(PSPFFT_ERR_UNSUPPORTED_SIZE, vlevel, "%s: no stage plan for axis %d (n = %d)", who, a,
                         p->n[a]);
@@ -990,6 +1003,7 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
             nbz = n0 <= mix[2].nb ? n0 : std::gcd(n0, mix[2].nb);
         }
         int zb = 1;  // generic z lines (NB = 0): no tiling, nz need not be a multiple of anything
+        if (planes) cap = 1;  // the plane kernels take untiled workspaces
         while (nbz > 0 && zb < cap && nbz % (2 * zb) == 0) zb *= 2;
         p->host.zb = zb;
     }
@@ -1007,6 +1021,12 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
         if (p->fused) {
             p->pE = ax.E;
             p->pK = K;
+        }
+        if (planes) {
+            if (p->host.zb != 1) return fail(PSPFFT_ERR_UNSUPPORTED_SIZE, vlevel, "%s: z tiles of a fused plan", who);
+            p->fused = true;
+            p->pE = 0;
+            p->pK = nx;
         }
     }
 
@@ -1291,7 +1311,7 @@ size_t pspfft_plan_resident_bytes(int nx, int ny, int nz, pspfft_precision prec)
         std::vector<std::complex<double>> tw;
         if (!build_axis(a, n[a], prec, ax, tw)) return 0;
         pspfft::MixInfo info;
-        if (mix_axis(a, n, prec, info)) mix_twiddles(n[a], info, tw);
+        if (mix_axis(a, n, prec, info) || (a == 0 && mix_plane(n, prec, info))) mix_twiddles(n[a], info, tw);
         bytes += tw.size() * cplx_size(prec);
     }
     // spectrum octant: main part and the kx = nx column

@@ -31,6 +31,7 @@ def _lengths(header, fields):
 
 
 LENGTHS = _lengths("mix_lines.h", 5)
+PLANES = _lengths("mix_plane.h", 4)
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -61,6 +62,23 @@ def check(n, dtypes=(torch.float64, torch.float32)):
 def test_every_length_on_each_axis(n):
     for mesh in ((n, 3, 2), (2, n, 3), (3, 2, n)):
         check(mesh)
+
+
+# x and y transforms of a plane in one kernel, odd and even n, against the five-pass plan too
+@pytest.mark.parametrize("n", PLANES)
+def test_planes(n):
+    from paper_1106_0557_amd import Plan
+
+    check((n, n, 5))
+    S = sources.random_field((n, n, 5), seed=n).to("cuda")
+    for dt, tol in ((torch.float64, FP64_TOL), (torch.float32, FP32_TOL)):
+        out = []
+        for five in (False, True):
+            plan = Plan(n, n, 5, h=0.1, dtype=dt, five_pass=five)
+            assert not (five and plan.fused)
+            out.append(plan.solve(S.to(dt)).double().cpu().numpy())
+            plan.close()
+        assert norms.rel_l2(out[0], out[1]) <= tol
 
 
 # several tiles per launch with a partial last one, three mixed axes, odd rows, and z lines
