@@ -70,6 +70,7 @@ struct AxisPlan {
 struct DevPlan {
     int nx, ny, nz, prec;  // prec: 0 = FP32, 1 = FP64
     int zb;                // z planes per tile of the workspace
+    int ks;                // log2 of the kx per slab of the workspace (w_slab; kNoSlabs: one slab)
     int gz;                // spectrum layout (above)
     AxisPlan ax[3];        // x, y, z
     const void *G;         // spectrum, main part
@@ -107,6 +108,7 @@ struct LaunchArgs {
     int xcd_remap;    // renumber workgroups so each XCD gets a contiguous range
     int wave_z;       // z pass: spectra kz-fastest, lines kept within one wavefront
     int gtile;        // generic line kernel: lines per workgroup (a power of two)
+    int rounds;       // half-length x rows: tiles that a workgroup takes one after the other (0: one)
     int glmax;        // generic line kernel: longest line of the launch
     int gtw;          // generic line kernel: stage twiddles copied into LDS after the two buffers
     int nt;           // streaming launch (workspaces beyond kStreamBytes): its line data takes
@@ -121,6 +123,27 @@ enum PassMode { X_FWD = 0, Y_FWD = 1, Z_CONV = 2, Y_INV = 3, X_INV = 4 };
 __host__ __device__ inline size_t w_row(int z, int ky, int ny, int nx, int zb) {
     const int sh = __builtin_ctz(static_cast<unsigned>(zb));  // zb is a power of two
     return ((static_cast<size_t>(z >> sh) * 2 * ny + ky) * zb + (z & (zb - 1))) * static_cast<size_t>(nx);
+}
+
+// Slabs of kx: the workspace main part of a large mesh is split along kx into slabs of kSlab values
+// (the last one may hold fewer), one after the other, each with the layout of w_row for rows of its
+// own width.  A y or z line then lies within one slab: without them, the lines of a z pass step
+// through the whole workspace, and beyond about 4 GB a CU's translation cache has lost a page when the
+// next tile comes back to it.  Measured, misses per z tile of 640, 768 and 1024 points (FP32 n^3): 49,
+// 96 and 139, and none at 576; one solve without and with slabs, ms: FP32 576^3 5.5 and 5.4, 640^3 8.1
+// and 7.1, 1024^3 36.6 and 28.7, 1152^3 57.9 and 49.2, FP64 640^3 17.3 and 15.5; no gain below
+// kSlabBytes (FP64 432^3 4.1 and 4.1, where x passes write 512-byte pieces for nothing).  Widths 16, 32, 64 and
+// 128 differ by 2 to 4 % (32 best); whole numbers of tiles fill each.
+constexpr int kSlabShift = 5, kSlab = 1 << kSlabShift, kNoSlabs = 30;
+constexpr size_t kSlabBytes = size_t(5) << 29;
+struct Slab {
+    int kx0, w;     // its first kx and width
+    size_t start;   // elements before it
+};
+__host__ __device__ inline Slab w_slab(int s, int ks, int nx, int ny, int nz) {
+    const int kx0 = s << ks, rest = nx - kx0;
+    const int w = rest < (1 << ks) ? rest : 1 << ks;
+    return Slab{kx0, w, static_cast<size_t>(kx0) * 2 * ny * nz};
 }
 
 // LDS layout of a workgroup (complex elements), identical on host and device.

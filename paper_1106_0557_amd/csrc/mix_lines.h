@@ -131,6 +131,7 @@ struct MixTile {
     static constexpr int BLOCK = TILE * G::NB;
     static constexpr size_t LDS = static_cast<size_t>(lds(TILE));
     static_assert(BLOCK <= 1024 && LDS <= 160 * 1024, "one workgroup fits");
+    static_assert(kSlab % TILE == 0, "no tile has lines of two slabs");
     // wavefronts per SIMD the z kernel is compiled for: two workgroups of 384 to 512 threads per
     // CU, three of 128 to 320; FP64 and the longest registers, what they leave
     static constexpr int WPS = !Z ? 1
@@ -139,7 +140,9 @@ struct MixTile {
                                    : (BLOCK > 512 ? 1 : (BLOCK >= 384 ? 4 : (BLOCK >= 128 ? 3 : 1)));
 };
 
-// x rows per workgroup: about 256 threads.  LDS row stride: positions P at
+// x rows per workgroup: about 256 threads.  In launches of many tiles a workgroup takes `rounds` of
+// them one after the other (mix_rounds), as each begins with the tables: at 1152 points 18 KB beside
+// two rows of 9 KB.  LDS row stride: positions P at
 // P + P/R0 for even R0 (consecutive butterflies then start on different banks).
 template <typename T, int N>
 struct MixRow {
@@ -305,6 +308,30 @@ __device__ __forceinline__ uint64_t uniform(uint64_t v) {
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+// Copy of a table of COUNT values into LDS by a workgroup of BLOCK threads in two steps: its loads go
+// out ahead of the line's own, and are written when those are on their way, so a workgroup starts
+// with one wait for memory instead of two.
+template <typename T, int COUNT, int BLOCK>
+struct MixTable {
+    static constexpr int D = ceil_div(COUNT, BLOCK);
+    T re[D], im[D];
+    __device__ __forceinline__ void load(const void *src, int tid) {
+        const auto *p = as_global(static_cast<const cx<T> *>(src));
+        sfor<0, D>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const int j = (i + 1) * BLOCK <= COUNT ? tid + i * BLOCK : min(tid + i * BLOCK, COUNT - 1);
+            re[i] = p[j].x;
+            im[i] = p[j].y;
+        });
+    }
+    __device__ __forceinline__ void store(cx<T> *dst, int tid) const {
+        sfor<0, D>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            if ((i + 1) * BLOCK <= COUNT || tid + i * BLOCK < COUNT) dst[tid + i * BLOCK] = cx<T>{re[i], im[i]};
+        });
+    }
+};
+
 // Problem and tile of a workgroup (segments are numbered tile-major, so that
 // problems sharing a plan read one spectrum slice together).
 struct MixJob {
@@ -363,6 +390,13 @@ __device__ __forceinline__ MixRowKx mix_z_row(int g, int nx, int ny) {
     return MixRowKx{second ? 2 * ny - 1 - pr : 1 + pr, j * TILE + rem - (second ? w : 0)};
 }
 
+// Slab of a tile that starts at line g0, with `lines` lines per kx (a whole number of tiles fills each
+// slab but the last, so that no tile has lines of two).
+template <typename P>
+__device__ __forceinline__ Slab mix_slab(P &pl, int g0, int lines) {
+    return w_slab(pl.ks < 30 ? uniform(g0 / (lines << pl.ks)) : 0, pl.ks, pl.nx, pl.ny, pl.nz);
+}
+
 template <typename T, int N, int TILE, int GL>
 __device__ __forceinline__ MixZ<T> mix_z_line(const LaunchArgs &args, int bid, int c, int t) {
     using cplan = const __attribute__((address_space(4))) DevPlan;
@@ -376,13 +410,17 @@ __device__ __forceinline__ MixZ<T> mix_z_line(const LaunchArgs &args, int bid, i
     size_t base = 0, line;  // values of the octant: before the tile's first row, and the lane's own
     if (!job.nyq) {
         z.ln.active = g < 2 * ny * nx;
-        const MixRowKx f = mix_z_row<TILE>(g0, nx, ny), q = mix_z_row<TILE>(z.ln.active ? g : g0, nx, ny);
+        const Slab sl = mix_slab(pl, g0, 2 * ny);
+        const int l0 = g0 - sl.kx0 * 2 * ny, l = z.ln.active ? l0 + c : l0;
+        const MixRowKx f = mix_z_row<TILE>(l0, sl.w, ny);
+        MixRowKx q = mix_z_row<TILE>(l, sl.w, ny);
         const int zb = pl.zb, sh = __builtin_ctz(static_cast<unsigned>(zb));
-        const size_t plane = static_cast<size_t>(2) * ny * nx;
-        z.ln.base = static_cast<char *>(job.pa->W);
+        const size_t plane = static_cast<size_t>(2) * ny * sl.w;
+        z.ln.base = static_cast<char *>(job.pa->W) + sl.start * CSZ;
         z.ln.step = plane * CSZ;  // zb divides NB and n0: whole tiles from one first-stage register to the next
         z.ln.lane = static_cast<uint32_t>(
-            ((static_cast<size_t>(t >> sh) << sh) * plane + (static_cast<size_t>(q.ky) * zb + (t & (zb - 1))) * nx + q.kx) * CSZ);
+            ((static_cast<size_t>(t >> sh) << sh) * plane + (static_cast<size_t>(q.ky) * zb + (t & (zb - 1))) * sl.w + q.kx) * CSZ);
+        q.kx += sl.kx0;
         const int k0 = uniform(f.ky <= ny ? f.ky : 2 * ny - f.ky), kyo = q.ky <= ny ? q.ky : 2 * ny - q.ky;
         if constexpr (GL == 2) {
             const int row = (nx + kGroup - 1) / kGroup * kGroup * (N + 1);
@@ -465,7 +503,11 @@ mix_col_kernel(const LaunchArgs args) {
     int c = tid % TILE, t = tid / TILE;  // adjacent lanes on adjacent lines
     const AxisPlan &ax = args.p[0].plan->ax[MODE == Z_CONV ? 2 : 1];
     cx<T> *twl = lds + N * TILE;
-    copy_to_lds<T>(twl, ax.mtw, 2 * G::NTW);
+    // (y passes with a CU to themselves: measured, 7 % of the inverse pass of 1152 points for the plain copy)
+    constexpr bool EARLY = MODE == Z_CONV || 2 * MixTile<T, N, false>::LDS <= 160 * 1024;
+    MixTable<T, 2 * G::NTW, MixTile<T, N, MODE == Z_CONV>::BLOCK> table;
+    if constexpr (EARLY) table.load(ax.mtw, tid);
+    else copy_to_lds<T>(twl, ax.mtw, 2 * G::NTW);
     const cx<T> *tw0 = twl, *tw1 = twl + G::NTW;
 
     if constexpr (MODE == Z_CONV) {
@@ -487,6 +529,7 @@ mix_col_kernel(const LaunchArgs args) {
         auto cur = mix_z_line<T, N, TILE, GL>(args, bid, c, t);
         load(cur);
         mix_load_g<T, N, 0>(cur, gv, t);
+        table.store(twl, tid);
         if constexpr (PERSIST) __builtin_amdgcn_s_waitcnt(0x0f70);  // nothing outstanding on entry (vmcnt 0)
         __syncthreads();  // twiddles visible
         for (;;) {
@@ -547,12 +590,13 @@ mix_col_kernel(const LaunchArgs args) {
         uint32_t lane;
         if (!job.nyq) {
             one.active = g < nz * nx;
-            const int gg = one.active ? g : g0;
-            const int z0 = uniform(g0 / nx), z = gg / nx, kx = gg - z * nx;
-            const size_t row0 = w_row(z0, 0, ny, nx, zb);
-            one.base = static_cast<char *>(job.pa->W) + row0 * CSZ;
-            one.step = static_cast<size_t>(zb) * nx * CSZ;
-            lane = static_cast<uint32_t>((w_row(z, 0, ny, nx, zb) - row0 + kx) * CSZ);
+            const Slab sl = mix_slab(pl, g0, nz);
+            const int l0 = g0 - sl.kx0 * nz, l = one.active ? l0 + c : l0;
+            const int z0 = uniform(l0 / sl.w), z = l / sl.w, kx = l - z * sl.w;
+            const size_t row0 = w_row(z0, 0, ny, sl.w, zb);
+            one.base = static_cast<char *>(job.pa->W) + (sl.start + row0) * CSZ;
+            one.step = static_cast<size_t>(zb) * sl.w * CSZ;
+            lane = static_cast<uint32_t>((w_row(z, 0, ny, sl.w, zb) - row0 + kx) * CSZ);
         } else {
             one.active = g < nz;
             one.base = static_cast<char *>(job.pa->Wn);
@@ -594,6 +638,7 @@ mix_col_kernel(const LaunchArgs args) {
                     x[i * G::R0 + r] = one.at(i * NB + r * G::n0);
                 });
             });
+            if constexpr (EARLY) table.store(twl, tid);
             __syncthreads();  // twiddles visible
             F::template fwd<0>(x, v, lds + c, tw0, t);
             store2(even);  // every row of the line is in registers since the transform's first barrier
@@ -604,6 +649,7 @@ mix_col_kernel(const LaunchArgs args) {
             cx<T> w[G::V];
             load2(v, even);
             load2(w, odd);
+            if constexpr (EARLY) table.store(twl, tid);
             __syncthreads();
             F::template inv<0, false>(v, x, lds + c, tw0, t);
             __syncthreads();
@@ -670,31 +716,57 @@ __device__ __forceinline__ cx<T> mix_unsplit(cx<T> a, cx<T> m, cx<T> e) {
     return cx<T>{sm.x - ed.y, sm.y + ed.x};
 }
 
+// Workspace row (z, y): at<r>(b) is its value k = b + r*nL.  In slabs, rows are kSlab values (fewer in
+// the last one) and k moves on to the next slab after each; where kSlab divides nL that takes one
+// address per butterfly.
+template <typename T, int N, bool SLABS>
+struct MixRowAt {
+    static constexpr int nL = MixLen<T, N>::nL;
+    static constexpr int whole = N / kSlab * kSlab, rest = N - whole;  // kx in slabs of full width
+    cx<T> *p, *last;
+    size_t size;
+    __device__ __forceinline__ MixRowAt(cx<T> *W, const DevPlan &pl, int z, int y) {
+        if constexpr (SLABS) {
+            const size_t zrow = w_row(z, y, pl.ny, 1, pl.zb);
+            size = static_cast<size_t>(2) * pl.ny * pl.nz;
+            p = W + zrow * kSlab;
+            last = W + whole * size + zrow * rest;
+        } else {
+            p = W + w_row(z, y, pl.ny, N, pl.zb);
+        }
+    }
+    template <int r>
+    __device__ __forceinline__ cx<T> &at(int b) const {
+        const int k = b + r * nL;
+        if constexpr (!SLABS) {
+            return p[k];
+        } else if constexpr (rest == 0 && nL % kSlab == 0) {
+            return *(p + b / kSlab * kSlab * size + b % kSlab + r * nL * size);
+        } else {
+            cx<T> *q = p + k / kSlab * kSlab * size + k % kSlab;
+            return rest > 0 && k >= whole ? last[k - whole] : *q;
+        }
+    }
+};
+
 // Row passes: rows r = z*ny + y of S / Phi, packed u[j] = s[2j] + i s[2j+1] (zero for 2j >= nx),
 // a transform of N = nx points and the split step with exp(-i pi k / n), as in the other row
-// kernels.  Consecutive lanes walk along a row.
-template <typename T, int N, int MODE>
-__global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const LaunchArgs args) {
+// kernels.  Consecutive lanes walk along a row.  SLABS: the workspace is in slabs of kx.
+// publish(): the tables' writes to LDS, after the loads of the rows.
+template <typename T, int N, int MODE, bool SLABS, typename Publish>
+__device__ __forceinline__ void mix_row_body(const MixJob &job, cx<T> *lds, int tid, Publish &&publish) {
     using G = MixLen<T, N>;
     using C = MixRow<T, N>;
     constexpr int NB = G::NB, ROWS = C::ROWS, S = C::S;
     using F = MixFFT<T, G, 1, C::PAD>;
-    extern __shared__ __align__(16) unsigned char smem[];
-    cx<T> *lds = reinterpret_cast<cx<T> *>(smem);
-    const int bid = tile_walk<true>().tile();
-    if (bid >= args.nwg) return;
-    const int tid = static_cast<int>(threadIdx.x), c = tid / NB, t = tid % NB;
-    const AxisPlan &ax = args.p[0].plan->ax[0];
-    cx<T> *twl = lds + ROWS * S, *post = twl + G::NTW;
-    copy_to_lds<T>(twl, ax.mtw, G::NTW);
-    copy_to_lds<T>(post, ax.post, N);
-    const MixJob job = mix_job(args, bid);
+    const int c = tid / NB, t = tid % NB;
+    const cx<T> *twl = lds + ROWS * S, *post = twl + G::NTW;
     const DevPlan &pl = *job.pa->plan;
     const int ny = pl.ny, nz = pl.nz;
     const int g = job.local * ROWS + c;
     const bool active = g < ny * nz;
     const int z = active ? g / ny : 0, y = active ? g - z * ny : 0;
-    cx<T> *wrow = static_cast<cx<T> *>(job.pa->W) + w_row(z, y, ny, N, pl.zb);
+    const MixRowAt<T, N, SLABS> w(static_cast<cx<T> *>(job.pa->W), pl, z, y);
     cx<T> *wnyq = static_cast<cx<T> *>(job.pa->Wn) + static_cast<size_t>(z) * 2 * ny + y;
     cx<T> *row = lds + c * S;
     const size_t f0 = static_cast<size_t>(active ? g : 0) * N;
@@ -710,8 +782,9 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
                 x[i * G::R0 + r] = mix_source<T, N, r * G::n0, G::n0>(s, b + r * G::n0);
             });
         });
+        publish();
         __syncthreads();  // tables visible
-        F::template fwd<0>(x, v, row, static_cast<const cx<T> *>(twl), t);
+        F::template fwd<0>(x, v, row, twl, t);
         // split: X[k] = (U[k] + U*[n-k])/2 - (i/2) exp(-i pi k/n) (U[k] - U*[n-k])
         F::template each<G::RL>(t, [&](auto ic, int b) {
             constexpr int i = decltype(ic)::value;
@@ -728,8 +801,8 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
                 sfor<0, G::RL>([&](auto rc) {
                     constexpr int r = decltype(rc)::value;
                     const int k = b + r * G::nL;
-                    const cx<T> u = v[i * G::RL + r], w = row[slot(k == 0 ? 0 : N - k)];
-                    wrow[k] = mix_split(u, w, post[k]);
+                    const cx<T> u = v[i * G::RL + r], m = row[slot(k == 0 ? 0 : N - k)];
+                    w.template at<r>(b) = mix_split(u, m, post[k]);
                     if (k == 0) *wnyq = cx<T>{u.x - u.y, T(0)};
                 });
             });
@@ -737,9 +810,10 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
         cx<T> xn = {T(0), T(0)};
         F::template each<G::RL>(t, [&](auto ic, int b) {
             constexpr int i = decltype(ic)::value;
-            sfor<0, G::RL>([&](auto rc) { constexpr int r = decltype(rc)::value; v[i * G::RL + r] = wrow[b + r * G::nL]; });
+            sfor<0, G::RL>([&](auto rc) { constexpr int r = decltype(rc)::value; v[i * G::RL + r] = w.template at<r>(b); });
         });
         if (t == 0) xn = *wnyq;
+        publish();
         F::template each<G::RL>(t, [&](auto ic, int b) {
             constexpr int i = decltype(ic)::value;
             cx<T> *p = row + F::in(b);
@@ -755,12 +829,13 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
             sfor<0, G::RL>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
                 const int k = b + r * G::nL;
-                const cx<T> a = v[i * G::RL + r], m = k == 0 ? xn : row[slot(N - k)];
-                v[i * G::RL + r] = mix_unsplit(a, m, post[k]);
+                cx<T> m = row[slot(k == 0 ? 0 : N - k)];
+                if (k == 0) m = xn;  // (a choice of values: one of addresses would put xn in memory)
+                v[i * G::RL + r] = mix_unsplit(v[i * G::RL + r], m, post[k]);
             });
         });
         __syncthreads();  // partners read
-        F::template inv<0, false>(v, x, row, static_cast<const cx<T> *>(twl), t);
+        F::template inv<0, false>(v, x, row, twl, t);
         if (active) {
             T *f = static_cast<T *>(job.pa->Phi) + f0;
             F::template each<G::R0>(t, [&](auto ic, int b) {
@@ -770,6 +845,40 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
                     mix_potential<T, N, r * G::n0, G::n0>(f, b + r * G::n0, x[i * G::R0 + r]);
                 });
             });
+        }
+    }
+}
+
+// MANY: args.rounds row tiles per workgroup, and plans with slabs (a kernel of its own: the loop and
+// the second layout cost registers, 10 to 16 % of the inverse passes of 144 points).
+template <typename T, int N, int MODE, bool MANY>
+__global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const LaunchArgs args) {
+    using C = MixRow<T, N>;
+    extern __shared__ __align__(16) unsigned char smem[];
+    cx<T> *lds = reinterpret_cast<cx<T> *>(smem);
+    const int rounds = MANY ? args.rounds : 1, first = tile_walk<true>().tile() * rounds;
+    if (first >= args.nwg) return;
+    const AxisPlan &ax = args.p[0].plan->ax[0];
+    cx<T> *twl = lds + C::ROWS * C::S, *post = twl + C::G::NTW;
+    int tid = static_cast<int>(threadIdx.x);
+    if constexpr (!MANY) {
+        MixTable<T, C::G::NTW, C::BLOCK> tw;
+        MixTable<T, N, C::BLOCK> split;
+        tw.load(ax.mtw, tid);
+        split.load(ax.post, tid);
+        mix_row_body<T, N, MODE, false>(mix_job(args, first), lds, tid, [&]() __attribute__((always_inline)) {
+            tw.store(twl, tid);
+            split.store(post, tid);
+        });
+    } else {
+        copy_to_lds<T>(twl, ax.mtw, C::G::NTW);
+        copy_to_lds<T>(post, ax.post, N);
+        for (int i = 0; i < rounds && first + i < args.nwg; ++i) {
+            asm volatile("" : "+v"(tid));  // addresses are derived again per tile
+            if (MODE == X_INV && i > 0) __syncthreads();  // the rows before are read (X_FWD: its first barrier)
+            const MixJob job = mix_job(args, first + i);
+            if (job.pa->plan->ks == kSlabShift) mix_row_body<T, N, MODE, true>(job, lds, tid, []() {});
+            else mix_row_body<T, N, MODE, false>(job, lds, tid, []() {});
         }
     }
 }
@@ -786,9 +895,10 @@ hipError_t launch_mix(int mode, const LaunchArgs &args, hipStream_t stream) {
     static int cus[kMaxDevices] = {0};
     constexpr bool PZ = mix_z_persist<T, N>();
     constexpr int GL = mix_spectrum(sizeof(T) == 4 ? 0 : 1, N);
-    void (*const fn[5])(LaunchArgs) = {mix_row_kernel<T, N, X_FWD>, mix_col_kernel<T, N, Y_FWD, GL, false>,
-                                       mix_col_kernel<T, N, Z_CONV, GL, PZ>, mix_col_kernel<T, N, Y_INV, GL, false>,
-                                       mix_row_kernel<T, N, X_INV>};
+    void (*const fn[7])(LaunchArgs) = {mix_row_kernel<T, N, X_FWD, false>,       mix_col_kernel<T, N, Y_FWD, GL, false>,
+                                       mix_col_kernel<T, N, Z_CONV, GL, PZ>,     mix_col_kernel<T, N, Y_INV, GL, false>,
+                                       mix_row_kernel<T, N, X_INV, false>,       mix_row_kernel<T, N, X_FWD, true>,
+                                       mix_row_kernel<T, N, X_INV, true>};
     if (mode < 0 || mode > 4) return hipErrorInvalidValue;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -811,9 +921,11 @@ hipError_t launch_mix(int mode, const LaunchArgs &args, hipStream_t stream) {
     const int block = row ? MixRow<T, N>::BLOCK : (mode == Z_CONV ? CZ::BLOCK : CY::BLOCK);
     const size_t lds = row ? MixRow<T, N>::LDS : (mode == Z_CONV ? CZ::LDS : CY::LDS);
     // whole rounds of the chunked tile order, or one persistent workgroup per CU
-    int grid = (args.nwg + 8 * kTileChunk - 1) / (8 * kTileChunk) * (8 * kTileChunk);
+    const int nwg = args.rounds > 0 ? (args.nwg + args.rounds - 1) / args.rounds : args.nwg;
+    int grid = (nwg + 8 * kTileChunk - 1) / (8 * kTileChunk) * (8 * kTileChunk);
     if (mode == Z_CONV && PZ && grid > cus[dev]) grid = cus[dev];
-    hipLaunchKernelGGL(fn[mode], dim3(grid), dim3(block), lds, stream, args);
+    const int many = args.rounds > 0 ? (mode == X_FWD ? 5 : 6) : mode;
+    hipLaunchKernelGGL(fn[row ? many : mode], dim3(grid), dim3(block), lds, stream, args);
     return hipGetLastError();
 }
 

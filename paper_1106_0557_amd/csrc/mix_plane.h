@@ -77,8 +77,10 @@ __global__ void __launch_bounds__((MixPlane<T, N>::BLOCK)) mix_plane_kernel(cons
     cx<T> *Wn = static_cast<cx<T> *>(ref.pa->Wn) + static_cast<size_t>(ref.z) * 2 * N;
     const AxisPlan &ax = args.p[0].plan->ax[0];  // the tables depend on n only
     cx<T> *twl = lds + N * S, *post = twl + 2 * G::NTW, *c0 = post + N;
-    copy_to_lds<T>(twl, ax.mtw, 2 * G::NTW);
-    copy_to_lds<T>(post, ax.post, N);
+    MixTable<T, 2 * G::NTW, C::BLOCK> table;
+    MixTable<T, N, C::BLOCK> split;
+    table.load(ax.mtw, tid);
+    split.load(ax.post, tid);
     const cx<T> *tw0 = twl, *tw1 = twl + G::NTW;
     auto slot = [](int P) { return C::PAD ? P + P / G::R0 : P; };
     cx<T> *row = lds + xc * S, *col = lds + slot(yc);
@@ -93,6 +95,8 @@ __global__ void __launch_bounds__((MixPlane<T, N>::BLOCK)) mix_plane_kernel(cons
                 x[i * G::R0 + r] = mix_source<T, N, r * G::n0, G::n0>(s, b + r * G::n0);
             });
         });
+        table.store(twl, tid);
+        split.store(post, tid);
         __syncthreads();  // tables visible
         Row::template fwd<0>(x, v, row, tw0, xt);
         // split: X[k] = (U[k] + U*[n-k])/2 - (i/2) exp(-i pi k/n) (U[k] - U*[n-k])
@@ -178,6 +182,8 @@ __global__ void __launch_bounds__((MixPlane<T, N>::BLOCK)) mix_plane_kernel(cons
         };
         load(v, std::integral_constant<int, 0>{});
         load(w, std::integral_constant<int, 1>{});
+        table.store(twl, tid);
+        split.store(post, tid);
         __syncthreads();  // tables visible
         Col::template inv<0, false>(v, x, col, tw0, yt);
         __syncthreads();

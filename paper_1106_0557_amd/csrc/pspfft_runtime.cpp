@@ -329,13 +329,28 @@ bool build_axis(int axis, int n, pspfft_precision prec, AxisPlan &ax, std::vecto
 // 7.75 -> 6.8 ms, 288 x 144 x 144 423 -> 290 us.  Lines of 128 stay with the radix
 // families (twelve FP32 128^3 z passes 0.203 ms there, 0.207 here; four FP64 ones
 // 0.147 and 0.156), except FP64 rows and y lines (a single 128^3 solve 108 -> 105 us).
-bool mix_axis(int axis, const int n[3], pspfft_precision prec, pspfft::MixInfo &info) {
+// Large meshes keep the workspace in slabs of kx (w_slab): `width` is then kSlab.
+bool mix_axis(int axis, const int n[3], pspfft_precision prec, int width, pspfft::MixInfo &info) {
     if (n[axis] == 128 && (axis == 2 || prec == PSPFFT_FP32)) return false;
     if (!pspfft::mix_info(prec == PSPFFT_FP32 ? 0 : 1, n[axis], info)) return false;
-    const size_t lim = (size_t(1) << 32) - 64, cs = cplx_size(prec), nx = n[0], ny = n[1];
+    const size_t lim = (size_t(1) << 32) - 64, cs = cplx_size(prec), nx = width, ny = n[1];
     if (axis == 2) return info.nb * 2 * ny * nx * cs < lim;
     if (axis == 1) return ((16 / nx + 2 + 16) * 2 * ny * nx + size_t(2) * info.nb * 16 * nx) * cs < lim;
     return true;
+}
+
+// The axes of a mesh that run on half-length lines.  Returns DevPlan::ks: slabs for meshes whose
+// workspace main part holds kSlabBytes or more, with half-length lines on all axes (PSPFFT_SLABS=1:
+// whatever their size), else one slab.
+int mix_axes(const int n[3], pspfft_precision prec, bool mixed[3], pspfft::MixInfo info[3]) {
+    const size_t main = static_cast<size_t>(2) * n[0] * n[1] * n[2] * cplx_size(prec);
+    const char *e = std::getenv("PSPFFT_SLABS");
+    const bool large = n[0] > pspfft::kSlab && (main >= pspfft::kSlabBytes || (e && std::atoi(e) == 1));
+    for (int slabs = large ? 1 : 0; slabs >= 0; --slabs) {
+        for (int a = 0; a < 3; ++a) mixed[a] = mix_axis(a, n, prec, slabs ? pspfft::kSlab : n[0], info[a]);
+        if (slabs && mixed[0] && mixed[1] && mixed[2]) return pspfft::kSlabShift;
+    }
+    return pspfft::kNoSlabs;
 }
 
 // x and y transforms of a plane by the plane kernels on half-length lines
@@ -345,8 +360,8 @@ bool mix_axis(int axis, const int n[3], pspfft_precision prec, pspfft::MixInfo &
 // 17.0, 36^3 36.5 -> 20.8; FP32 48^3 27.0 -> 20.8, 64^3 26.2 -> 22.9 (32 of them
 // 156 -> 154 us).
 bool mix_plane(const int n[3], pspfft_precision prec, pspfft::MixInfo &info) {
-    if (n[0] != n[1] || !pspfft::mix_plane_info(prec == PSPFFT_FP32 ? 0 : 1, n[0], info)) return false;
-    return n[0] <= 64 || !family_axis(0, n[0], prec);
+    if (n[0] != n[1] || (n[0] > 64 && family_axis(0, n[0], prec))) return false;
+    return pspfft::mix_plane_info(prec == PSPFFT_FP32 ? 0 : 1, n[0], info);
 }
 
 // Appends the stage twiddles of half-length lines (AxisPlan::mtw) of n points: 2n values, whatever the stages.
@@ -370,8 +385,10 @@ void mix_twiddles(int n, const pspfft::MixInfo &info, std::vector<std::complex<d
 
 // Spectrum layout (DevPlan::gz 2) and size: values of G and of Gn.
 bool mix_spectrum_blocked(const int n[3], pspfft_precision prec) {
-    pspfft::MixInfo info;
-    return mix_axis(2, n, prec, info) && pspfft::mix_spectrum(prec == PSPFFT_FP32 ? 0 : 1, n[2]) == 2;
+    pspfft::MixInfo info[3];
+    bool mixed[3];
+    mix_axes(n, prec, mixed, info);
+    return mixed[2] && pspfft::mix_spectrum(prec == PSPFFT_FP32 ? 0 : 1, n[2]) == 2;
 }
 size_t spectrum_main(const int n[3], pspfft_precision prec) {
     const size_t row = mix_spectrum_blocked(n, prec) ? round_up(n[0], pspfft::kGroup) : n[0];
@@ -555,6 +572,16 @@ bool number_tiles(LaunchArgs &args, int mode, int tile, const std::vector<int> &
     return true;
 }
 
+// Row tiles that a workgroup of the half-length x passes takes one after the other (0: one, by the
+// kernel for that).  Each workgroup begins with the tables, so longer ones read them less often: worth it
+// where a tile has few rows and the chip is left with several rounds of workgroups.  Measured, forward
+// pass in ms with 1, 4 and 8 tiles: FP32 1152^3 (2 rows a tile) 6.5, 4.9, 4.7, 960^3 (4) 3.10, 2.54,
+// 2.47, 512^3 (8) 0.342, 0.335, 0.344; FP64 512^3 (8) 0.92, 0.83; nine FP32 192^3 (16) 0.158, 0.165.
+int mix_rounds(int rows, int tiles, bool slabs) {
+    if (tiles < 16384 || rows > 8) return slabs ? 1 : 0;
+    return rows < 8 ? 8 : 4;
+}
+
 // Grouped launches of a pass by half-length lines: one per precision and length.
 pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_plan_t *plans,
                          const pspfft_workspace_t *ws, const void *const *S, void *const *Phi, hipStream_t stream) {
@@ -575,6 +602,9 @@ pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_pla
             LaunchArgs args;
             add_problems(args, idx, c0, c1, plans, ws, S, Phi);
             if (!number_tiles(args, mode, tile, idx, c0, plans)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
+            bool slabs = false;
+            for (size_t j = c0; j < c1; ++j) slabs |= plans[idx[j]]->host.ks != pspfft::kNoSlabs;
+            if (axis == 0) args.rounds = mix_rounds(info.rows, args.nwg, slabs);
             PSPFFT_LOG(3, "pass %d prec %d half-length lines of %d: %d problems in %d segments, %d workgroups of %d "
                           "lines", mode, prec, n, args.count, args.nseg, args.nwg, tile);
             if (pspfft::launch_mix_lines(mode, prec, n, args, stream) != hipSuccess) return PSPFFT_ERR_DEVICE;
@@ -929,9 +959,12 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
     pspfft::MixInfo mix[3];
     bool mixed[3], planes = false;
     size_t mix_at[3];
+    p->host.ks = mix_axes(p->n, prec, mixed, mix);
+    if (!(flags & PSPFFT_PLAN_FIVE_PASS) && mix_plane(p->n, prec, mix[0])) {
+        mixed[0] = planes = true;
+        p->host.ks = pspfft::kNoSlabs;
+    }
     for (int a = 0; a < 3; ++a) {
-        mixed[a] = mix_axis(a, p->n, prec, mix[a]);
-        if (a == 0 && !(flags & PSPFFT_PLAN_FIVE_PASS) && mix_plane(p->n, prec, mix[0])) mixed[0] = planes = true;
         if (!build_axis(a, p->n[a], prec, p->host.ax[a], tws[a]))
             return fail(PSPFFT_ERR_UNSUPPORTED_SIZE, vlevel, "%s: no stage plan for axis %d (n = %d)", who, a,
                         p->n[a]);
@@ -984,15 +1017,18 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
         p->host.ax[a].mtw = mixed[a] ? static_cast<char *>(p->tw[a]) + mix_at[a] * cs : nullptr;
         bytes += tb;
     }
-    // Workspace z tiles.  Only meshes whose z planes span 4 MB or more are
-    // tiled: there the z lines of the z pass miss the address translation
-    // caches, while for smaller planes the wider row stride costs more than it
-    // saves.  The tile is the largest power of two up to 16 (PSPFFT_ZTILE
-    // overrides the cap) dividing the z lines' threads per line.
+    // Workspace z tiles.  Only meshes whose z planes span 4 MB or more (half-length z lines: 1 MB) are
+    // tiled: there the z lines of the z pass miss the address translation caches, while for smaller
+    // planes the wider row stride costs more than it saves.  Half-length z lines take 2 planes a tile
+    // in slabs, 16 in meshes without them of more than 512 planes of 4 MB, else 4: larger tiles help z
+    // passes and cost y passes, one FP32 512^3 solve taking 3.65, 3.13, 3.12 and 3.29 ms with 1, 4, 8 and 16.
+    // The tile is the largest power of two up to that (PSPFFT_ZTILE overrides the cap) dividing the z
+    // lines' threads per line.
     {
         const size_t plane = static_cast<size_t>(2) * ny * nx * cs;
         int cap = plane >= (size_t(4) << 20) ? 16 : 1;
         if (mixed[2]) cap = plane < (size_t(1) << 20) ? 1 : (nz > 512 && plane >= (size_t(4) << 20) ? 16 : 4);
+        if (p->host.ks == pspfft::kSlabShift) cap = 2;  // y passes lose less than z passes gain
         if (const char *e = std::getenv("PSPFFT_ZTILE")) {
             const int v = std::atoi(e);
             if (v >= 1 && v <= 16 && (v & (v - 1)) == 0) cap = v;
@@ -1306,12 +1342,15 @@ size_t pspfft_plan_resident_bytes(int nx, int ny, int nz, pspfft_precision prec)
     if (!sizes_ok(nx, ny, nz, prec)) return 0;
     const int n[3] = {nx, ny, nz};
     size_t bytes = sizeof(DevPlan);
+    pspfft::MixInfo mix[3];
+    bool mixed[3];
+    mix_axes(n, prec, mixed, mix);
+    mixed[0] = mix_plane(n, prec, mix[0]) || mixed[0];
     for (int a = 0; a < 3; ++a) {  // twiddle tables, as pspfft_plan_create builds them
         AxisPlan ax;
         std::vector<std::complex<double>> tw;
         if (!build_axis(a, n[a], prec, ax, tw)) return 0;
-        pspfft::MixInfo info;
-        if (mix_axis(a, n, prec, info) || (a == 0 && mix_plane(n, prec, info))) mix_twiddles(n[a], info, tw);
+        if (mixed[a]) mix_twiddles(n[a], mix[a], tw);
         bytes += tw.size() * cplx_size(prec);
     }
     // spectrum octant: main part and the kx = nx column

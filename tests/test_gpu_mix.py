@@ -101,6 +101,33 @@ def test_tiled_workspaces(n, ztile, monkeypatch):
     check(n)
 
 
+# whole and partial last slabs, odd rows, partial tiles, and z tiles within slabs
+@pytest.mark.parametrize("n", [(96, 25, 27), (45, 100, 150), (80, 27, 160), (125, 30, 80), (243, 25, 192)])
+def test_slabs(n, monkeypatch):
+    """Workspaces in slabs of kx (PSPFFT_SLABS), which large meshes get by themselves."""
+    monkeypatch.setenv("PSPFFT_SLABS", "1")
+    check(n)
+
+
+# 32 problems of 563 row tiles (8 rows): workgroups take four tiles each, over problem boundaries
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_several_row_tiles_per_workgroup(dtype):
+    import paper_1106_0557_amd as ps
+
+    n = (270, 75, 60)
+    check(n, (dtype,))
+    plan = ps.Plan(*n, h=0.1, dtype=dtype)
+    ws = [plan.workspace() for _ in range(32)]
+    S = [sources.random_field(n, seed=i).to("cuda", dtype) for i in range(32)]
+    out = [torch.empty_like(s) for s in S]
+    ps.solve_batched(ws, S, out)
+    alone = [plan.solve(s) for s in S]
+    assert all(torch.equal(a, b) for a, b in zip(out, alone))
+    for w in ws:
+        w.close()
+    plan.close()
+
+
 @pytest.mark.parametrize("n", [(25, 18, 60), (16, 10, 135), (40, 12, 960)])
 def test_blocked_spectrum_exports_the_octant(n):
     from paper_1106_0557_amd import Plan
