@@ -60,8 +60,8 @@ struct MixPlane {
     static_assert(BLOCK <= 1024 && LDS <= 160 * 1024, "one workgroup fits");
 };
 
-template <typename T, int N, bool FWD>
-__global__ void __launch_bounds__((MixPlane<T, N>::BLOCK)) mix_plane_kernel(const LaunchArgs args) {
+template <typename T, int N, bool FWD, typename Args>
+__global__ void __launch_bounds__((MixPlane<T, N>::BLOCK)) mix_plane_kernel(const Args args) {
     using C = MixPlane<T, N>;
     using G = typename C::G;
     constexpr int NB = G::NB, S = C::S;
@@ -223,20 +223,31 @@ template <typename T, int N>
 hipError_t launch_mix_plane_n(bool fwd, const LaunchArgs &args, hipStream_t stream) {
     constexpr int kMaxDevices = 64;
     static bool ready[kMaxDevices] = {false};
-    void (*const fn[2])(LaunchArgs) = {mix_plane_kernel<T, N, false>, mix_plane_kernel<T, N, true>};
+    constexpr bool SOLO = N <= 64;  // up to there the host is slower than the card
+    void (*const fn[2])(LaunchArgs) = {mix_plane_kernel<T, N, false, LaunchArgs>, mix_plane_kernel<T, N, true, LaunchArgs>};
+    using Solo = std::conditional_t<SOLO, SoloArgs, LaunchArgs>;
+    void (*const solo[2])(Solo) = {mix_plane_kernel<T, N, false, Solo>, mix_plane_kernel<T, N, true, Solo>};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
     if (!ready[dev]) {
-        for (auto f : fn) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    160 * 1024);
+        for (const void *f : {reinterpret_cast<const void *>(fn[0]), reinterpret_cast<const void *>(fn[1]),
+                              reinterpret_cast<const void *>(solo[0]), reinterpret_cast<const void *>(solo[1])}) {
+            e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (e != hipSuccess) return e;
         }
         ready[dev] = true;
     }
-    hipLaunchKernelGGL(fn[fwd ? 1 : 0], dim3(args.nwg), dim3(MixPlane<T, N>::BLOCK), (MixPlane<T, N>::LDS), stream, args);
+    const dim3 grid(args.nwg), block(MixPlane<T, N>::BLOCK);
+    if constexpr (SOLO) {
+        if (args.count == 1) {
+            const SoloArgs one = {{args.p[0]}};
+            hipLaunchKernelGGL(solo[fwd ? 1 : 0], grid, block, (MixPlane<T, N>::LDS), stream, one);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL(fn[fwd ? 1 : 0], grid, block, (MixPlane<T, N>::LDS), stream, args);
     return hipGetLastError();
 }
 

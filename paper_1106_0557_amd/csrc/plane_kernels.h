@@ -56,12 +56,17 @@ struct PlaneRef {
     const ProbArg *pa;
     int z;
 };
-__device__ __forceinline__ PlaneRef plane_ref(const LaunchArgs &args, int pl) {
-    int sgi = 0;
-    while (sgi + 1 < args.nseg && pl >= args.seg[sgi + 1].wg_begin) ++sgi;
-    const Segment &sg = args.seg[sgi];
-    const int local = pl - sg.wg_begin;
-    return PlaneRef{&args.p[sg.first + local % sg.group], local / sg.group};
+template <typename Args>
+__device__ __forceinline__ PlaneRef plane_ref(const Args &args, int pl) {
+    if constexpr (Args::kProblems == 1) {
+        return PlaneRef{args.p, pl};
+    } else {
+        int sgi = 0;
+        while (sgi + 1 < args.nseg && pl >= args.seg[sgi + 1].wg_begin) ++sgi;
+        const Segment &sg = args.seg[sgi];
+        const int local = pl - sg.wg_begin;
+        return PlaneRef{&args.p[sg.first + local % sg.group], local / sg.group};
+    }
 }
 
 // Each workgroup takes planes blockIdx.x, blockIdx.x + gridDim.x, ...  The
