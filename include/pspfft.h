@@ -38,11 +38,14 @@
  * also reported as messages of level PSPFFT_CONSOLE_ERROR (see Messages).
  *
  * Supported sizes.  Each of nx, ny, nz may be any 2^a 3^b 5^c from 1 to 2048
- * (2n <= 4096 points per doubled line), in both precisions.  Sizes 2^a * o with
- * o in {1, 3, 5, 9} and n >= 8, 10, 12, 18 (x: twice that, the packed real
- * transform having length n), up to 2048 (FP32) or 1152 (FP64) for y and z and
- * 4096 or 2304 for x, run on compile-time radix-family kernels; the other sizes
- * on a generic line kernel (slower; a plan that uses it reports a warning).
+ * (2n <= 4096 points per doubled line), in both precisions.  The sizes from 25
+ * to 1152 outside the radix families, and of the others 80, 96 and 144 to 1152
+ * (128 in part), run on half-length line kernels with radices of their own.
+ * Sizes 2^a * o with o in {1, 3, 5, 9} and n >= 8, 10, 12, 18 (x: twice that, the
+ * packed real transform having length n), up to 2048 (FP32) or 1152 (FP64) for y
+ * and z and 4096 or 2304 for x, otherwise run on compile-time radix-family
+ * kernels; the remaining sizes (15 and below, or above 1152) on a generic line
+ * kernel (slower; a plan that uses it reports a warning).
  * Rows nx of 2560, 3072 and 4096 (FP32) or 2304 (FP64) are also accepted.
  * Other sizes return PSPFFT_ERR_UNSUPPORTED_SIZE.
  * S and Phi must be aligned to two reals (8 bytes FP32, 16 bytes FP64).
@@ -154,7 +157,8 @@ typedef enum {
  * the x and y transforms of each z plane when nx == ny = E*K (E in
  * {16, 20, 24, 36}, K a power of two dividing the power-of-two part of E, so at
  * most two stages) and the plane of x spectra fits in the 160 KB of LDS: FP32
- * up to n = 128, FP64 up to n = 80.  Both forms compute the same potential to
+ * up to n = 128, FP64 up to n = 80, and for the other sizes nx == ny from 25 to
+ * 120 (FP32) or 81 (FP64).  Both forms compute the same potential to
  * rounding; the fused one moves 2ny nz (nx+1) fewer complex values per solve.
  */
 pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], pspfft_precision prec,
@@ -165,7 +169,9 @@ int pspfft_plan_fused(pspfft_plan_t plan);
 
 /*
  * 1 if the plan keeps its spectrum kz-fastest, 0 otherwise (and for NULL).
- * That is the case where the z pass keeps each line within one wavefront,
+ * That is the case for half-length z lines (in blocks of 8 kx, even kz before odd
+ * ones, but for nz = 80, 96, 128, 144, 160 and 192 and in FP64 320, 576, 640, 1024
+ * and 1152), and where the z pass keeps each line within one wavefront,
  * which reads its spectrum values in contiguous runs: z lines of three stages
  * E, M, K with 16, 32 or 64 threads per line (2 nz = 16*16*2, 36*4*4, 24*8*4,
  * 16*16*4 or 24*8*8, that is nz = 256, 288, 384, 512 or 768), four-stage FP32
@@ -184,11 +190,17 @@ int pspfft_plan_spectrum_kz_fastest(pspfft_plan_t plan);
  * where B = pspfft_workspace_ztile(plan) (a power of two up to 16 dividing nz):
  * the value at (z, ky, kx < nx) is W[z / B][ky][z % B][kx] and the one at kx = nx
  * is Wn[z][ky].  Grouping B z planes keeps each z line of the z pass within
- * nz / B memory regions.  After the forward x and y passes it holds the
+ * nz / B memory regions.  Large meshes (W of 2.5 GiB or more, all three lengths
+ * on half-length lines) keep W in slabs of pspfft_workspace_slab(plan) kx, one
+ * after the other, each laid out like that with the slab's width (the last one's
+ * may be smaller) in place of nx.  After the forward x and y passes it holds the
  * transform along x and y of the zero-padded source for z < nz; after the z pass
  * the same after the convolution.  Returns 0 for NULL.
  */
 int pspfft_workspace_ztile(pspfft_plan_t plan);
+
+/* kx per slab of W: nx where W is one slab.  Returns 0 for NULL. */
+int pspfft_workspace_slab(pspfft_plan_t plan);
 
 /* Release a plan and everything it owns (Sec. 3.2, Destroy).  The memory is
  * freed with hipFree, which waits for the work already queued on the device,

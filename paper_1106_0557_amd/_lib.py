@@ -34,6 +34,7 @@ PASS_NAMES = ("x_fwd", "y_fwd", "z_conv", "y_inv", "x_inv")
 EXPORTS = (
     "pspfft_plan_create", "pspfft_plan_create_ex", "pspfft_plan_fused", "pspfft_plan_spectrum_kz_fastest",
     "pspfft_workspace_ztile",
+    "pspfft_workspace_slab",
     "pspfft_destroy", "pspfft_solve",
     "pspfft_workspace_create", "pspfft_workspace_wrap", "pspfft_workspace_destroy",
     "pspfft_solve_ws", "pspfft_solve_batched", "pspfft_pass_batched",
@@ -85,6 +86,7 @@ def load():
         "pspfft_plan_fused": ([vp], ip),
         "pspfft_plan_spectrum_kz_fastest": ([vp], ip),
         "pspfft_workspace_ztile": ([vp], ip),
+        "pspfft_workspace_slab": ([vp], ip),
         "pspfft_destroy": ([vp], ip),
         "pspfft_solve": ([vp, vp, vp, vp], ip),
         "pspfft_solve_noalloc": ([vp, vp, vp, vp], ip),

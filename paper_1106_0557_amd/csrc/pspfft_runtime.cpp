@@ -341,11 +341,11 @@ bool mix_axis(int axis, const int n[3], pspfft_precision prec, int width, pspfft
 
 // The axes of a mesh that run on half-length lines.  Returns DevPlan::ks: slabs for meshes whose
 // workspace main part holds kSlabBytes or more, with half-length lines on all axes (PSPFFT_SLABS=1:
-// whatever their size), else one slab.
+// whatever their size; 0: never), else one slab.
 int mix_axes(const int n[3], pspfft_precision prec, bool mixed[3], pspfft::MixInfo info[3]) {
     const size_t main = static_cast<size_t>(2) * n[0] * n[1] * n[2] * cplx_size(prec);
     const char *e = std::getenv("PSPFFT_SLABS");
-    const bool large = n[0] > pspfft::kSlab && (main >= pspfft::kSlabBytes || (e && std::atoi(e) == 1));
+    const bool large = n[0] > pspfft::kSlab && (e ? std::atoi(e) == 1 : main >= pspfft::kSlabBytes);
     for (int slabs = large ? 1 : 0; slabs >= 0; --slabs) {
         for (int a = 0; a < 3; ++a) mixed[a] = mix_axis(a, n, prec, slabs ? pspfft::kSlab : n[0], info[a]);
         if (slabs && mixed[0] && mixed[1] && mixed[2]) return pspfft::kSlabShift;
@@ -1393,6 +1393,10 @@ int pspfft_plan_fused(pspfft_plan_t plan) { return plan && plan->fused ? 1 : 0; 
 int pspfft_plan_spectrum_kz_fastest(pspfft_plan_t plan) { return plan && plan->host.gz ? 1 : 0; }
 
 int pspfft_workspace_ztile(pspfft_plan_t plan) { return plan ? plan->host.zb : 0; }
+
+int pspfft_workspace_slab(pspfft_plan_t plan) {
+    return !plan ? 0 : plan->host.ks == pspfft::kNoSlabs ? plan->n[0] : pspfft::kSlab;
+}
 
 pspfft_status pspfft_plan_info(pspfft_plan_t plan, int dims[3], double h[3], pspfft_precision *prec) {
     if (!plan) return PSPFFT_ERR_INVALID_ARGUMENT;
