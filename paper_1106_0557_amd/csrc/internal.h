@@ -122,6 +122,7 @@ struct LaunchArgs {
 // host (2.8 us with these, 4.2 us with LaunchArgs), which is what a sequence of small solves waits for.
 struct SoloArgs {
     static constexpr int kProblems = 1;
+    int nwg;
     ProbArg p[1];
 };
 

@@ -242,7 +242,7 @@ hipError_t launch_mix_plane_n(bool fwd, const LaunchArgs &args, hipStream_t stre
     const dim3 grid(args.nwg), block(MixPlane<T, N>::BLOCK);
     if constexpr (SOLO) {
         if (args.count == 1) {
-            const SoloArgs one = {{args.p[0]}};
+            const SoloArgs one = {args.nwg, {args.p[0]}};
             hipLaunchKernelGGL(solo[fwd ? 1 : 0], grid, block, (MixPlane<T, N>::LDS), stream, one);
             return hipGetLastError();
         }

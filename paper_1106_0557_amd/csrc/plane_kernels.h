@@ -77,8 +77,10 @@ __device__ __forceinline__ PlaneRef plane_ref(const Args &args, int pl) {
 // a whole plane of input would not fit in registers beside the one in use.
 // NT (inverse planes of a streaming launch): the W rows are loaded with
 // nontemporal accesses; they are read once.
-template <typename T, int E, int K, bool FWD, bool NT = false>
-__global__ void __launch_bounds__(E * K * K) plane_kernel(const LaunchArgs args) {
+// SoloArgs: one problem whose planes have a workgroup each.
+template <typename T, int E, int K, bool FWD, bool NT = false, typename Args = LaunchArgs>
+__global__ void __launch_bounds__(E * K * K) plane_kernel(const Args args) {
+    constexpr bool MORE = Args::kProblems > 1;  // a workgroup may take further planes
     constexpr int n = E * K;
     constexpr int NB = K;
     constexpr int H = E / 2;
@@ -208,7 +210,7 @@ __global__ void __launch_bounds__(E * K * K) plane_kernel(const LaunchArgs args)
                 // stores retire in order, so a load issued after them could not be
                 // waited for without waiting for them.
                 if constexpr (PF) {
-                    if (nxt < args.nwg) load_src(nxt);
+                    if (MORE && nxt < args.nwg) load_src(nxt);
                 }
                 // Column 0 carries C = A + i B, A and B the transforms of the real
                 // columns kx = 0 and kx = n: A[ky] = (C[ky] + conj C[-ky])/2 goes to
@@ -248,7 +250,7 @@ __global__ void __launch_bounds__(E * K * K) plane_kernel(const LaunchArgs args)
                 ColF::template run<K>(w, ax, lds, SP, twl, cp, yt);  // Y[2j+1]
                 emit(w, 1);
             }
-            if (nxt >= args.nwg) break;
+            if (!MORE || nxt >= args.nwg) break;
             pl = nxt;
             __syncthreads();  // LDS readers of this plane are done
         }
@@ -332,7 +334,7 @@ __global__ void __launch_bounds__(E * K * K) plane_kernel(const LaunchArgs args)
             }
             __syncthreads();
             const int nxt = pl + G;
-            if (nxt < args.nwg) load_even(nxt);
+            if (MORE && nxt < args.nwg) load_even(nxt);
             {  // x step
                 const cx<T> *row = lds + xc * SP;
                 const cx<T> p0 = row[0];  // X[y][0] + i X[y][n], both real
@@ -361,8 +363,8 @@ __global__ void __launch_bounds__(E * K * K) plane_kernel(const LaunchArgs args)
 #pragma unroll
                 for (int m = 0; m < H; ++m) at<T>(plane, off + m * NB * CSZ) = v[m];
             }
-            if (nxt < args.nwg) stage_nyquist();  // `sep` is free until the next y step
-            if (nxt >= args.nwg) return false;
+            if (MORE && nxt < args.nwg) stage_nyquist();  // `sep` is free until the next y step
+            if (!MORE || nxt >= args.nwg) return false;
             pl = nxt;
             __syncthreads();  // LDS readers of this plane are done
             return true;
@@ -395,6 +397,7 @@ hipError_t launch_plane_kernel(const LaunchArgs &args, size_t lds, hipStream_t s
     auto fn = plane_kernel<T, E, K, FWD>;
     // inverse planes of a streaming launch: nontemporal row loads
     auto fs = plane_kernel<T, E, K, FWD, !FWD>;
+    auto solo = plane_kernel<T, E, K, FWD, false, SoloArgs>;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -405,6 +408,9 @@ hipError_t launch_plane_kernel(const LaunchArgs &args, size_t lds, hipStream_t s
                                     160 * 1024);
             if (e != hipSuccess) return e;
         }
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(solo), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                160 * 1024);
+        if (e != hipSuccess) return e;
         int per_cu = 0, cus = 0;
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, E * K * K, lds);
         if (e != hipSuccess) return e;
@@ -422,6 +428,11 @@ hipError_t launch_plane_kernel(const LaunchArgs &args, size_t lds, hipStream_t s
                       (static_cast<long>(resident[dev]) * per);
     int grid = static_cast<int>(gens * resident[dev]);
     if (grid > args.nwg) grid = args.nwg;
+    if (args.count == 1 && grid == args.nwg && !args.nt) {
+        const SoloArgs one = {args.nwg, {args.p[0]}};
+        hipLaunchKernelGGL(solo, dim3(grid), dim3(E * K * K), lds, stream, one);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(args.nt ? fs : fn, dim3(grid), dim3(E * K * K), lds, stream, args);
     return hipGetLastError();
 }
