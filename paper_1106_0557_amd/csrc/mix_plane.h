@@ -17,6 +17,10 @@
 // One plane per workgroup.  What bounds a small mesh is latency: few planes, a
 // chain of dependent loads, LDS exchanges and arithmetic.  The threads per line
 // are therefore as many as keep each at 4 to 10 values where the plane is small.
+// Large batches of the longer ones are bounded by one plane per CU, whose stores
+// wait for its transforms.  Measured: eight FP32 120^3, whole solves, 383 us in
+// five passes and 326 us here (forward planes 3.0 TB/s, inverse 3.2); FP64 32^3,
+// sequential solves, 22.2 us with the family planes and 15.3 us here.
 #pragma once
 
 #include "mix_lines.h"

@@ -325,7 +325,7 @@ bool build_axis(int axis, int n, pspfft_precision prec, AxisPlan &ax, std::vecto
 // first-stage position block of NB planes; y: the planes that a tile's lines
 // span, in tiles of up to 16).  Measured against the kernels that took the
 // lengths before, one solve: FP32 480^3 12.0 -> 2.7 ms, 512^3 3.46 -> 3.2, 768^3
-// 16.9 -> 14.4, 1024^3 46.6 -> 35.2, 1152^3 71.5 -> 57; 192^3 173 -> 147 us; FP64 512^3
+// 16.9 -> 14.4, 1024^3 46.6 -> 35.2, 1152^3 71.5 -> 57 (49 in slabs); 192^3 173 -> 147 us; FP64 512^3
 // 7.75 -> 6.8 ms, 288 x 144 x 144 423 -> 290 us.  Lines of 128 stay with the radix
 // families (twelve FP32 128^3 z passes 0.203 ms there, 0.207 here; four FP64 ones
 // 0.147 and 0.156), except FP64 rows and y lines (a single 128^3 solve 108 -> 105 us).
@@ -356,8 +356,8 @@ int mix_axes(const int n[3], pspfft_precision prec, bool mixed[3], pspfft::MixIn
 // x and y transforms of a plane by the plane kernels on half-length lines
 // (mix_plane.h): the lengths outside the radix families, and up to 64 the others
 // too, where the threads of a plane are few and each solve waits for its chain
-// of stages.  Measured, us per sequential solve: FP64 24^3 26.0 -> 17.4, 32^3 22.2 ->
-// 17.0, 36^3 36.5 -> 20.8; FP32 48^3 27.0 -> 20.8, 64^3 26.2 -> 22.9 (32 of them
+// of stages.  Measured, us per sequential solve: FP64 24^3 26.0 -> 15.6, 32^3 22.2 ->
+// 15.3, 36^3 36.5 -> 19.4; FP32 48^3 27.0 -> 19.4, 64^3 26.2 -> 22.2 (32 of them
 // 156 -> 154 us).
 bool mix_plane(const int n[3], pspfft_precision prec, pspfft::MixInfo &info) {
     if (n[0] != n[1] || (n[0] > 64 && family_axis(0, n[0], prec))) return false;

@@ -105,7 +105,13 @@ def test_tiled_workspaces(n, ztile, monkeypatch):
 @pytest.mark.parametrize("n", [(96, 25, 27), (45, 100, 150), (80, 27, 160), (125, 30, 80), (243, 25, 192)])
 def test_slabs(n, monkeypatch):
     """Workspaces in slabs of kx (PSPFFT_SLABS), which large meshes get by themselves."""
-    monkeypatch.setenv("PSPFFT_SLABS", "1")
+    from paper_1106_0557_amd import Plan, _lib
+
+    for v, want in (("0", n[0]), ("1", 32)):
+        monkeypatch.setenv("PSPFFT_SLABS", v)
+        plan = Plan(*n, h=0.1, dtype=torch.float32)
+        assert _lib.load().pspfft_workspace_slab(plan._handle) == want
+        plan.close()
     check(n)
 
 
