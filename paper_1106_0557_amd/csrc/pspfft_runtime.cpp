@@ -1053,7 +1053,8 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
         const AxisPlan &ax = p->host.ax[0];
         const int K = ax.nst == 1 ? 1 : ax.R[1];
         p->fused = !(flags & PSPFFT_PLAN_FIVE_PASS) && nx == ny && ax.nst <= 2 && ax.E * K == nx &&
-                   ax.ntw == nx - 1 && pspfft::plane_fits(p->host.prec, ax.E, K) && p->host.zb == 1;
+                   ax.ntw == nx - 1 && pspfft::plane_fits(p->host.prec, ax.E, K) && p->host.zb == 1 &&
+                   p->host.ks == pspfft::kNoSlabs;  // the plane kernels take W in one slab, untiled
         if (p->fused) {
             p->pE = ax.E;
             p->pK = K;
