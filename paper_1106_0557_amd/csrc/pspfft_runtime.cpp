@@ -960,8 +960,11 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
     bool mixed[3], planes = false;
     size_t mix_at[3];
     p->host.ks = mix_axes(p->n, prec, mixed, mix);
-    if (!(flags & PSPFFT_PLAN_FIVE_PASS) && mix_plane(p->n, prec, mix[0])) {
+    pspfft::MixInfo plane;
+    const bool plane_table = mix_plane(p->n, prec, plane);
+    if (plane_table && !(flags & PSPFFT_PLAN_FIVE_PASS)) {
         mixed[0] = planes = true;
+        mix[0] = plane;
         p->host.ks = pspfft::kNoSlabs;
     }
     for (int a = 0; a < 3; ++a) {
@@ -995,7 +998,9 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
     if (hipGetDevice(&p->device) != hipSuccess) return fail(PSPFFT_ERR_DEVICE, vlevel, "%s: hipGetDevice", who);
     for (int a = 0; a < 3; ++a) {
         mix_at[a] = tws[a].size();
+        // (five-pass plans keep the table of the planes too: pspfft_plan_resident_bytes knows a plan by its size alone)
         if (mixed[a]) mix_twiddles(p->n[a], mix[a], tws[a]);
+        else if (a == 0 && plane_table) mix_twiddles(p->n[a], plane, tws[a]);
         const std::vector<std::complex<double>> &tw = tws[a];
         const size_t tb = tw.size() * cs;
         pspfft_status st = alloc(&p->tw[a], tb);

@@ -48,3 +48,16 @@ def test_square_meshes_in_slabs(n, ztile, monkeypatch):
         r = norms.report(got, ref)
         assert r["rel_l2"] <= (FP64_TOL if dt == torch.float64 else FP32_TOL), (n, dt, r)
         assert dt == torch.float32 or r["rel_max"] <= FP64_TOL, (n, dt, r)
+
+
+# lengths with plane kernels: family ones, others, and one that has row kernels of its own too
+@pytest.mark.parametrize("n", [16, 24, 32, 60, 64, 81, 120])
+@pytest.mark.parametrize("five_pass", [False, True])
+def test_resident_bytes_of_both_forms(n, five_pass):
+    """pspfft_plan_resident_bytes counts a plan whichever form its passes have."""
+    import paper_1106_0557_amd as ps
+
+    for dt in (torch.float32, torch.float64):
+        plan = ps.Plan(n, n, 12, h=0.1, dtype=dt, five_pass=five_pass)
+        assert plan.resident_bytes == ps.plan_resident_bytes(n, n, 12, dt)
+        plan.close()
