@@ -196,11 +196,18 @@ struct MixFFT {
         each<G::R0>(t, [&](auto ic, int b) {
             constexpr int i = decltype(ic)::value;
             cx<T> u[G::R0];
-            sfor<0, G::R0>([&](auto rc) {
-                constexpr int r = decltype(rc)::value;
-                u[r] = rot<2 * G::R0, -1, SH * r>(x[i * G::R0 + r]);
-            });
-            dft<G::R0, -1>(u);
+            sfor<0, G::R0>([&](auto rc) { constexpr int r = decltype(rc)::value; u[r] = x[i * G::R0 + r]; });
+            if constexpr (SH) {
+                // (values of their own: the sums that this has in common with the s = 0 transform would
+                // otherwise be kept beside x from there on, 6 to 10 registers more and spills in z passes)
+                sfor<0, G::R0>([&](auto rc) {
+                    cx<T> &q = u[decltype(rc)::value];
+                    asm volatile("" : "+v"(q.x), "+v"(q.y));
+                });
+                dft_half<G::R0>(u);
+            } else {
+                dft<G::R0, -1>(u);
+            }
             cx<T> *p = col + out0(b);
             sfor<0, G::R0>([&](auto rc) { constexpr int r = decltype(rc)::value; p[r * LW] = u[r]; });
         });
@@ -288,13 +295,17 @@ struct MixFFT {
             cx<T> u[G::R0];
             const cx<T> *p = col + out0(b);
             sfor<0, G::R0>([&](auto rc) { constexpr int r = decltype(rc)::value; u[r] = p[r * LW]; });
-            dft<G::R0, 1>(u);
-            sfor<0, G::R0>([&](auto rc) {
+            auto put = [&](auto rc, cx<T> w) __attribute__((always_inline)) {
                 constexpr int r = decltype(rc)::value;
-                const cx<T> w = rot<2 * G::R0, 1, SH * r>(u[r]);
                 if constexpr (ADD) o[i * G::R0 + r] = o[i * G::R0 + r] + w;
                 else o[i * G::R0 + r] = w;
-            });
+            };
+            if constexpr (SH) {
+                dft_half_adj<G::R0>(u, put);
+            } else {
+                dft<G::R0, 1>(u);
+                sfor<0, G::R0>([&](auto rc) { put(rc, u[decltype(rc)::value]); });
+            }
         });
     }
 };
