@@ -88,7 +88,8 @@ struct ProbArg {
 
 // A run of `group` consecutive problems p[first .. first+group) with the same
 // plan.  Its workgroups are numbered tile-major (tile, member), so the members
-// that read the same spectrum slice are neighbours in the launch.
+// that read the same spectrum slice are neighbours in the launch; those of the
+// half-length x and y passes problem by problem (mix_job).
 struct Segment {
     int wg_begin;     // first workgroup of the segment
     int first;        // index of its first problem in LaunchArgs::p

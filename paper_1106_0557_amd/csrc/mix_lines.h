@@ -343,20 +343,32 @@ struct MixTable {
     }
 };
 
-// Problem and tile of a workgroup (segments are numbered tile-major, so that
-// problems sharing a plan read one spectrum slice together).
+// Problem and tile of a workgroup.  A segment's problems share a plan: z passes number its tiles
+// tile-major, so that the problems read one spectrum slice together; x and y passes, which have nothing
+// to share, problem by problem, so that a chunk of the tile order (tile_walk) is adjacent tiles of one problem
+// whatever their count.  Measured, tile-major and problem by problem, whole solves in ms: eight FP64 128^3 0.773 and
+// 0.742, sixteen 1.475 and 1.396, eight 192^3 2.67 and 2.45; FP32 eight 288^3 4.84 and 4.63 (y passes -10 to -15 %),
+// sixteen 192^3 2.48 and 2.41.
 struct MixJob {
     const ProbArg *pa;
     int local;
     bool nyq;
 };
+template <bool TILE_MAJOR>
 __device__ __forceinline__ MixJob mix_job(const LaunchArgs &args, int bid) {
     int sgi = 0;
     while (sgi + 1 < args.nseg && bid >= args.seg[sgi + 1].wg_begin) ++sgi;
     const Segment &sg = args.seg[sgi];
-    int local = bid - sg.wg_begin;
-    const int member = uniform(local % sg.group);
-    local = uniform(local / sg.group);
+    int local = bid - sg.wg_begin, member = 0;
+    if constexpr (TILE_MAJOR) {
+        member = uniform(local % sg.group);
+        local = uniform(local / sg.group);
+    } else if (sg.group > 1) {
+        const int end = sgi + 1 < args.nseg ? args.seg[sgi + 1].wg_begin : args.nwg;
+        const int tiles = uniform((end - sg.wg_begin) / sg.group);  // of each problem
+        member = uniform(local / tiles);
+        local = uniform(local % tiles);
+    }
     const bool nyq = local >= sg.wg_main;
     return MixJob{&args.p[sg.first + member], nyq ? local - sg.wg_main : local, nyq};
 }
@@ -413,7 +425,7 @@ __device__ __forceinline__ MixZ<T> mix_z_line(const LaunchArgs &args, int bid, i
     using cplan = const __attribute__((address_space(4))) DevPlan;
     constexpr size_t CSZ = sizeof(cx<T>);
     constexpr int NB = MixLen<T, N>::NB;
-    const MixJob job = mix_job(args, bid);
+    const MixJob job = mix_job<true>(args, bid);
     const auto &pl = *(cplan *)job.pa->plan;
     const int nx = pl.nx, ny = pl.ny;
     const int g0 = job.local * TILE, g = g0 + c;
@@ -593,7 +605,7 @@ mix_col_kernel(const LaunchArgs args) {
         // doubled side of the transform)
         using cplan = const __attribute__((address_space(4))) DevPlan;
         constexpr size_t CSZ = sizeof(cx<T>);
-        const MixJob job = mix_job(args, bid);
+        const MixJob job = mix_job<false>(args, bid);
         const auto &pl = *(cplan *)job.pa->plan;
         const int nx = pl.nx, ny = pl.ny, nz = pl.nz, zb = pl.zb;
         const int g0 = job.local * TILE, g = g0 + c;
@@ -877,7 +889,7 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
         MixTable<T, N, C::BLOCK> split;
         tw.load(ax.mtw, tid);
         split.load(ax.post, tid);
-        mix_row_body<T, N, MODE, false>(mix_job(args, first), lds, tid, [&]() __attribute__((always_inline)) {
+        mix_row_body<T, N, MODE, false>(mix_job<false>(args, first), lds, tid, [&]() __attribute__((always_inline)) {
             tw.store(twl, tid);
             split.store(post, tid);
         });
@@ -887,7 +899,7 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
         for (int i = 0; i < rounds && first + i < args.nwg; ++i) {
             asm volatile("" : "+v"(tid));  // addresses are derived again per tile
             if (MODE == X_INV && i > 0) __syncthreads();  // the rows before are read (X_FWD: its first barrier)
-            const MixJob job = mix_job(args, first + i);
+            const MixJob job = mix_job<false>(args, first + i);
             if (job.pa->plan->ks == kSlabShift) mix_row_body<T, N, MODE, true>(job, lds, tid, []() {});
             else mix_row_body<T, N, MODE, false>(job, lds, tid, []() {});
         }

@@ -61,3 +61,23 @@ def test_resident_bytes_of_both_forms(n, five_pass):
         plan = ps.Plan(n, n, 12, h=0.1, dtype=dt, five_pass=five_pass)
         assert plan.resident_bytes == ps.plan_resident_bytes(n, n, 12, dt)
         plan.close()
+
+
+# launches over several plans that share a length: segments of several problems, partial tiles, Nyquist lines
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_passes_over_problems_of_several_plans(dtype):
+    import paper_1106_0557_amd as ps
+
+    meshes = [(45, 100, 27)] * 3 + [(75, 100, 50)] * 2 + [(45, 30, 50)] + [(75, 30, 27)] * 9
+    plans = {n: ps.Plan(*n, h=0.1, dtype=dtype) for n in set(meshes)}
+    ws = [plans[n].workspace() for n in meshes]
+    S = [sources.random_field(n, seed=i).to("cuda", dtype) for i, n in enumerate(meshes)]
+    out = [torch.full_like(s, float("nan")) for s in S]
+    for p in range(5):
+        ps.pass_batched(p, ws, S=S, Phi=out)
+    alone = [plans[n].solve(s) for n, s in zip(meshes, S)]
+    assert all(torch.equal(a, b) for a, b in zip(out, alone))
+    for w in ws:
+        w.close()
+    for p in plans.values():
+        p.close()
