@@ -106,7 +106,7 @@ struct LaunchArgs {
     int count;        // problems in this launch
     int nseg;         // segments
     int nwg;          // workgroups doing work (the grid may be padded to a multiple of 8)
-    int xcd_remap;    // renumber workgroups so each XCD gets a contiguous range
+    int xcd_remap;    // renumber workgroups so each XCD gets a contiguous range (half-length lines: 1 or 0)
     int wave_z;       // z pass: spectra kz-fastest, lines kept within one wavefront
     int gtile;        // generic line kernel: lines per workgroup (a power of two)
     int rounds;       // half-length x rows: tiles that a workgroup takes one after the other (0: one)

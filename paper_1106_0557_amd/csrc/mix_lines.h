@@ -373,6 +373,13 @@ __device__ __forceinline__ MixJob mix_job(const LaunchArgs &args, int bid) {
     return MixJob{&args.p[sg.first + member], nyq ? local - sg.wg_main : local, nyq};
 }
 
+// First tile (x rows: run of tiles) of an x or y workgroup: one contiguous eighth of the launch for each
+// XCD, or the chunked order.
+__device__ __forceinline__ int mix_tile(const LaunchArgs &args) {
+    const int b = static_cast<int>(blockIdx.x);
+    return args.xcd_remap ? (b & 7) * (static_cast<int>(gridDim.x) >> 3) + (b >> 3) : tile_walk<true>().tile();
+}
+
 // A lane's line: position p at base + p*step + lane bytes, base and step the same for the
 // whole workgroup; the lane's own share (its line and its thread's first position t) in 32 bits.
 template <typename T>
@@ -520,7 +527,7 @@ mix_col_kernel(const LaunchArgs args) {
     extern __shared__ __align__(16) unsigned char smem[];
     cx<T> *lds = reinterpret_cast<cx<T> *>(smem);
     TileWalk walk = tile_walk<true>();
-    int bid = walk.tile();
+    int bid = MODE == Z_CONV ? walk.tile() : mix_tile(args);
     if (bid >= args.nwg) return;
     const int tid = static_cast<int>(threadIdx.x);
     int c = tid % TILE, t = tid / TILE;  // adjacent lanes on adjacent lines
@@ -879,7 +886,7 @@ __global__ void __launch_bounds__((MixRow<T, N>::BLOCK)) mix_row_kernel(const La
     using C = MixRow<T, N>;
     extern __shared__ __align__(16) unsigned char smem[];
     cx<T> *lds = reinterpret_cast<cx<T> *>(smem);
-    const int rounds = MANY ? args.rounds : 1, first = tile_walk<true>().tile() * rounds;
+    const int rounds = MANY ? args.rounds : 1, first = mix_tile(args) * rounds;
     if (first >= args.nwg) return;
     const AxisPlan &ax = args.p[0].plan->ax[0];
     cx<T> *twl = lds + C::ROWS * C::S, *post = twl + C::G::NTW;
@@ -943,9 +950,10 @@ hipError_t launch_mix(int mode, const LaunchArgs &args, hipStream_t stream) {
     using CY = MixTile<T, N, false>;
     const int block = row ? MixRow<T, N>::BLOCK : (mode == Z_CONV ? CZ::BLOCK : CY::BLOCK);
     const size_t lds = row ? MixRow<T, N>::LDS : (mode == Z_CONV ? CZ::LDS : CY::LDS);
-    // whole rounds of the chunked tile order, or one persistent workgroup per CU
+    // whole rounds of the tile order, or one persistent workgroup per CU
     const int nwg = args.rounds > 0 ? (args.nwg + args.rounds - 1) / args.rounds : args.nwg;
-    int grid = (nwg + 8 * kTileChunk - 1) / (8 * kTileChunk) * (8 * kTileChunk);
+    const int whole = args.xcd_remap ? 8 : 8 * kTileChunk;
+    int grid = (nwg + whole - 1) / whole * whole;
     if (mode == Z_CONV && PZ && grid > cus[dev]) grid = cus[dev];
     const int many = args.rounds > 0 ? (mode == X_FWD ? 5 : 6) : mode;
     hipLaunchKernelGGL(fn[row ? many : mode], dim3(grid), dim3(block), lds, stream, args);

@@ -605,6 +605,12 @@ pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_pla
             bool slabs = false;
             for (size_t j = c0; j < c1; ++j) slabs |= plans[idx[j]]->host.ks != pspfft::kNoSlabs;
             if (axis == 0) args.rounds = mix_rounds(info.rows, args.nwg, slabs);
+            // x and y passes whose data stays in the Infinity Cache: each XCD takes one contiguous eighth of the
+            // planes, and finds in its L2 what it wrote in the pass before; larger launches gain more from the
+            // chunked order (TileWalk).  Measured, us a solve in chunks and in eighths: FP32 256 x 96 x 32 44.3
+            // and 39.7, 256 x 128 x 64 66.4 and 59.2, 240^3 283 and 277, 288^3 (382 MB) 547 and 553; FP64
+            // 100^3 64.9 and 60.0, 192^3 293 and 288, 256^3 (537 MB) 687 and 697.
+            args.xcd_remap = axis != 2 && !streaming_launch(plans, idx, c0, c1) ? 1 : 0;
             PSPFFT_LOG(3, "pass %d prec %d half-length lines of %d: %d problems in %d segments, %d workgroups of %d "
                           "lines", mode, prec, n, args.count, args.nseg, args.nwg, tile);
             if (pspfft::launch_mix_lines(mode, prec, n, args, stream) != hipSuccess) return PSPFFT_ERR_DEVICE;

@@ -81,3 +81,23 @@ def test_passes_over_problems_of_several_plans(dtype):
         w.close()
     for p in plans.values():
         p.close()
+
+
+# launches below and above the Infinity Cache's size number their tiles differently: one problem (65 MB) and seven
+@pytest.mark.parametrize("n", [(135, 150, 100), (150, 100, 135)])
+def test_tile_orders_of_small_and_large_launches(n):
+    import paper_1106_0557_amd as ps
+
+    h = (0.021, 0.017, 0.013)
+    plan = ps.Plan(*n, h=h, dtype=torch.float64)
+    assert plan.workspace_bytes < (256 << 20) < 7 * plan.workspace_bytes
+    ws = [plan.workspace() for _ in range(7)]
+    S = [sources.random_field(n, seed=i).to("cuda") for i in range(7)]
+    out = [torch.full_like(s, float("nan")) for s in S]
+    ps.solve_batched(ws, S, out)
+    assert all(torch.equal(o, plan.solve(s)) for o, s in zip(out, S))
+    r = norms.report(out[6].cpu().numpy(), oracle.solve_fft(S[6].cpu().numpy(), h))
+    assert r["rel_l2"] <= FP64_TOL and r["rel_max"] <= FP64_TOL, (n, r)
+    for w in ws:
+        w.close()
+    plan.close()
