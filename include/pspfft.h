@@ -143,7 +143,10 @@ typedef enum {
     PSPFFT_PLAN_DEFAULT = 0,
     /* Always run the five separate passes, even where the x and y transforms
      * of a plane could share one kernel. */
-    PSPFFT_PLAN_FIVE_PASS = 1
+    PSPFFT_PLAN_FIVE_PASS = 1,
+    /* pspfft_pass_batched keeps W of a large mesh in slabs, as whole solves do
+     * (pspfft_workspace_slab): faster, for callers that do not read W. */
+    PSPFFT_PLAN_SLABS = 8
 } pspfft_plan_flags;
 /* Option bits 4..6: the plan's own message level (the paper's VerbosityOption
  * argument of Create), PSPFFT_PLAN_VERBOSITY(PSPFFT_CONSOLE_INFO_1) and so on. */
@@ -190,16 +193,23 @@ int pspfft_plan_spectrum_kz_fastest(pspfft_plan_t plan);
  * where B = pspfft_workspace_ztile(plan) (a power of two up to 16 dividing nz):
  * the value at (z, ky, kx < nx) is W[z / B][ky][z % B][kx] and the one at kx = nx
  * is Wn[z][ky].  Grouping B z planes keeps each z line of the z pass within
- * nz / B memory regions.  Large meshes (W of 2.5 GiB or more, all three lengths
- * on half-length lines) keep W in slabs of pspfft_workspace_slab(plan) kx, one
- * after the other, each laid out like that with the slab's width (the last one's
- * may be smaller) in place of nx.  After the forward x and y passes it holds the
+ * nz / B memory regions.  After the forward x and y passes it holds the
  * transform along x and y of the zero-padded source for z < nz; after the z pass
- * the same after the convolution.  Returns 0 for NULL.
+ * the same after the convolution.  This is W between passes issued one by one
+ * (pspfft_pass_batched); the contents after a whole solve are unspecified.
+ * Returns 0 for NULL.
  */
 int pspfft_workspace_ztile(pspfft_plan_t plan);
 
-/* kx per slab of W: nx where W is one slab.  Returns 0 for NULL. */
+/*
+ * kx per slab of W between passes issued one by one: nx, W being one slab,
+ * unless the plan was created with PSPFFT_PLAN_SLABS and is large (W of 2.5 GiB or
+ * more, all three lengths on half-length lines; the few FP64 meshes of more than
+ * 1152 x 1078 in x and y with 972 or 1080 planes: always).  W is then in slabs
+ * of this many kx, one after the other, each laid out as above with the slab's
+ * width (the last one's may be smaller) in place of nx.  Whole solves keep large
+ * workspaces in slabs whatever the option.  Returns 0 for NULL.
+ */
 int pspfft_workspace_slab(pspfft_plan_t plan);
 
 /* Release a plan and everything it owns (Sec. 3.2, Destroy).  The memory is

@@ -52,7 +52,7 @@ def plan_resident_bytes(nx: int, ny: int, nz: int, dtype=torch.float32) -> int:
     return int(_lib.load().pspfft_plan_resident_bytes(nx, ny, nz, _prec(dtype)))
 
 
-PLAN_FIVE_PASS = 1  # pspfft_plan_flags
+PLAN_FIVE_PASS, PLAN_SLABS = 1, 8  # pspfft_plan_flags
 
 
 def set_verbosity(level: int) -> None:
@@ -86,12 +86,14 @@ class Plan:
 
     ``five_pass=True`` keeps the five separate passes where the x and y
     transforms of a plane could otherwise share one kernel (``fused``).
+    ``slabs=True`` lets ``pass_batched`` keep a large workspace in slabs of ``slab``
+    kx, as whole solves do (faster; for callers that do not read the workspace).
     ``verbosity`` (one of the CONSOLE_* levels) is the plan's own message level,
     the paper's VerbosityOption of Create; by default the process-wide level.
     """
 
     def __init__(self, nx: int, ny: int, nz: int, h, dtype=torch.float32, five_pass: bool = False,
-                 verbosity: int | None = None):
+                 verbosity: int | None = None, slabs: bool = False):
         lib = _lib.load()
         if isinstance(h, (int, float)):
             h = (float(h),) * 3
@@ -101,7 +103,7 @@ class Plan:
         self.dtype = dtype
         handle = ctypes.c_void_p()
         h3 = (ctypes.c_double * 3)(*self.h)
-        flags = PLAN_FIVE_PASS if five_pass else 0
+        flags = (PLAN_FIVE_PASS if five_pass else 0) | (PLAN_SLABS if slabs else 0)
         if verbosity is not None:
             flags |= (int(verbosity) + 1) << _lib.PLAN_VERBOSITY_SHIFT
         _lib.check(lib.pspfft_plan_create_ex(int(nx), int(ny), int(nz), h3, _prec(dtype), flags,
@@ -112,6 +114,7 @@ class Plan:
         self.fused = bool(lib.pspfft_plan_fused(self._handle))
         self.spectrum_kz_fastest = bool(lib.pspfft_plan_spectrum_kz_fastest(self._handle))
         self.ztile = int(lib.pspfft_workspace_ztile(self._handle))  # z planes per workspace tile
+        self.slab = int(lib.pspfft_workspace_slab(self._handle))  # kx per workspace slab (nx: one slab)
         # passes that launch work for this plan (a fused plan skips the y passes)
         self.active_passes = tuple(p for p in range(5) if lib.pspfft_pass_bytes(self._handle, p) > 0)
 

@@ -34,8 +34,9 @@ struct pspfft_plan_s {
     int n[3];
     double h[3];
     pspfft_precision prec;
-    DevPlan host;            // copy of the device plan (device pointers inside)
-    DevPlan *dev = nullptr;  // device copy read by the kernels
+    DevPlan host;            // copy of the device plan (device pointers inside): pass by pass
+    DevPlan whole;           // the same for whole solves, whose workspace layout is their own (mix_choice)
+    DevPlan *dev = nullptr;  // device copies read by the kernels: host, then whole
     void *tw[3] = {nullptr, nullptr, nullptr};
     void *G = nullptr, *Gn = nullptr;
     pspfft_workspace_t ws = nullptr;  // default workspace, allocated by the first pspfft_solve
@@ -339,18 +340,29 @@ bool mix_axis(int axis, const int n[3], pspfft_precision prec, int width, pspfft
     return true;
 }
 
-// The axes of a mesh that run on half-length lines.  Returns DevPlan::ks: slabs for meshes whose
-// workspace main part holds kSlabBytes or more, with half-length lines on all axes (PSPFFT_SLABS=1:
-// whatever their size; 0: never), else one slab.
-int mix_axes(const int n[3], pspfft_precision prec, bool mixed[3], pspfft::MixInfo info[3]) {
+// The axes of a mesh that run on half-length lines, and where the workspace is in slabs: `whole` in whole
+// solves, `pass` in single passes too.  Slabs need half-length lines on all axes, and pay for meshes whose
+// workspace main part holds kSlabBytes or more (PSPFFT_SLABS=1: whatever their size, in single passes too; 0: never).
+// A program that reads W between single passes finds it in one slab unless its plan asks for slabs
+// (PSPFFT_PLAN_SLABS): nothing can be read between the passes of a whole solve.  Both must read one
+// spectrum: where the z lines' addresses fit 32 bits in slabs only (FP64, planes of more than 1152 x 1078 values), only
+// those of 1024 points have family kernels with the same layout of it, and plans of other lengths keep slabs throughout.
+struct MixChoice {
+    bool mixed[3];            // in one slab
+    pspfft::MixInfo info[3];
+    bool whole, pass;
+    bool half(int axis) const { return mixed[axis] || whole; }  // somewhere
+};
+MixChoice mix_choice(const int n[3], pspfft_precision prec, bool flag) {
+    MixChoice c;
     const size_t main = static_cast<size_t>(2) * n[0] * n[1] * n[2] * cplx_size(prec);
     const char *e = std::getenv("PSPFFT_SLABS");
-    const bool large = n[0] > pspfft::kSlab && (e ? std::atoi(e) == 1 : main >= pspfft::kSlabBytes);
-    for (int slabs = large ? 1 : 0; slabs >= 0; --slabs) {
-        for (int a = 0; a < 3; ++a) mixed[a] = mix_axis(a, n, prec, slabs ? pspfft::kSlab : n[0], info[a]);
-        if (slabs && mixed[0] && mixed[1] && mixed[2]) return pspfft::kSlabShift;
-    }
-    return pspfft::kNoSlabs;
+    c.whole = n[0] > pspfft::kSlab && (e ? std::atoi(e) == 1 : main >= pspfft::kSlabBytes);
+    for (int a = 0; a < 3; ++a) c.whole = c.whole && mix_axis(a, n, prec, pspfft::kSlab, c.info[a]);
+    for (int a = 0; a < 3; ++a) c.mixed[a] = mix_axis(a, n, prec, n[0], c.info[a]);
+    const bool one_spectrum = c.mixed[2] || (prec == PSPFFT_FP64 && n[2] == 1024);
+    c.pass = c.whole && (flag || e || !one_spectrum);
+    return c;
 }
 
 // x and y transforms of a plane by the plane kernels on half-length lines
@@ -385,10 +397,7 @@ void mix_twiddles(int n, const pspfft::MixInfo &info, std::vector<std::complex<d
 
 // Spectrum layout (DevPlan::gz 2) and size: values of G and of Gn.
 bool mix_spectrum_blocked(const int n[3], pspfft_precision prec) {
-    pspfft::MixInfo info[3];
-    bool mixed[3];
-    mix_axes(n, prec, mixed, info);
-    return mixed[2] && pspfft::mix_spectrum(prec == PSPFFT_FP32 ? 0 : 1, n[2]) == 2;
+    return mix_choice(n, prec, false).half(2) && pspfft::mix_spectrum(prec == PSPFFT_FP32 ? 0 : 1, n[2]) == 2;
 }
 size_t spectrum_main(const int n[3], pspfft_precision prec) {
     const size_t row = mix_spectrum_blocked(n, prec) ? round_up(n[0], pspfft::kGroup) : n[0];
@@ -535,14 +544,17 @@ int generic_tile(int L, size_t csz) {
 // per kMaxProblems problems).  The launch's tile follows its longest line; a
 // line's arithmetic does not depend on the tile (each butterfly reads only its
 // own line), so results are the same alone and in any batch.
+// The plan as the passes of whole solves and single passes read it.
+const DevPlan &layout(pspfft_plan_t p, bool whole) { return whole ? p->whole : p->host; }
+
 // Problems p[c0 .. c1) of `idx` as the launch's problems, those of one plan (neighbours) as a segment.
 void add_problems(LaunchArgs &args, const std::vector<int> &idx, size_t c0, size_t c1, const pspfft_plan_t *plans,
-                  const pspfft_workspace_t *ws, const void *const *S, void *const *Phi) {
+                  const pspfft_workspace_t *ws, const void *const *S, void *const *Phi, bool whole) {
     std::memset(&args, 0, sizeof(args));
     args.count = static_cast<int>(c1 - c0);
     for (size_t j = c0; j < c1; ++j) {
         const int i = idx[j];
-        args.p[j - c0] = ProbArg{plans[i]->dev, S ? S[i] : nullptr, Phi ? Phi[i] : nullptr, ws[i]->W, ws[i]->Wn};
+        args.p[j - c0] = ProbArg{plans[i]->dev + (whole ? 1 : 0), S ? S[i] : nullptr, Phi ? Phi[i] : nullptr, ws[i]->W, ws[i]->Wn};
         if (j > c0 && plans[idx[j - 1]] == plans[i]) {
             args.seg[args.nseg - 1].group += 1;
             continue;
@@ -584,7 +596,8 @@ int mix_rounds(int rows, int tiles, bool slabs) {
 
 // Grouped launches of a pass by half-length lines: one per precision and length.
 pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_plan_t *plans,
-                         const pspfft_workspace_t *ws, const void *const *S, void *const *Phi, hipStream_t stream) {
+                         const pspfft_workspace_t *ws, const void *const *S, void *const *Phi, bool whole,
+                         hipStream_t stream) {
     const int axis = pspfft::pass_axis(mode);
     std::map<std::pair<int, int>, std::vector<int>> groups;
     for (int i : all) groups[{plans[i]->host.prec, plans[i]->n[axis]}].push_back(i);
@@ -600,10 +613,10 @@ pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_pla
         for (size_t c0 = 0; c0 < idx.size(); c0 += pspfft::kMaxProblems) {
             const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
             LaunchArgs args;
-            add_problems(args, idx, c0, c1, plans, ws, S, Phi);
+            add_problems(args, idx, c0, c1, plans, ws, S, Phi, whole);
             if (!number_tiles(args, mode, tile, idx, c0, plans)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
             bool slabs = false;
-            for (size_t j = c0; j < c1; ++j) slabs |= plans[idx[j]]->host.ks != pspfft::kNoSlabs;
+            for (size_t j = c0; j < c1; ++j) slabs |= layout(plans[idx[j]], whole).ks != pspfft::kNoSlabs;
             if (axis == 0) args.rounds = mix_rounds(info.rows, args.nwg, slabs);
             // x and y passes whose data stays in the Infinity Cache: each XCD takes one contiguous eighth of the
             // planes, and finds in its L2 what it wrote in the pass before; larger launches gain more from the
@@ -620,7 +633,7 @@ pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_pla
 }
 
 pspfft_status launch_generic_lines(int mode, const std::vector<int> &all, const pspfft_plan_t *plans,
-                                   const pspfft_workspace_t *ws, const void *const *S, void *const *Phi,
+                                   const pspfft_workspace_t *ws, const void *const *S, void *const *Phi, bool whole,
                                    hipStream_t stream) {
     const int axis = pspfft::pass_axis(mode);
     std::map<int, std::vector<int>> groups;
@@ -635,7 +648,7 @@ pspfft_status launch_generic_lines(int mode, const std::vector<int> &all, const 
         for (size_t c0 = 0; c0 < idx.size(); c0 += pspfft::kMaxProblems) {
             const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
             LaunchArgs args;
-            add_problems(args, idx, c0, c1, plans, ws, S, Phi);
+            add_problems(args, idx, c0, c1, plans, ws, S, Phi, whole);
             int lmax = 1;
             for (size_t j = c0; j < c1; ++j) lmax = std::max(lmax, plans[idx[j]]->host.ax[axis].L);
             args.gtile = generic_tile(lmax, csz);
@@ -660,22 +673,22 @@ pspfft_status launch_generic_lines(int mode, const std::vector<int> &all, const 
 
 // Grouped launches of a line pass (X_FWD .. X_INV kernels) for the problems idx.
 pspfft_status launch_lines(int mode, const std::vector<int> &all_in, const pspfft_plan_t *plans,
-                           const pspfft_workspace_t *ws, const void *const *S, void *const *Phi,
+                           const pspfft_workspace_t *ws, const void *const *S, void *const *Phi, bool whole,
                            hipStream_t stream) {
     const int axis = pspfft::pass_axis(mode);
     const bool row = axis == 0;
     // axes of half-length lines, and those outside the radix families (the generic kernel)
     std::vector<int> all, gen, mix;
     for (int i : all_in) {
-        const AxisPlan &ax = plans[i]->host.ax[axis];
+        const AxisPlan &ax = layout(plans[i], whole).ax[axis];
         (ax.mtw ? mix : ax.E ? all : gen).push_back(i);
     }
     if (!mix.empty()) {
-        const pspfft_status st = launch_mix(mode, mix, plans, ws, S, Phi, stream);
+        const pspfft_status st = launch_mix(mode, mix, plans, ws, S, Phi, whole, stream);
         if (st != PSPFFT_OK) return st;
     }
     if (!gen.empty()) {
-        const pspfft_status st = launch_generic_lines(mode, gen, plans, ws, S, Phi, stream);
+        const pspfft_status st = launch_generic_lines(mode, gen, plans, ws, S, Phi, whole, stream);
         if (st != PSPFFT_OK) return st;
     }
     // One kernel per (precision, radix family E, last-stage radix K, spectrum
@@ -734,7 +747,7 @@ pspfft_status launch_lines(int mode, const std::vector<int> &all_in, const pspff
                 const int i = idx[j];
                 const pspfft_plan_t pl = plans[i];
                 ProbArg &a = args.p[j - c0];
-                a.plan = pl->dev;
+                a.plan = pl->dev + (whole ? 1 : 0);
                 a.S = S ? S[i] : nullptr;
                 a.Phi = Phi ? Phi[i] : nullptr;
                 a.W = ws[i]->W;
@@ -814,7 +827,7 @@ pspfft_status launch_lines(int mode, const std::vector<int> &all_in, const pspff
 
 // Grouped launches of the fused plane kernels (forward or inverse) for the problems idx.
 pspfft_status launch_planes(bool fwd, const std::vector<int> &all, const pspfft_plan_t *plans,
-                            const pspfft_workspace_t *ws, const void *const *S, void *const *Phi,
+                            const pspfft_workspace_t *ws, const void *const *S, void *const *Phi, bool whole,
                             hipStream_t stream) {
     std::map<std::tuple<int, int, int>, std::vector<int>> groups;
     for (int i : all) groups[{static_cast<int>(plans[i]->prec), plans[i]->pE, plans[i]->pK}].push_back(i);
@@ -828,7 +841,7 @@ pspfft_status launch_planes(bool fwd, const std::vector<int> &all, const pspfft_
         for (size_t c0 = 0; c0 < idx.size(); c0 += pspfft::kMaxProblems) {
             const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
             LaunchArgs args;
-            add_problems(args, idx, c0, c1, plans, ws, S, Phi);
+            add_problems(args, idx, c0, c1, plans, ws, S, Phi, whole);
             args.nt = streaming_launch(plans, idx, c0, c1) ? 1 : 0;
             long wg = 0;
             for (int k = 0; k < args.nseg; ++k) {  // one workgroup per z plane
@@ -851,8 +864,9 @@ pspfft_status launch_planes(bool fwd, const std::vector<int> &all, const pspfft_
 
 // One pass for `count` problems.  Plans with fused planes run their x and y
 // transforms together in X_FWD and X_INV and have nothing to do in Y_FWD and Y_INV.
+// whole: a pass of a whole solve.
 pspfft_status run_pass(int mode, int count, const pspfft_plan_t *plans, const pspfft_workspace_t *ws,
-                       const void *const *S, void *const *Phi, hipStream_t stream) {
+                       const void *const *S, void *const *Phi, bool whole, hipStream_t stream) {
     const pspfft_status bad = PSPFFT_ERR_INVALID_ARGUMENT;
     if (count < 0) return fail(bad, -1, "pass %d: negative count", mode);
     if (count == 0) return PSPFFT_OK;
@@ -876,8 +890,8 @@ pspfft_status run_pass(int mode, int count, const pspfft_plan_t *plans, const ps
         else if (mode == pspfft::X_FWD || mode == pspfft::X_INV) planes.push_back(i);
     }
     pspfft_status st = PSPFFT_OK;
-    if (!planes.empty()) st = launch_planes(mode == pspfft::X_FWD, planes, plans, ws, S, Phi, stream);
-    if (st == PSPFFT_OK && !lines.empty()) st = launch_lines(mode, lines, plans, ws, S, Phi, stream);
+    if (!planes.empty()) st = launch_planes(mode == pspfft::X_FWD, planes, plans, ws, S, Phi, whole, stream);
+    if (st == PSPFFT_OK && !lines.empty()) st = launch_lines(mode, lines, plans, ws, S, Phi, whole, stream);
     if (st != PSPFFT_OK) return fail(st, plans[0]->verbosity, "pass %d of %d problems", mode, count);
     return PSPFFT_OK;
 }
@@ -924,7 +938,8 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
     const int vlevel = vbits ? static_cast<int>(vbits) - 1 : -1;
     const char *who = "pspfft_plan_create";
     if (!out || !h) return fail(PSPFFT_ERR_INVALID_ARGUMENT, vlevel, "%s: null %s", who, !out ? "out" : "h");
-    if ((flags & ~(static_cast<unsigned>(PSPFFT_PLAN_FIVE_PASS) | (7u << PSPFFT_PLAN_VERBOSITY_SHIFT))) ||
+    if ((flags & ~(static_cast<unsigned>(PSPFFT_PLAN_FIVE_PASS | PSPFFT_PLAN_SLABS) |
+                   (7u << PSPFFT_PLAN_VERBOSITY_SHIFT))) ||
         vbits > PSPFFT_CONSOLE_INFO_2 + 1)
         return fail(PSPFFT_ERR_INVALID_ARGUMENT, vlevel, "%s: unknown flags 0x%x", who, flags);
     if (prec != PSPFFT_FP32 && prec != PSPFFT_FP64)
@@ -962,16 +977,15 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
 
     // stage plans and twiddle tables (FP64, rounded once to the plan precision)
     std::vector<std::complex<double>> tws[3];
-    pspfft::MixInfo mix[3];
-    bool mixed[3], planes = false;
+    MixChoice mix = mix_choice(p->n, prec, (flags & PSPFFT_PLAN_SLABS) != 0);
+    bool planes = false;
     size_t mix_at[3];
-    p->host.ks = mix_axes(p->n, prec, mixed, mix);
     pspfft::MixInfo plane;
     const bool plane_table = mix_plane(p->n, prec, plane);
-    if (plane_table && !(flags & PSPFFT_PLAN_FIVE_PASS)) {
-        mixed[0] = planes = true;
-        mix[0] = plane;
-        p->host.ks = pspfft::kNoSlabs;
+    if (plane_table && !(flags & PSPFFT_PLAN_FIVE_PASS)) {  // (they take W in one slab)
+        mix.mixed[0] = planes = true;
+        mix.info[0] = plane;
+        mix.whole = mix.pass = false;
     }
     for (int a = 0; a < 3; ++a) {
         if (!build_axis(a, p->n[a], prec, p->host.ax[a], tws[a]))
@@ -992,10 +1006,10 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
             off += std::snprintf(radices + off, sizeof(radices) - off, s2 ? " x %d" : "%d", ax.R[s2]);
         PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_INFO_2, "  axis %c: n = %d, line of %d points, stages %s, %s", "xyz"[a],
                    ax.n, ax.L, ax.nst ? radices : "none", ax.E ? "radix-family kernels" : "generic line kernel");
-        if (mixed[a])
+        if (mix.half(a))
             PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_INFO_2, "  axis %c: half-length lines, stages %d x %d%s", "xyz"[a],
-                       mix[a].radix[0], mix[a].radix[1],
-                       mix[a].radix[2] > 1 ? (" x " + std::to_string(mix[a].radix[2])).c_str() : "");
+                       mix.info[a].radix[0], mix.info[a].radix[1],
+                       mix.info[a].radix[2] > 1 ? (" x " + std::to_string(mix.info[a].radix[2])).c_str() : "");
         else if (!ax.E)
             PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_WARNING,
                        "plan %d x %d x %d %s: axis %c (n = %d) runs on the generic line kernel, slower than the "
@@ -1005,7 +1019,7 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
     for (int a = 0; a < 3; ++a) {
         mix_at[a] = tws[a].size();
         // (five-pass plans keep the table of the planes too: pspfft_plan_resident_bytes knows a plan by its size alone)
-        if (mixed[a]) mix_twiddles(p->n[a], mix[a], tws[a]);
+        if (mix.half(a)) mix_twiddles(p->n[a], mix.info[a], tws[a]);
         else if (a == 0 && plane_table) mix_twiddles(p->n[a], plane, tws[a]);
         const std::vector<std::complex<double>> &tw = tws[a];
         const size_t tb = tw.size() * cs;
@@ -1025,7 +1039,7 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
             return fail(PSPFFT_ERR_DEVICE, vlevel, "%s: twiddle upload", who);
         p->host.ax[a].tw = p->tw[a];
         p->host.ax[a].post = a == 0 ? static_cast<char *>(p->tw[a]) + p->host.ax[a].ntw * cs : nullptr;
-        p->host.ax[a].mtw = mixed[a] ? static_cast<char *>(p->tw[a]) + mix_at[a] * cs : nullptr;
+        p->host.ax[a].mtw = mix.half(a) ? static_cast<char *>(p->tw[a]) + mix_at[a] * cs : nullptr;
         bytes += tb;
     }
     // Workspace z tiles.  Only meshes whose z planes span 4 MB or more (half-length z lines: 1 MB) are
@@ -1035,37 +1049,44 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
     // passes and cost y passes, one FP32 512^3 solve taking 3.65, 3.13, 3.12 and 3.29 ms with 1, 4, 8 and 16.
     // The tile is the largest power of two up to that (PSPFFT_ZTILE overrides the cap) dividing the z
     // lines' threads per line.
-    {
+    auto ztile = [&](bool half, bool slabs) {
         const size_t plane = static_cast<size_t>(2) * ny * nx * cs;
         int cap = plane >= (size_t(4) << 20) ? 16 : 1;
-        if (mixed[2]) cap = plane < (size_t(1) << 20) ? 1 : (nz > 512 && plane >= (size_t(4) << 20) ? 16 : 4);
-        if (p->host.ks == pspfft::kSlabShift) cap = 2;  // y passes lose less than z passes gain
+        if (half) cap = plane < (size_t(1) << 20) ? 1 : (nz > 512 && plane >= (size_t(4) << 20) ? 16 : 4);
+        if (slabs) cap = 2;  // y passes lose less than z passes gain
         if (const char *e = std::getenv("PSPFFT_ZTILE")) {
             const int v = std::atoi(e);
             if (v >= 1 && v <= 16 && (v & (v - 1)) == 0) cap = v;
         }
         int nbz = p->host.ax[2].NB;
-        if (mixed[2]) {  // whole tiles between a thread's first-stage positions t + NB*i + r*n0
-            const int n0 = nz / mix[2].radix[0];
-            nbz = n0 <= mix[2].nb ? n0 : std::gcd(n0, mix[2].nb);
+        if (half) {  // whole tiles between a thread's first-stage positions t + NB*i + r*n0
+            const int n0 = nz / mix.info[2].radix[0];
+            nbz = n0 <= mix.info[2].nb ? n0 : std::gcd(n0, mix.info[2].nb);
         }
         int zb = 1;  // generic z lines (NB = 0): no tiling, nz need not be a multiple of anything
         if (planes) cap = 1;  // the plane kernels take untiled workspaces
         while (nbz > 0 && zb < cap && nbz % (2 * zb) == 0) zb *= 2;
-        p->host.zb = zb;
-    }
+        return zb;
+    };
     // kz-fastest spectrum for wavefront-owned z lines and for z lines on the
     // generic kernel (whose lanes of a line walk consecutive kz); in blocks of
     // kGroup kx for half-length z lines (whose lanes take kGroup kx or more)
-    p->host.gz = mixed[2] ? pspfft::mix_spectrum(p->host.prec, nz)
-                          : (z_wave_lines(p) || p->host.ax[2].E == 0 ? 1 : 0);
+    p->host.gz = mix.half(2) ? pspfft::mix_spectrum(p->host.prec, nz)
+                             : (z_wave_lines(p) || p->host.ax[2].E == 0 ? 1 : 0);
+    p->whole = p->host;  // (complete but for the spectrum's address)
+    p->whole.ks = mix.whole ? pspfft::kSlabShift : pspfft::kNoSlabs;
+    p->whole.zb = ztile(mix.half(2), mix.whole);
+    p->host.ks = mix.pass ? pspfft::kSlabShift : pspfft::kNoSlabs;
+    p->host.zb = ztile(mix.pass || mix.mixed[2], mix.pass);
+    for (int a = 0; a < 3; ++a)
+        if (!mix.pass && !mix.mixed[a]) p->host.ax[a].mtw = nullptr;
     // fused x-y plane kernels: nx == ny = E*K (at most two stages) and the plane fits in LDS
     {
         const AxisPlan &ax = p->host.ax[0];
         const int K = ax.nst == 1 ? 1 : ax.R[1];
         p->fused = !(flags & PSPFFT_PLAN_FIVE_PASS) && nx == ny && ax.nst <= 2 && ax.E * K == nx &&
                    ax.ntw == nx - 1 && pspfft::plane_fits(p->host.prec, ax.E, K) && p->host.zb == 1 &&
-                   p->host.ks == pspfft::kNoSlabs;  // the plane kernels take W in one slab, untiled
+                   !mix.whole;  // the plane kernels take W in one slab, untiled
         if (p->fused) {
             p->pE = ax.E;
             p->pK = K;
@@ -1111,15 +1132,16 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
             hipStreamSynchronize(s) != hipSuccess)
             return fail(PSPFFT_ERR_DEVICE, vlevel, "%s: spectrum of the doubled Green's function", who);
     }
-    p->host.G = p->G;
-    p->host.Gn = p->Gn;
+    p->host.G = p->whole.G = p->G;
+    p->host.Gn = p->whole.Gn = p->Gn;
 
+    const DevPlan both[2] = {p->host, p->whole};
     void *dv = nullptr;
-    if ((st = alloc(&dv, sizeof(DevPlan))) != PSPFFT_OK) return fail(st, vlevel, "%s: plan table", who);
+    if ((st = alloc(&dv, sizeof(both))) != PSPFFT_OK) return fail(st, vlevel, "%s: plan table", who);
     p->dev = static_cast<DevPlan *>(dv);
-    if (hipMemcpy(p->dev, &p->host, sizeof(DevPlan), hipMemcpyHostToDevice) != hipSuccess)
+    if (hipMemcpy(p->dev, both, sizeof(both), hipMemcpyHostToDevice) != hipSuccess)
         return fail(PSPFFT_ERR_DEVICE, vlevel, "%s: plan table upload", who);
-    bytes += sizeof(DevPlan);
+    bytes += sizeof(both);
     p->bytes = bytes;  // the default workspace comes with the first pspfft_solve
 
     PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_INFO_1,
@@ -1189,7 +1211,7 @@ pspfft_status pspfft_pass_batched(pspfft_pass pass, int count, const pspfft_plan
                                   hipStream_t stream) {
     if (pass < PSPFFT_PASS_X_FWD || pass > PSPFFT_PASS_X_INV)
         return fail(PSPFFT_ERR_INVALID_ARGUMENT, -1, "pspfft_pass_batched: unknown pass %d", static_cast<int>(pass));
-    return run_pass(static_cast<int>(pass), count, plans, ws, S, Phi, stream);
+    return run_pass(static_cast<int>(pass), count, plans, ws, S, Phi, false, stream);
 }
 
 pspfft_status pspfft_solve_batched(int count, const pspfft_plan_t *plans, const pspfft_workspace_t *ws,
@@ -1242,7 +1264,7 @@ pspfft_status solve_all(int count, const pspfft_plan_t *plans, const pspfft_work
                         void *const *Phi, hipStream_t stream) {
     pspfft_status st = check_batch(count, plans, ws, S, Phi);
     for (int mode = pspfft::X_FWD; st == PSPFFT_OK && mode <= pspfft::X_INV; ++mode)
-        st = run_pass(mode, count, plans, ws, S, Phi, stream);
+        st = run_pass(mode, count, plans, ws, S, Phi, true, stream);
     return st;
 }
 
@@ -1353,16 +1375,15 @@ size_t pspfft_plan_resident_bytes(int nx, int ny, int nz, pspfft_precision prec)
     if (prec != PSPFFT_FP32 && prec != PSPFFT_FP64) return 0;
     if (!sizes_ok(nx, ny, nz, prec)) return 0;
     const int n[3] = {nx, ny, nz};
-    size_t bytes = sizeof(DevPlan);
-    pspfft::MixInfo mix[3];
-    bool mixed[3];
-    mix_axes(n, prec, mixed, mix);
-    mixed[0] = mix_plane(n, prec, mix[0]) || mixed[0];
+    size_t bytes = 2 * sizeof(DevPlan);
+    const MixChoice mix = mix_choice(n, prec, false);
+    pspfft::MixInfo plane;
+    const bool plane_table = mix_plane(n, prec, plane);
     for (int a = 0; a < 3; ++a) {  // twiddle tables, as pspfft_plan_create builds them
         AxisPlan ax;
         std::vector<std::complex<double>> tw;
         if (!build_axis(a, n[a], prec, ax, tw)) return 0;
-        if (mixed[a]) mix_twiddles(n[a], mix[a], tw);
+        if (mix.half(a) || (a == 0 && plane_table)) mix_twiddles(n[a], mix.half(a) ? mix.info[a] : plane, tw);
         bytes += tw.size() * cplx_size(prec);
     }
     // spectrum octant: main part and the kx = nx column

@@ -100,7 +100,7 @@ class GpuExecutor:
         p = self.plans.get(k)
         if p is None:
             nx, ny, nz = req.n
-            p = self.ps.Plan(nx, ny, nz, h=req.h, dtype=self.dtype)
+            p = self.ps.Plan(nx, ny, nz, h=req.h, dtype=self.dtype, slabs=True)  # the server never reads W
             self.plans[k] = p
         return p
 

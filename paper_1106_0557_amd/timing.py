@@ -40,7 +40,7 @@ def main(argv=None):
         _, h, S = sources.config5(n=n, device="cuda")
         src = S.to(dt)
         del S
-        plan = ps.Plan(n, n, n, h=h, dtype=dt)
+        plan = ps.Plan(n, n, n, h=h, dtype=dt, slabs=True)  # the passes as whole solves run them
         w = plan.workspace()
         out = torch.empty_like(src)
         t_settle, k = time.perf_counter(), 0

@@ -101,3 +101,83 @@ def test_tile_orders_of_small_and_large_launches(n):
     for w in ws:
         w.close()
     plan.close()
+
+
+def workspace_planes(plan, W, zs):
+    """Rows ky and values kx < nx of planes zs of a workspace main part, by the header's layout."""
+    nx, ny, nz = plan.n
+    B, parts = plan.ztile, []
+    for kx0 in range(0, nx, plan.slab):
+        w = min(plan.slab, nx - kx0)
+        slab = W[2 * ny * nz * kx0:2 * ny * nz * (kx0 + w)].view(nz // B, 2 * ny, B, w)
+        parts.append(torch.stack([slab[z // B, :, z % B] for z in zs]))
+    return torch.cat(parts, dim=2)
+
+
+def check_passes(n, dtype, tol, slab, zs, **option):
+    import paper_1106_0557_amd as ps
+
+    nx, ny, nz = n
+    plan = ps.Plan(*n, h=0.1, dtype=dtype, **option)
+    assert plan.slab == slab
+    mem = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+    ws = ps.Workspace(plan, memory=mem)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(sum(n))
+    S = torch.rand((nz, ny, nx), generator=gen, dtype=dtype, device="cuda") - 0.5
+    out = torch.full_like(S, float("nan"))
+    for p in (ps.PASS_X_FWD, ps.PASS_Y_FWD):
+        ps.pass_batched(p, [ws], S=[S], Phi=[out])
+    want = torch.fft.fft(torch.fft.rfft(S[zs].double(), n=2 * nx, dim=2), n=2 * ny, dim=1)
+    W = mem.view(torch.complex64 if dtype == torch.float32 else torch.complex128)
+    got = workspace_planes(plan, W, zs)
+    assert float((got - want[:, :, :nx]).norm() / want.norm()) <= tol, n
+    main = (2 * nx * ny * nz * W.element_size() + 255) // 256 * 256 // W.element_size()
+    nyq = W[main:main + 2 * ny * nz].view(nz, 2 * ny)[zs]
+    assert float((nyq - want[:, :, nx]).norm() / want.norm()) <= tol, n
+    for p in (ps.PASS_Z_CONV, ps.PASS_Y_INV, ps.PASS_X_INV):
+        ps.pass_batched(p, [ws], S=[S], Phi=[out])
+    solved = ws.solve(S)
+    assert float((out - solved).norm() / solved.norm()) <= tol, n
+    ws.close()
+    plan.close()
+
+
+# a partial last slab, odd rows, tiles of several planes
+@pytest.mark.parametrize("n", [(96, 25, 27), (243, 25, 192), (80, 100, 144)])
+def test_single_passes_in_slabs(n, monkeypatch):
+    monkeypatch.setenv("PSPFFT_SLABS", "1")
+    for dtype, tol in ((torch.float64, FP64_TOL), (torch.float32, FP32_TOL)):
+        check_passes(n, dtype, tol, 32, [0, 5, n[2] - 1])
+
+
+@pytest.mark.parametrize("slabs", [False, True])
+def test_single_passes_of_a_large_mesh(slabs):
+    """W in one slab between single passes, unless the plan asks for slabs; whole solves agree."""
+    n = (600, 576, 540)  # W of 2.8 GiB in FP32
+    check_passes(n, torch.float32, FP32_TOL, 32 if slabs else 600, [0, 17, 539], slabs=slabs)
+
+
+# FP32 z lines of more than 512 threads a workgroup, one persistent workgroup per CU: more tiles than the 256 CUs,
+# the last ones partial, and problems of two plans in one launch
+@pytest.mark.parametrize("n", [(75, 18, 1080), (81, 18, 1125), (75, 18, 1152)])
+def test_persistent_z_lines_of_several_tiles(n):
+    import paper_1106_0557_amd as ps
+
+    h = (0.021, 0.017, 0.013)
+    meshes = [n, n, (20, 6, n[2])]
+    assert 2 * n[0] * n[1] > 8 * 256 and 2 * n[0] * n[1] % 8
+    plans = {m: ps.Plan(*m, h=h, dtype=torch.float32) for m in set(meshes)}
+    ws = [plans[m].workspace() for m in meshes]
+    S = [sources.random_field(m, seed=i).to("cuda", torch.float32) for i, m in enumerate(meshes)]
+    out = [torch.full_like(s, float("nan")) for s in S]
+    for p in range(5):
+        ps.pass_batched(p, ws, S=S, Phi=out)
+    for m, s, o in zip(meshes, S, out):
+        assert torch.equal(o, plans[m].solve(s)), m
+    r = norms.report(out[1].double().cpu().numpy(), oracle.solve_fft(S[1].double().cpu().numpy(), h))
+    assert r["rel_l2"] <= FP32_TOL, (n, r)
+    for w in ws:
+        w.close()
+    for p in plans.values():
+        p.close()
