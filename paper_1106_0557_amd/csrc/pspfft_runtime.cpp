@@ -842,7 +842,8 @@ pspfft_status launch_planes(bool fwd, const std::vector<int> &all, const pspfft_
             const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
             LaunchArgs args;
             add_problems(args, idx, c0, c1, plans, ws, S, Phi, whole);
-            args.nt = streaming_launch(plans, idx, c0, c1) ? 1 : 0;
+            // (the planes on half-length lines take no nontemporal accesses)
+            args.nt = E && streaming_launch(plans, idx, c0, c1) ? 1 : 0;
             long wg = 0;
             for (int k = 0; k < args.nseg; ++k) {  // one workgroup per z plane
                 pspfft::Segment &sg = args.seg[k];
@@ -852,8 +853,12 @@ pspfft_status launch_planes(bool fwd, const std::vector<int> &all, const pspfft_
                 wg += nz * sg.group;
             }
             args.nwg = static_cast<int>(wg);
-            PSPFFT_LOG(3, "plane %s prec %d E %d K %d: %d problems, %ld workgroups of %d threads, %zu B LDS, "
-                          "streaming %d", fwd ? "fwd" : "inv", prec, E, K, args.count, wg, E * K * K, lds, args.nt);
+            if (E)
+                PSPFFT_LOG(3, "plane %s prec %d E %d K %d: %d problems, %ld workgroups of %d threads, %zu B LDS, "
+                              "streaming %d", fwd ? "fwd" : "inv", prec, E, K, args.count, wg, E * K * K, lds, args.nt);
+            else
+                PSPFFT_LOG(3, "plane %s prec %d half-length lines of %d: %d problems, %ld workgroups",
+                           fwd ? "fwd" : "inv", prec, K, args.count, wg);
             if ((E ? pspfft::launch_plane(fwd, prec, E, K, args, static_cast<int>(wg), lds, stream)
                    : pspfft::launch_mix_plane(fwd, prec, K, args, stream)) != hipSuccess)
                 return PSPFFT_ERR_DEVICE;
@@ -1007,7 +1012,8 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
         PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_INFO_2, "  axis %c: n = %d, line of %d points, stages %s, %s", "xyz"[a],
                    ax.n, ax.L, ax.nst ? radices : "none", ax.E ? "radix-family kernels" : "generic line kernel");
         if (mix.half(a))
-            PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_INFO_2, "  axis %c: half-length lines, stages %d x %d%s", "xyz"[a],
+            PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_INFO_2,
+                       "  axis %c: taken by half-length lines instead, stages %d x %d%s", "xyz"[a],
                        mix.info[a].radix[0], mix.info[a].radix[1],
                        mix.info[a].radix[2] > 1 ? (" x " + std::to_string(mix.info[a].radix[2])).c_str() : "");
         else if (!ax.E)
@@ -1146,8 +1152,9 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
 
     PSPFFT_MSG(vlevel, PSPFFT_CONSOLE_INFO_1,
                "plan %d x %d x %d %s: %zu bytes resident, %s, spectrum %s, workspace %zu bytes per solve "
-               "(z tile %d)", nx, ny, nz, pname, bytes, p->fused ? "fused x-y planes" : "five passes",
-               p->host.gz ? "kz-fastest" : "kx-fastest", ws_bytes(p->n, prec), p->host.zb);
+               "(z tile %d%s)", nx, ny, nz, pname, bytes, p->fused ? "fused x-y planes" : "five passes",
+               p->host.gz == 2 ? "in blocks of kx" : p->host.gz ? "kz-fastest" : "kx-fastest", ws_bytes(p->n, prec),
+               p->whole.zb, mix.whole ? ", slabs of 32 kx" : "");
     guard.armed = false;
     *out = p;
     return PSPFFT_OK;
