@@ -25,7 +25,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-parameter", "-fno-
 
 DEVICE_SOURCES = ([f"pass_{p}_e{e}.hip" for p in ("f32", "f64") for e in (36, 24, 20, 16)]
                   + [f"mix_{p}_{c}.hip" for p in ("f32", "f64") for c in "edcba"]
-                  + ["mix_plane_f32.hip", "mix_plane_f64.hip", "line_generic.hip", "pass_f32_e32.hip",
+                  + ["mix_plane_f32.hip", "mix_plane_f64.hip", "line_generic.hip",
                      "mix_info.hip", "green.hip", "noalloc.hip"])
 HOST_SOURCES = ["pspfft_runtime.cpp"]
 

@@ -210,7 +210,7 @@ __host__ __device__ constexpr int fix_tile(int prec, int mode, int /*nb*/) {
 }
 
 __host__ __device__ constexpr int max_block_for(int prec, int E) {
-    return prec == 0 ? (E == 16 ? 1024 : (E <= 24 || E == 32 ? 512 : 256)) : (E == 16 ? 512 : 256);
+    return prec == 0 ? (E == 16 ? 1024 : (E <= 24 ? 512 : 256)) : (E == 16 ? 512 : 256);
 }
 
 // Line forms of the line-pass instances (template parameter FIX): FIX & 7 is
@@ -275,62 +275,71 @@ __host__ __device__ constexpr int col_ldsw(int prec, int mode, int E, int NB) {
     return col_tables_global(prec, mode, E, NB) ? tile : col_stride(E * NB, tile, prec == 0 ? 8 : 16);
 }
 
-// Threads per line of the wavefront-owned column kernel: ST compile-time stages
-// with radices E, M, K (ST = 3) or E, M, M, K (4), M = E & -E.
-__host__ __device__ constexpr int wave_nb(int E, int K, int ST) {
-    return ST == 4 ? (E & -E) * (E & -E) * K : (E & -E) * K;
-}
+// The wavefront-owned z kernel: FP32 lines of kWaveE*NB points, NB = 32 or 64 threads, in four stages with radices 36, 4,
+// 4 and K (1152 and 2304 points).  Threads per line:
+constexpr int kWaveE = 36;
+__host__ __device__ constexpr int wave_nb(int K) { return 16 * K; }
 
-// Lines per workgroup of the wavefront-owned column kernel for lines of NB
-// threads, ST compile-time stages: the default tile, halved while the
-// workgroup exceeds the family's largest or the tile's rows and the stage
-// twiddles exceed the LDS (lines of 1536 points in the 24-family; four-stage
-// lines: 1152 and 2304 points in the 36-family, 640 and 1280 in the 20-family).
-__host__ __device__ constexpr int wave_tile(int prec, int mode, int E, int NB, int ST = 3) {
-    int t = fix_tile(prec, mode, NB);
-    const long L = static_cast<long>(E) * NB, csz = prec == 0 ? 8 : 16;
-    while (t > 1 && (static_cast<long>(t) * NB > max_block_for(prec, E) ||
+// Its lines per workgroup: the default tile, halved while the workgroup exceeds
+// the family's largest or the tile's rows and the stage twiddles exceed the LDS.
+__host__ __device__ constexpr int wave_tile(int NB) {
+    int t = fix_tile(0, Z_CONV, NB);
+    const long L = static_cast<long>(kWaveE) * NB, csz = 8;
+    while (t > 1 && (static_cast<long>(t) * NB > max_block_for(0, kWaveE) ||
                      (t * static_cast<long>(wave_line_stride(static_cast<int>(L))) + L - 1) * csz > 160 * 1024))
         t /= 2;
     return t;
 }
 
-// Whether the wavefront-owned column kernel keeps the stage twiddles in LDS
-// after the tile's rows: always for three-stage lines; for four-stage ones
-// unless leaving them in global memory (a table the L1 holds) lets one more
+// Whether it keeps the stage twiddles in LDS after the tile's rows: unless
+// leaving them in global memory (a table the L1 holds) lets one more
 // workgroup share a CU.
-__host__ __device__ constexpr bool wave_tw_lds(int prec, int mode, int E, int NB, int ST = 3) {
-    if (ST != 4) return true;
-    const long L = static_cast<long>(E) * NB, csz = prec == 0 ? 8 : 16, cap = 160 * 1024;
-    const long rows = wave_tile(prec, mode, E, NB, ST) * static_cast<long>(wave_line_stride(static_cast<int>(L))) * csz;
+__host__ __device__ constexpr bool wave_tw_lds(int NB) {
+    const long L = static_cast<long>(kWaveE) * NB, csz = 8, cap = 160 * 1024;
+    const long rows = wave_tile(NB) * static_cast<long>(wave_line_stride(static_cast<int>(L))) * csz;
     return cap / rows <= cap / (rows + (L - 1) * csz);
 }
 
-// LDS bytes of the wavefront-owned column kernel of pass `mode` for lines of
-// length L = E*NB: one row per line of the tile, then the stage twiddles (when
+// Its LDS bytes: one row per line of the tile, then the stage twiddles (when
 // they are kept in LDS).
-__host__ __device__ constexpr size_t wave_lds_bytes(int prec, int mode, int E, int NB, int ST = 3) {
-    const int L = E * NB;
-    return static_cast<size_t>(wave_tile(prec, mode, E, NB, ST) * wave_line_stride(L) +
-                               (wave_tw_lds(prec, mode, E, NB, ST) ? L - 1 : 0)) *
-           (prec == 0 ? 8 : 16);
+__host__ __device__ constexpr size_t wave_lds_bytes(int NB) {
+    const int L = kWaveE * NB;
+    return static_cast<size_t>(wave_tile(NB) * wave_line_stride(L) + (wave_tw_lds(NB) ? L - 1 : 0)) * 8;
 }
 
-// Wavefronts per SIMD the wavefront-owned kernel is compiled for: as many as
-// its workgroups that fit a CU's LDS bring (so that the register allocation
-// does not keep a second workgroup out), at least one.
-__host__ __device__ constexpr int wave_waves_per_simd(int prec, int mode, int E, int NB, int ST = 3) {
-    if (ST != 4) return 1;
-    const long per_cu = 160L * 1024 / static_cast<long>(wave_lds_bytes(prec, mode, E, NB, ST));
-    const long w = per_cu * wave_tile(prec, mode, E, NB, ST) * NB / 64 / 4;
+// Wavefronts per SIMD it is compiled for: as many as its workgroups that fit a
+// CU's LDS bring (so that the register allocation does not keep a second
+// workgroup out), at least one.
+__host__ __device__ constexpr int wave_waves_per_simd(int NB) {
+    const long per_cu = 160L * 1024 / static_cast<long>(wave_lds_bytes(NB));
+    const long w = per_cu * wave_tile(NB) * NB / 64 / 4;
     return w < 1 ? 1 : (w > 8 ? 8 : static_cast<int>(w));
 }
-__host__ __device__ constexpr size_t wave_z_lds_bytes(int prec, int E, int NB) {
-    return wave_lds_bytes(prec, Z_CONV, E, NB);
+
+// Lines of L points of a radix family that pass `mode` still runs on the family's kernels: half-length lines have
+// the mesh sizes 80, 96 and 144 to 1152 (128: FP64 x and y), but for z lines of meshes whose planes are too large for
+// their 32-bit addresses (more than 2^32 bytes in a block of up to 128 positions: no planes of up to 4096 x 2048 values
+// with fewer than 512 cells along z in FP32, 256 in FP64).  Those have 64-bit addresses (wide).
+__host__ __device__ constexpr bool family_line(int prec, int mode, int L, bool wide) {
+    const bool row = mode == X_FWD || mode == X_INV;
+    const int n = row ? L : L / 2;
+    if (n > (row ? 2 : 1) * (prec == 0 ? 2048 : 1152)) return false;
+    if (mode == Z_CONV && wide && n >= (prec == 0 ? 512 : 256)) return true;
+    const bool half = n == 80 || n == 96 || (n >= 144 && n <= 1152) || (n == 128 && prec == 1 && mode != Z_CONV);
+    return !half;
+}
+// Some line of family E whose last stage has radix K does.
+__host__ __device__ constexpr bool family_last(int prec, int mode, int E, int K) {
+    for (int nb = 1; nb <= 4096 / E; nb *= 2) {
+        int last = nb;
+        while (last > (E & -E)) last /= E & -E;
+        if (last == K && (family_line(prec, mode, E * nb, false) || family_line(prec, mode, E * nb, true))) return true;
+    }
+    return false;
 }
 
 // Fused plane kernels (x and y transforms of one z plane per workgroup) for
-// nx == ny = n = E*K: n*K threads, the LDS plane (n rows of row_stride(n, K))
+// nx == ny = n = E*K above 64 (mix_plane): n*K threads, the LDS plane (n rows of row_stride(n, K))
 // followed by the n - 1 stage twiddles, the n split factors and 2n values of
 // column 0.
 __host__ __device__ constexpr size_t plane_lds_bytes(int prec, int E, int K) {
@@ -340,7 +349,7 @@ __host__ __device__ constexpr size_t plane_lds_bytes(int prec, int E, int K) {
 // FP64 workgroups stay at 256 threads or fewer, where the two line transforms
 // each thread holds fit in registers.
 __host__ __device__ constexpr bool plane_fits(int prec, int E, int K) {
-    return K >= 1 && K <= (E & -E) && E * K * K <= (prec == 0 ? 1024 : 256) &&
+    return K >= 1 && K <= (E & -E) && E * K > 64 && E * K * K <= (prec == 0 ? 1024 : 256) &&
            plane_lds_bytes(prec, E, K) <= 160 * 1024;
 }
 
@@ -360,11 +369,6 @@ PSPFFT_DECLARE_FAMILY(launch_f64_e20, plane_f64_e20)
 PSPFFT_DECLARE_FAMILY(launch_f64_e24, plane_f64_e24)
 PSPFFT_DECLARE_FAMILY(launch_f64_e36, plane_f64_e36)
 #undef PSPFFT_DECLARE_FAMILY
-// Radix family E = 32 (FP32): z lines of 2048 points (32*32*2) kept within one
-// wavefront; its launcher takes only those z passes.
-hipError_t launch_f32_e32(int mode, int K, int fix, const LaunchArgs &args, int grid, int block, size_t lds,
-                          hipStream_t stream);
-
 inline hipError_t launch_pass(int mode, int prec, int E, int K, int fix, const LaunchArgs &args, int grid,
                               int block, size_t lds, hipStream_t stream) {
     if (grid <= 0) return hipSuccess;
@@ -373,7 +377,6 @@ inline hipError_t launch_pass(int mode, int prec, int E, int K, int fix, const L
         case 20: return launch_f32_e20(mode, K, fix, args, grid, block, lds, stream);
         case 24: return launch_f32_e24(mode, K, fix, args, grid, block, lds, stream);
         case 36: return launch_f32_e36(mode, K, fix, args, grid, block, lds, stream);
-        case 32: return launch_f32_e32(mode, K, fix, args, grid, block, lds, stream);
         case 116: return launch_f64_e16(mode, K, fix, args, grid, block, lds, stream);
         case 120: return launch_f64_e20(mode, K, fix, args, grid, block, lds, stream);
         case 124: return launch_f64_e24(mode, K, fix, args, grid, block, lds, stream);

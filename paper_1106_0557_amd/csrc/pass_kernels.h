@@ -667,39 +667,32 @@ __device__ __forceinline__ TileWalk tile_walk() {
 // Store of one complex value through a raw buffer resource: a store at or past
 // `bytes` is dropped by the hardware's range check, so lanes without a line
 // store nothing without a branch around the store.
-// NT: a nontemporal store (cache-policy bit 1).
-template <typename T, bool NT = false>
+template <typename T>
 __device__ __forceinline__ void buffer_store(const cx<T> v, char *base, uint32_t bytes, uint32_t off) {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, static_cast<short>(0),
                                                                         static_cast<int>(bytes), 0x00020000);
     if constexpr (sizeof(T) == 4) {
         typedef unsigned u2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rs, off, 0, NT ? 2 : 0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rs, off, 0, 0);
     } else {
         typedef unsigned u4 __attribute__((ext_vector_type(4)));
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), rs, off, 0, NT ? 2 : 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), rs, off, 0, 0);
     }
 }
 
-// One z line of a compile-time Z_CONV launch for lane (c, t) of the tile that
-// virtual workgroup `bid` handles: the same decomposition as pass_kernel's.
-// WIDE (z lines of arrays of 4 GB or more): 64-bit bases per position block
-// (LinePtrW), `bytes` is the position stride (a lane's offset stays below it),
-// and g points at the line's own spectrum run.
-template <typename T, bool WIDE = false>
+// Line of lane (c, t) of the tile that virtual workgroup `bid` handles in the wavefront-owned z kernel: the same
+// decomposition as pass_kernel's, with 64-bit bases per position block (LinePtrW) and the spectrum kz-fastest
+// (octant index (kyo*nx + kx)*(nz+1) + kz, Nyquist column kyo*(nz+1) + kz).
 struct ZLine {
-    std::conditional_t<WIDE, LinePtrW<T>, LinePtr<T, true>> lane;  // positions t + NB*m in W (or Wn)
-    const gbl<const char> *g;  // spectrum octant (G, or Gn for the Nyquist column)
+    LinePtrW<float> lane;      // positions t + NB*m in W (or Wn)
+    const gbl<const char> *g;  // the line's own run of the spectrum octant
     uint32_t glo, ghi, gstep;  // byte offsets of positions t + NB*m (m < E/2) and NB*(E-m) - t
-    uint32_t bytes;            // size of the line's array (W or Wn)
+    uint32_t bytes;            // position stride (a lane's offset stays below it)
     int active;
 };
-
-// GZ: the spectrum is stored kz-fastest (octant index (kyo*nx + kx)*(nz+1) + kz,
-// Nyquist column kyo*(nz+1) + kz), for lanes that walk along a line.
-template <typename T, int E, int NB, int TILE, bool GZ = false, bool WIDE = false>
-__device__ __forceinline__ ZLine<T, WIDE> z_line(const LaunchArgs &args, int bid, int c, int t) {
-    constexpr int CSZ = static_cast<int>(sizeof(cx<T>));
+template <int NB, int TILE>
+__device__ __forceinline__ ZLine z_line(const LaunchArgs &args, int bid, int c, int t) {
+    constexpr int CSZ = static_cast<int>(sizeof(cx<float>));
     int sgi = 0;
     while (sgi + 1 < args.nseg && bid >= args.seg[sgi + 1].wg_begin) ++sgi;
     const Segment &sg = args.seg[sgi];
@@ -716,10 +709,10 @@ __device__ __forceinline__ ZLine<T, WIDE> z_line(const LaunchArgs &args, int bid
     const bool nyq = local >= sg.wg_main;
     if (nyq) local -= sg.wg_main;
     const int g = local * TILE + c;
-    ZLine<T, WIDE> zl;
+    ZLine zl;
     int ky, kx;
-    size_t lane_off;
-    const void *arr;
+    size_t lane_off, plane;
+    void *arr;
     if (!nyq) {
         // rows of the plane in the order 0, 1, 2ny-1, 2, 2ny-2, ..., ny: ky and its
         // mirror (same spectrum values) go to neighbouring tiles
@@ -728,106 +721,40 @@ __device__ __forceinline__ ZLine<T, WIDE> z_line(const LaunchArgs &args, int bid
         kx = g - vrow * nx;
         ky = vrow == 0 ? 0 : (vrow == 2 * ny - 1 ? ny : ((vrow & 1) ? (vrow + 1) >> 1 : 2 * ny - (vrow >> 1)));
         arr = pa.W;
+        plane = static_cast<size_t>(2) * ny * nx;
         // z = t + NB*m sits in tile z/zb at row z%zb; zb divides NB
         const int zb = pl.zb;
         const int sh = __builtin_ctz(static_cast<unsigned>(zb));
         lane_off = static_cast<size_t>(ky) * zb * nx + kx +
                    (static_cast<size_t>(t >> sh) * 2 * ny * zb + (t & (zb - 1))) * nx;
-        if constexpr (WIDE) {
-            zl.lane = LinePtrW<T>{const_cast<char *>(static_cast<const char *>(arr)),
-                                  (zl.active ? lane_off : 0) * CSZ, static_cast<size_t>(NB) * 2 * ny * nx * CSZ};
-            zl.bytes = static_cast<uint32_t>(zl.lane.step);
-        } else {
-            zl.lane = line_ptr<T, true>(arr, zl.active ? lane_off : 0, static_cast<size_t>(NB) * 2 * ny * nx, CSZ);
-            zl.bytes = static_cast<uint32_t>(static_cast<size_t>(pl.nz) * 2 * ny * nx * CSZ);
-        }
     } else {
         zl.active = g < 2 * ny;
         ky = g;
         kx = nx;
         arr = pa.Wn;
+        plane = static_cast<size_t>(2) * ny;
         lane_off = static_cast<size_t>(g) + static_cast<size_t>(t) * 2 * ny;
-        if constexpr (WIDE) {
-            zl.lane = LinePtrW<T>{const_cast<char *>(static_cast<const char *>(arr)),
-                                  (zl.active ? lane_off : 0) * CSZ, static_cast<size_t>(NB) * 2 * ny * CSZ};
-            zl.bytes = static_cast<uint32_t>(zl.lane.step);
-        } else {
-            zl.lane = line_ptr<T, true>(arr, zl.active ? lane_off : 0, static_cast<size_t>(NB) * 2 * ny, CSZ);
-            zl.bytes = static_cast<uint32_t>(static_cast<size_t>(pl.nz) * 2 * ny * CSZ);
-        }
     }
+    zl.lane = LinePtrW<float>{static_cast<char *>(arr), (zl.active ? lane_off : 0) * CSZ, NB * plane * CSZ};
+    zl.bytes = static_cast<uint32_t>(zl.lane.step);
     // G~ is even in ky and kz: octant index min(k, 2n - k)
     const int kyo = ky <= ny ? ky : 2 * ny - ky;
+    const size_t gb = (nyq ? static_cast<size_t>(kyo) : static_cast<size_t>(kyo) * nx + kx) * (pl.nz + 1);
     zl.g = as_global(static_cast<const char *>(nyq ? pl.Gn : pl.G));
-    size_t gb, gs;
-    if constexpr (GZ) {
-        gb = (nyq ? static_cast<size_t>(kyo) : static_cast<size_t>(kyo) * nx + kx) * (pl.nz + 1);
-        gs = 1;
-    } else {
-        gb = nyq ? static_cast<size_t>(kyo) : static_cast<size_t>(kyo) * nx + kx;
-        gs = nyq ? static_cast<size_t>(ny + 1) : static_cast<size_t>(ny + 1) * nx;
-    }
-    if constexpr (WIDE && GZ) {
-        // the line's own run of the spectrum: offsets within it stay small
-        if (zl.active) zl.g += gb * sizeof(T);
-        gb = 0;
-    }
-    zl.glo = zl.active ? static_cast<uint32_t>((gb + t * gs) * sizeof(T)) : 0u;
-    zl.ghi = zl.active ? static_cast<uint32_t>((gb + (NB - t) * gs) * sizeof(T)) : 0u;
-    zl.gstep = static_cast<uint32_t>(static_cast<size_t>(NB) * gs * sizeof(T));
+    if (zl.active) zl.g += gb * sizeof(float);
+    zl.glo = zl.active ? static_cast<uint32_t>(t * sizeof(float)) : 0u;
+    zl.ghi = zl.active ? static_cast<uint32_t>((NB - t) * sizeof(float)) : 0u;
+    zl.gstep = static_cast<uint32_t>(NB * sizeof(float));
     return zl;
 }
 
-// One y line of a compile-time Y_FWD / Y_INV launch for lane (c, t) of the
-// tile that virtual workgroup `bid` handles: line (z, kx) has position y at
-// w_row(z, y) + kx; the Nyquist line of plane z is contiguous in Wn.  No
-// spectrum (g stays null).
-template <typename T, int NB, int TILE>
-__device__ __forceinline__ ZLine<T> y_line(const LaunchArgs &args, int bid, int c, int t) {
-    constexpr int CSZ = static_cast<int>(sizeof(cx<T>));
-    int sgi = 0;
-    while (sgi + 1 < args.nseg && bid >= args.seg[sgi + 1].wg_begin) ++sgi;
-    const Segment &sg = args.seg[sgi];
-    int local = bid - sg.wg_begin;
-    const int member = local % sg.group;
-    local /= sg.group;
-    const ProbArg &pa = args.p[sg.first + member];
-    using cplan = const __attribute__((address_space(4))) DevPlan;
-    const auto &pl = *(cplan *)pa.plan;
-    const int nx = pl.nx, ny = pl.ny, nz = pl.nz;
-    const bool nyq = local >= sg.wg_main;
-    if (nyq) local -= sg.wg_main;
-    const int g = local * TILE + c;
-    ZLine<T> yl;
-    if (!nyq) {
-        yl.active = g < nz * nx;
-        const int z = yl.active ? g / nx : 0;
-        const int kx = g - z * nx;
-        const size_t es = static_cast<size_t>(pl.zb) * nx;
-        const size_t lane_off = w_row(z, 0, ny, nx, pl.zb) + kx + static_cast<size_t>(t) * es;
-        yl.lane = line_ptr<T, true>(pa.W, yl.active ? lane_off : 0, NB * es, CSZ);
-        yl.bytes = static_cast<uint32_t>(static_cast<size_t>(nz) * 2 * ny * nx * CSZ);
-    } else {
-        yl.active = g < nz;
-        const size_t lane_off = static_cast<size_t>(g) * 2 * ny + t;
-        yl.lane = line_ptr<T, true>(pa.Wn, yl.active ? lane_off : 0, NB, CSZ);
-        yl.bytes = static_cast<uint32_t>(static_cast<size_t>(nz) * 2 * ny * CSZ);
-    }
-    yl.g = nullptr;
-    yl.glo = yl.ghi = yl.gstep = 0u;
-    return yl;
-}
-
-// Column passes (Y_FWD, Z_CONV, Y_INV) for lines of 16, 32 or 64 threads
-// (ST = 3: radices E, M, K with M*K = NB; ST = 4: E, M, M, K with M*M*K = NB,
-// FP32 only; a tile of wave_tile() lines): each line lies within one wavefront
-// (wavefront w holds lines w*64/NB onwards), so the stage exchanges stay inside
-// the wavefront and need no workgroup barrier.  The tile's stored half (all of
-// it for Y_INV) is loaded with adjacent lanes on adjacent lines (128-byte row
-// segments) and transposed through each line's LDS row; the results (the
-// stored half, all of them for Y_FWD) go back the same way.  Z_CONV: the
-// spectrum is stored kz-fastest for such plans, so each line's values are read
-// in contiguous runs.
+// z pass of FP32 lines of 1152 or 2304 points (radices 36, 4, 4, K; a tile of wave_tile() lines) in planes too large for
+// half-length lines: each line lies within one wavefront (wavefront w holds lines
+// w*64/NB onwards), so the stage exchanges stay inside the wavefront and need no
+// workgroup barrier.  The tile's stored half is loaded with adjacent lanes on
+// adjacent lines (128-byte row segments) and transposed through each line's LDS
+// row; the results go back the same way.  The spectrum is stored kz-fastest for
+// such plans, so each line's values are read in contiguous runs.
 //
 // PERSIST: the workgroup walks its tiles (tile_walk) and issues the next
 // tile's line (and spectrum) loads before the current tile's stores.  Vector
@@ -840,137 +767,100 @@ __device__ __forceinline__ ZLine<T> y_line(const LaunchArgs &args, int bid, int 
 // loop is entered with nothing outstanding, and plan fields are read through
 // the constant address space (scalar loads; a vector load there would wait for
 // the previous tile's stores).  Otherwise the workgroup takes one tile.
-template <typename T, int E, int K, int MODE, bool PERSIST, int ST = 3, bool WIDE = false, bool NT = false>
-__global__ void __launch_bounds__((max_block_for(sizeof(T) == 4 ? 0 : 1, E)))
-__attribute__((amdgpu_waves_per_eu(wave_waves_per_simd(sizeof(T) == 4 ? 0 : 1, MODE, E,
-                                                       wave_nb(E, K, ST), ST))))
-wave_col_kernel(const LaunchArgs args) {
+template <int K, bool PERSIST>
+__global__ void __launch_bounds__((max_block_for(0, kWaveE)))
+__attribute__((amdgpu_waves_per_eu(wave_waves_per_simd(wave_nb(K))))) wave_col_kernel(const LaunchArgs args) {
     extern __shared__ __align__(16) unsigned char smem[];
-    cx<T> *lds = reinterpret_cast<cx<T> *>(smem);
-    static_assert(MODE == Y_FWD || MODE == Z_CONV || MODE == Y_INV, "column passes");
-    static_assert(ST == 3 || (ST == 4 && sizeof(T) == 4), "three-stage lines, or four-stage ones in FP32");
-    static_assert(!WIDE || MODE == Z_CONV, "64-bit bases for z lines only");
-    constexpr int H = E / 2;
-    constexpr int NB = wave_nb(E, K, ST);
-    static_assert(NB == 16 || NB == 32 || NB == 64, "lines of 16, 32 or 64 threads");
+    cx<float> *lds = reinterpret_cast<cx<float> *>(smem);
+    constexpr int E = kWaveE, H = E / 2;
+    constexpr int NB = wave_nb(K);
+    static_assert(NB == 32 || NB == 64, "lines of 32 or 64 threads");
     constexpr int L = E * NB;
-    constexpr int TILE = wave_tile(sizeof(T) == 4 ? 0 : 1, MODE, E, NB, ST);
+    constexpr int TILE = wave_tile(NB);
     constexpr int S = wave_line_stride(L);
-    constexpr int NLOAD = MODE == Y_INV ? E : H;   // forward transforms read the stored half
-    constexpr int NSTORE = MODE == Y_FWD ? E : H;  // inverse ones keep the first half
-    constexpr bool ZC = MODE == Z_CONV;
-    using FFT_F = LineFFT<T, E, -1, true, NB, S>;
-    using FFT_I = LineFFT<T, E, +1, true, NB, S>;
+    using FFT_F = LineFFT<float, E, -1, true, NB, S>;
+    using FFT_I = LineFFT<float, E, +1, true, NB, S>;
 
     // (one tile per workgroup: the launch pads its grid to a multiple of 64, so
     // that the chunked order maps the workgroups onto the tiles one to one)
-    TileWalk walk = tile_walk<E != 16>();
+    TileWalk walk = tile_walk<true>();
     int bid = walk.tile();
     if (bid >= args.nwg) return;
     const int tid = threadIdx.x;
     const int cc = tid & (TILE - 1), tc = tid >> __builtin_ctz(TILE);  // adjacent lanes on adjacent lines
     const int cw = tid >> __builtin_ctz(NB), tw = tid & (NB - 1);       // line cw lies in one wavefront
-    const AxisPlan &ax0 = args.p[0].plan->ax[ZC ? 2 : 1];
-    constexpr bool TWL = wave_tw_lds(sizeof(T) == 4 ? 0 : 1, MODE, E, NB, ST);
+    const AxisPlan &ax0 = args.p[0].plan->ax[2];
     const auto twl = [&]() __attribute__((always_inline)) {
-        if constexpr (TWL) {
-            cx<T> *p = lds + TILE * S;
-            copy_to_lds<T>(p, ax0.tw, ax0.ntw);  // published by the first barrier below
-            return static_cast<const cx<T> *>(p);
+        if constexpr (wave_tw_lds(NB)) {
+            cx<float> *p = lds + TILE * S;
+            copy_to_lds<float>(p, ax0.tw, ax0.ntw);  // published by the first barrier below
+            return static_cast<const cx<float> *>(p);
         } else {
-            return as_global(static_cast<const cx<T> *>(ax0.tw));
+            return as_global(static_cast<const cx<float> *>(ax0.tw));
         }
     }();
     // position P = t + NB*m of a line's row sits at P + P/16 = t + t/16 + m*(NB + NB/16)
     constexpr int RM = NB + NB / 16;
-    cx<T> *rowc = lds + cc * S + tc + (tc >> 4);
-    cx<T> *roww = lds + cw * S + tw + (tw >> 4);
+    cx<float> *rowc = lds + cc * S + tc + (tc >> 4);
+    cx<float> *roww = lds + cw * S + tw + (tw >> 4);
 
-    auto line = [&](int b) __attribute__((always_inline)) {
-        if constexpr (ZC) return z_line<T, E, NB, TILE, false, WIDE>(args, b, cc, tc);
-        else return y_line<T, NB, TILE>(args, b, cc, tc);
-    };
-    auto load_g = [&](int b, T *gv) __attribute__((always_inline)) {
-        if constexpr (ZC) {
-            const ZLine<T, WIDE> zl = z_line<T, E, NB, TILE, true, WIDE>(args, b, cw, tw);
+    auto load_g = [&](int b, float *gv) __attribute__((always_inline)) {
+        const ZLine zl = z_line<NB, TILE>(args, b, cw, tw);
 #pragma unroll
-            for (int m = 0; m < E; ++m) {
-                const uint32_t idx = m < H ? m : E - m - 1;
-                gv[m] = *reinterpret_cast<const gbl<T> *>(zl.g + ((m < H ? zl.glo : zl.ghi) + idx * zl.gstep));
-            }
+        for (int m = 0; m < E; ++m) {
+            const uint32_t idx = m < H ? m : E - m - 1;
+            gv[m] = *reinterpret_cast<const gbl<float> *>(zl.g + ((m < H ? zl.glo : zl.ghi) + idx * zl.gstep));
         }
     };
-    auto cur = line(bid);
-    T gnx[ZC ? E : 1];
-    if constexpr (sizeof(T) == 4) {
+    auto cur = z_line<NB, TILE>(args, bid, cc, tc);
+    float gnx[E];
+    {
         // the line first (loads retire in order: its rows can be written
         // while the spectrum values are still in flight)
-        cx<T> first[NLOAD];
+        cx<float> first[H];
 #pragma unroll
-        for (int m = 0; m < NLOAD; ++m) first[m] = NT ? ld_nt(&cur.lane[m]) : cur.lane[m];
+        for (int m = 0; m < H; ++m) first[m] = cur.lane[m];
         load_g(bid, gnx);
 #pragma unroll
-        for (int m = 0; m < NLOAD; ++m) rowc[m * RM] = first[m];
-    } else {
-        // FP64: sixteen-byte values held there do not stay in registers
-        load_g(bid, gnx);
-#pragma unroll
-        for (int m = 0; m < NLOAD; ++m) rowc[m * RM] = NT ? ld_nt(&cur.lane[m]) : cur.lane[m];
+        for (int m = 0; m < H; ++m) rowc[m * RM] = first[m];
     }
     if constexpr (PERSIST) __builtin_amdgcn_s_waitcnt(0x0f70);  // nothing outstanding on entry (vmcnt 0)
     for (;;) {
         __syncthreads();  // the tile is in the rows (and, first time, the twiddles)
-        cx<T> v[E];
+        cx<float> v[E];
 #pragma unroll
-        for (int m = 0; m < E; ++m) v[m] = m < NLOAD ? roww[m * RM] : cx<T>{T(0), T(0)};
-        if constexpr (MODE != Y_INV) FFT_F::template run<K, true, true>(v, ax0, lds, S, twl, cw, tw);
-        if constexpr (ZC) {
+        for (int m = 0; m < E; ++m) v[m] = m < H ? roww[m * RM] : cx<float>{0.0f, 0.0f};
+        FFT_F::template run<K, true, true>(v, ax0, lds, S, twl, cw, tw);
 #pragma unroll
-            for (int m = 0; m < E; ++m) v[m] = scale(v[m], gnx[m]);
-        }
-        // the next tile's line (and spectrum values), before this tile's stores
+        for (int m = 0; m < E; ++m) v[m] = scale(v[m], gnx[m]);
+        // the next tile's line and spectrum values, before this tile's stores
         walk.i += walk.step;
         const int nbid = walk.tile();
         const bool more = PERSIST && nbid < args.nwg;
-        const int fbid = more ? nbid : bid;
-        // FP64: the line is loaded after this tile's stores (the extra 16-byte
-        // values held across the inverse transform do not stay in registers)
-        constexpr bool PF = PERSIST && sizeof(T) == 4;
         auto fol = cur;
-        cx<T> nxt[PF ? NLOAD : 1];
+        cx<float> nxt[PERSIST ? H : 1];
         if constexpr (PERSIST) {
-            fol = line(fbid);
-            if constexpr (PF) {
+            const int fbid = more ? nbid : bid;
+            fol = z_line<NB, TILE>(args, fbid, cc, tc);
 #pragma unroll
-                for (int m = 0; m < NLOAD; ++m) nxt[m] = NT ? ld_nt(&fol.lane[m]) : fol.lane[m];
-            }
+            for (int m = 0; m < H; ++m) nxt[m] = fol.lane[m];
             load_g(fbid, gnx);
         }
         (void)nxt;
-        if constexpr (MODE != Y_FWD) FFT_I::template run<K, true, true>(v, ax0, lds, S, twl, cw, tw);
+        FFT_I::template run<K, true, true>(v, ax0, lds, S, twl, cw, tw);
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int m = 0; m < NSTORE; ++m) roww[m * RM] = v[m];
+        for (int m = 0; m < H; ++m) roww[m * RM] = v[m];
         __syncthreads();  // results are in the rows
 #pragma unroll
-        for (int m = 0; m < NSTORE; ++m) {
-            if constexpr (WIDE) {
-                buffer_store<T, NT>(rowc[m * RM], cur.lane.block(m), cur.bytes,
-                                    cur.active ? static_cast<uint32_t>(cur.lane.lane) : 0xfffffff0u);
-            } else {
-                const uint32_t off = static_cast<uint32_t>(cur.lane.lane) +
-                                     static_cast<uint32_t>(m) * static_cast<uint32_t>(cur.lane.step);
-                buffer_store<T, NT>(rowc[m * RM], cur.lane.base, cur.bytes, cur.active ? off : 0xfffffff0u);
-            }
-        }
+        for (int m = 0; m < H; ++m)
+            buffer_store<float>(rowc[m * RM], cur.lane.block(m), cur.bytes,
+                                cur.active ? static_cast<uint32_t>(cur.lane.lane) : 0xfffffff0u);
         if (!more) break;
         __syncthreads();  // the rows have been read
-        if constexpr (PF) {
+        if constexpr (PERSIST) {
 #pragma unroll
-            for (int m = 0; m < NLOAD; ++m) rowc[m * RM] = nxt[m];
-        } else {
-#pragma unroll
-            for (int m = 0; m < NLOAD; ++m) rowc[m * RM] = NT ? ld_nt(&fol.lane[m]) : fol.lane[m];
+            for (int m = 0; m < H; ++m) rowc[m * RM] = nxt[m];
         }
         cur = fol;
         bid = nbid;
@@ -1077,7 +967,6 @@ __global__ void __launch_bounds__((max_block_for(sizeof(T) == 4 ? 0 : 1, E))) co
     constexpr int H = E / 2;
     constexpr int NLOAD = MODE == Y_INV ? E : H;   // forward transforms read the stored half
     constexpr int NSTORE = MODE == Y_FWD ? E : H;  // inverse ones keep the first half
-    constexpr int CSZ = static_cast<int>(sizeof(cx<T>));
     constexpr int NB = fix_nb(FIX, E, K);
     constexpr int TILE = pass_tile(prec, MODE, E, NB);
     constexpr int L = E * NB;
@@ -1209,72 +1098,6 @@ hipError_t launch_col(const LaunchArgs &args, int grid, int block, size_t lds, h
     return hipGetLastError();
 }
 
-inline int zconv_persist_mode();
-
-// The wavefront-owned column kernel: persistent where one workgroup fills a
-// compute unit (zconv_persist_mode), otherwise one tile per workgroup.
-template <typename T, int E, int K, int MODE, int ST = 3, bool WIDE = false>
-hipError_t launch_wave_col(const LaunchArgs &args, hipStream_t stream) {
-    constexpr int kMaxDevices = 64;
-    constexpr int prec = sizeof(T) == 4 ? 0 : 1;
-    constexpr int NB = wave_nb(E, K, ST);
-    constexpr int block = wave_tile(prec, MODE, E, NB, ST) * NB;
-    constexpr size_t lds = wave_lds_bytes(prec, MODE, E, NB, ST);
-    static_assert(lds <= 160 * 1024, "tile rows and twiddles fit the LDS");
-    static int per_cu[kMaxDevices] = {0}, cus[kMaxDevices] = {0};
-    auto fp = wave_col_kernel<T, E, K, MODE, true, ST, WIDE>;
-    auto fo = wave_col_kernel<T, E, K, MODE, false, ST, WIDE>;
-    // FP32 z lines below 4 GB of a streaming launch: nontemporal line loads and stores
-    constexpr bool NTZ = MODE == Z_CONV && sizeof(T) == 4 && !WIDE;
-    auto fpn = wave_col_kernel<T, E, K, MODE, true, ST, WIDE, NTZ>;
-    auto fon = wave_col_kernel<T, E, K, MODE, false, ST, WIDE, NTZ>;
-    const bool nt = NTZ && args.nt;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    if (per_cu[dev] == 0) {
-        for (auto f : {fp, fo, fpn, fon}) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    160 * 1024);
-            if (e != hipSuccess) return e;
-        }
-        int p = 0, c = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&p, fp, block, lds);
-        if (e != hipSuccess) return e;
-        e = hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        per_cu[dev] = p > 0 ? p : 1;
-        cus[dev] = c > 0 ? c : 1;
-    }
-    const int mode = zconv_persist_mode();
-    if (mode == 1 || (mode < 0 && per_cu[dev] == 1)) {
-        int grid = per_cu[dev] * cus[dev];
-        if (grid > args.nwg) grid = args.nwg;
-        hipLaunchKernelGGL(nt ? fpn : fp, dim3(grid), dim3(block), lds, stream, args);
-    } else {
-        // chunked tile order (tile_walk): a grid of whole chunk rounds (8 XCDs x kTileChunk)
-        constexpr int round = E != 16 ? 8 * kTileChunk : 1;
-        const int grid = (args.nwg + round - 1) / round * round;
-        hipLaunchKernelGGL(nt ? fon : fo, dim3(grid), dim3(block), lds, stream, args);
-    }
-    return hipGetLastError();
-}
-
-// The y passes take wavefront-owned lines (three stages, 32 or 64 threads per
-// line) where the column kernel's tile needs more LDS than this, so that a CU
-// holds only one of its workgroups (PSPFFT_WAVE_Y_LDS overrides, in bytes;
-// 0 always).  Measured, with two or more per CU the column kernel is as fast.
-inline size_t wave_y_min_lds() {
-    static long v = -1;
-    if (v < 0) {
-        long x = 80 * 1024;
-        if (const char *e = std::getenv("PSPFFT_WAVE_Y_LDS")) x = std::atol(e);
-        v = x >= 0 ? x : 80 * 1024;
-    }
-    return static_cast<size_t>(v);
-}
-
 // Where the wavefront-owned column kernel runs persistently
 // (PSPFFT_ZCONV_PERSIST: 0 never, 1 always, unset: where one workgroup fills a
 // compute unit).  With two or more workgroups per unit the hardware already
@@ -1304,85 +1127,79 @@ hipError_t launch_kernel(const LaunchArgs &args, int grid, int block, size_t lds
     return hipGetLastError();
 }
 
-// The wavefront-owned column kernel exists for three-stage lines of 16, 32 or 64
-// threads and four-stage FP32 lines of 32 or 64 threads whose tile of
-// wave_tile() lines fits the family's largest workgroup and the LDS.
-template <typename T, int E, int K, int MODE, int ST = 3>
-constexpr bool wave_col_fits() {
-    constexpr int prec = sizeof(T) == 4 ? 0 : 1;
-    constexpr int M = E & -E;
-    if constexpr (ST == 4) {
-        constexpr int NB = wave_nb(E, K, ST);
-        return prec == 0 && M < E && (NB == 32 || NB == 64) &&
-               wave_tile(prec, MODE, E, NB, ST) * NB <= max_block_for(prec, E) &&
-               wave_lds_bytes(prec, MODE, E, NB, ST) <= 160 * 1024;
-    } else {
-        constexpr int NB = M * K;
-        return (NB == 16 || NB == 32 || NB == 64) && wave_tile(prec, MODE, E, NB) * NB <= max_block_for(prec, E) &&
-               wave_lds_bytes(prec, MODE, E, NB) <= 160 * 1024;
+// The wavefront-owned z kernel: persistent where one workgroup fills a
+// compute unit (zconv_persist_mode), otherwise one tile per workgroup.
+template <int K>
+hipError_t launch_wave_col(const LaunchArgs &args, hipStream_t stream) {
+    constexpr int kMaxDevices = 64;
+    constexpr int NB = wave_nb(K);
+    constexpr int block = wave_tile(NB) * NB;
+    constexpr size_t lds = wave_lds_bytes(NB);
+    static_assert(lds <= 160 * 1024, "tile rows and twiddles fit the LDS");
+    static int per_cu[kMaxDevices] = {0}, cus[kMaxDevices] = {0};
+    auto fp = wave_col_kernel<K, true>;
+    auto fo = wave_col_kernel<K, false>;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    if (per_cu[dev] == 0) {
+        for (auto f : {fp, fo}) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    160 * 1024);
+            if (e != hipSuccess) return e;
+        }
+        int p = 0, c = 0;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&p, fp, block, lds);
+        if (e != hipSuccess) return e;
+        e = hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        per_cu[dev] = p > 0 ? p : 1;
+        cus[dev] = c > 0 ? c : 1;
     }
+    const int mode = zconv_persist_mode();
+    if (mode == 1 || (mode < 0 && per_cu[dev] == 1)) {
+        int grid = per_cu[dev] * cus[dev];
+        if (grid > args.nwg) grid = args.nwg;
+        hipLaunchKernelGGL(fp, dim3(grid), dim3(block), lds, stream, args);
+    } else {
+        // chunked tile order (tile_walk): a grid of whole chunk rounds (8 XCDs x kTileChunk)
+        constexpr int round = 8 * kTileChunk;
+        const int grid = (args.nwg + round - 1) / round * round;
+        hipLaunchKernelGGL(fo, dim3(grid), dim3(block), lds, stream, args);
+    }
+    return hipGetLastError();
 }
 
-// The y passes take the wavefront-owned kernel where its tile equals the
-// column kernel's (pass_tile), from which the host counted the launch's tiles:
-// three-stage lines whose default tile fits the family's largest workgroup,
-// and four-stage lines where the kernel runs two workgroups per CU (twiddles
-// in global memory: the 36-family).  Measured, 576^3 FP32 (1152-point lines):
-// y passes 1.53 / 1.77 -> 1.47 / 1.56 ms; with one workgroup per CU (the
-// 20-family's 640-point lines of 320^3) 0.176 / 0.199 -> 0.215 / 0.213 ms.
-template <typename T, int E, int K, int MODE, int ST>
-constexpr bool wave_y_fits() {
+// Pass MODE of the family lines that are left to it (family_line); the others have no instances.
+template <typename T, int E, int K, int FIX, int MODE>
+hipError_t launch_one(const LaunchArgs &args, int grid, int block, size_t lds, hipStream_t stream) {
     constexpr int prec = sizeof(T) == 4 ? 0 : 1;
-    constexpr int NB = wave_nb(E, K, ST);
-    return (NB == 32 || NB == 64) && wave_col_fits<T, E, K, MODE, ST>() &&
-           ((ST == 3 && fix_tile(prec, MODE, NB) * NB <= max_block_for(prec, E)) ||
-            (ST == 4 && !wave_tw_lds(prec, MODE, E, NB, ST))) &&
-           wave_tile(prec, MODE, E, NB, ST) == pass_tile(prec, MODE, E, NB);
+    constexpr bool row = MODE == X_FWD || MODE == X_INV;
+    if constexpr (FIX == 0 ? !family_last(prec, MODE, E, K)
+                           : !family_line(prec, MODE, E * fix_nb(FIX, E, K), (FIX & kFixWide) != 0)) {
+        return hipErrorInvalidValue;
+    } else {
+        if constexpr (MODE == Z_CONV) {
+            if (args.wave_z) {  // a kz-fastest spectrum, which only wave_col_kernel reads
+                if constexpr (prec == 0 && E == kWaveE && FIX == 4 + kFixWide)
+                    return launch_wave_col<K>(args, stream);
+                return hipErrorInvalidValue;
+            }
+        }
+        if constexpr (row || FIX == 0) return launch_kernel<T, E, K, MODE, FIX>(args, grid, block, lds, stream);
+        else return launch_col<T, E, K, MODE, FIX>(args, grid, block, lds, stream);
+    }
 }
 
 template <typename T, int E, int K, int FIX>
 hipError_t launch_mode(int mode, const LaunchArgs &args, int grid, int block, size_t lds, hipStream_t stream) {
     switch (mode) {
-        case X_FWD: return launch_kernel<T, E, K, X_FWD, FIX>(args, grid, block, lds, stream);
-        case Y_FWD:
-            if constexpr (FIX == 3 && wave_y_fits<T, E, K, Y_FWD, 3>()) {
-                if (col_default_lds(sizeof(T) == 4 ? 0 : 1, Y_FWD, E, wave_nb(E, K, 3)) > wave_y_min_lds())
-                    return launch_wave_col<T, E, K, Y_FWD>(args, stream);
-            }
-            if constexpr (FIX == 4 && wave_y_fits<T, E, K, Y_FWD, 4>()) {
-                if (col_default_lds(sizeof(T) == 4 ? 0 : 1, Y_FWD, E, wave_nb(E, K, 4)) > wave_y_min_lds())
-                    return launch_wave_col<T, E, K, Y_FWD, 4>(args, stream);
-            }
-            if constexpr (FIX != 0) return launch_col<T, E, K, Y_FWD, FIX>(args, grid, block, lds, stream);
-            else return launch_kernel<T, E, K, Y_FWD, FIX>(args, grid, block, lds, stream);
-        case Z_CONV:
-            if constexpr (FIX == 3 && wave_col_fits<T, E, K, Z_CONV>()) {
-                if (args.wave_z) return launch_wave_col<T, E, K, Z_CONV>(args, stream);
-            }
-            if constexpr (FIX == 4 && wave_col_fits<T, E, K, Z_CONV, 4>()) {
-                if (args.wave_z) return launch_wave_col<T, E, K, Z_CONV, 4>(args, stream);
-            }
-            if constexpr (FIX == 3 + kFixWide && wave_col_fits<T, E, K, Z_CONV>()) {
-                if (args.wave_z) return launch_wave_col<T, E, K, Z_CONV, 3, true>(args, stream);
-            }
-            if constexpr (FIX == 4 + kFixWide && wave_col_fits<T, E, K, Z_CONV, 4>()) {
-                if (args.wave_z) return launch_wave_col<T, E, K, Z_CONV, 4, true>(args, stream);
-            }
-            if (args.wave_z) return hipErrorInvalidValue;  // a kz-fastest spectrum needs wave_col_kernel
-            if constexpr (FIX != 0) return launch_col<T, E, K, Z_CONV, FIX>(args, grid, block, lds, stream);
-            else return launch_kernel<T, E, K, Z_CONV, FIX>(args, grid, block, lds, stream);
-        case Y_INV:
-            if constexpr (FIX == 3 && wave_y_fits<T, E, K, Y_INV, 3>()) {
-                if (col_default_lds(sizeof(T) == 4 ? 0 : 1, Y_INV, E, wave_nb(E, K, 3)) > wave_y_min_lds())
-                    return launch_wave_col<T, E, K, Y_INV>(args, stream);
-            }
-            if constexpr (FIX == 4 && wave_y_fits<T, E, K, Y_INV, 4>()) {
-                if (col_default_lds(sizeof(T) == 4 ? 0 : 1, Y_INV, E, wave_nb(E, K, 4)) > wave_y_min_lds())
-                    return launch_wave_col<T, E, K, Y_INV, 4>(args, stream);
-            }
-            if constexpr (FIX != 0) return launch_col<T, E, K, Y_INV, FIX>(args, grid, block, lds, stream);
-            else return launch_kernel<T, E, K, Y_INV, FIX>(args, grid, block, lds, stream);
-        case X_INV: return launch_kernel<T, E, K, X_INV, FIX>(args, grid, block, lds, stream);
+        case X_FWD: return launch_one<T, E, K, FIX, X_FWD>(args, grid, block, lds, stream);
+        case Y_FWD: return launch_one<T, E, K, FIX, Y_FWD>(args, grid, block, lds, stream);
+        case Z_CONV: return launch_one<T, E, K, FIX, Z_CONV>(args, grid, block, lds, stream);
+        case Y_INV: return launch_one<T, E, K, FIX, Y_INV>(args, grid, block, lds, stream);
+        case X_INV: return launch_one<T, E, K, FIX, X_INV>(args, grid, block, lds, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -142,21 +142,6 @@ int xcd_remap_mode(int mode) {
     return (mode >= 0 && mode < 5) ? modes[mode] : 0;
 }
 
-// FP32 z lines of 2048 points on the 32-family (radices 32, 32, 2: 64 threads
-// per line, so the line fits one wavefront; PSPFFT_Z32=0 keeps the 16-family's
-// 16, 16, 8, 128 threads per line).  Measured, one 1024^3 solve: z pass 24.4 ->
-// 18.2 ms.  Lines of 1024 points stay on the 16-family: as 32 x 32 (two lines
-// per wavefront, eight wavefronts per CU instead of sixteen) the 512^3 z pass
-// takes 1.56 ms instead of 1.43.
-bool z32_enabled() {
-    static int v = -1;
-    if (v < 0) {
-        const char *e = std::getenv("PSPFFT_Z32");
-        v = e && std::atoi(e) == 0 ? 0 : 1;
-    }
-    return v == 1;
-}
-
 // Lines per workgroup of each pass; PSPFFT_TILE="a,b,c,d,e" overrides (powers of two).
 int line_tile(int mode, int dflt) {
     static int v[5] = {-1, -1, -1, -1, -1};
@@ -485,30 +470,18 @@ bool arrays_below_4gb(pspfft_plan_t p) {
     return ws_bytes(p->n, p->prec) < lim && nx * ny * nz * r < lim && (nz + 1) * (ny + 1) * nx * r < lim;
 }
 
-// The z pass runs by wavefront-owned lines (wave_col_kernel) where its lines
-// have three stages E, M, K with M*K = 32 or 64 threads, or 16 threads where the
-// tile's rows take more than half the LDS (one workgroup per CU; measured, the
-// smaller 16-thread tiles gain nothing over the column kernel), or four stages
-// in FP32 (E, M, M, K with 32 or 64 threads), and the compile-time instance
-// exists.  Arrays of 4 GB or more take its 64-bit form, which needs a z line's
-// NB-position block (NB*2ny*nx values) below 4 GB.  Such plans keep the
-// spectrum kz-fastest, and their z launches always take that kernel.
+// A block of as many positions as family z lines have threads fits 32-bit byte offsets.
+bool z_block_below_4gb(pspfft_plan_t p) {
+    const size_t nb = p->host.ax[2].NB;
+    return nb * 2 * p->n[1] * p->n[0] * cplx_size(p->prec) < (size_t(1) << 32) - 64;
+}
+
+// Family z lines that wave_col_kernel takes, in planes too large for half-length lines: FP32 lines of 1152 and 2304
+// points (36, 4, 4, K).  Such plans keep the spectrum kz-fastest, and their z launches always take that kernel.
 bool z_wave_lines(pspfft_plan_t p) {
     const AxisPlan &az = p->host.ax[2];
-    if (az.E == 0) return false;  // generic kernel
-    const int prec = p->host.prec, M = az.E & -az.E, NB = az.NB;
-    const size_t block_bytes = static_cast<size_t>(NB) * 2 * p->n[1] * p->n[0] * (prec == 0 ? 8 : 16);
-    if (!arrays_below_4gb(p) && block_bytes >= (size_t(1) << 32) - 64) return false;
-    if (az.nst == 4)  // four-stage FP32 lines of 32 or 64 threads, wave_tile() lines per workgroup
-        return prec == 0 && M < az.E && az.R[1] == M && az.R[2] == M && M * M * az.R[3] == NB &&
-               (NB == 32 || NB == 64) &&
-               pspfft::wave_tile(prec, pspfft::Z_CONV, az.E, NB, 4) * NB <= pspfft::max_block_for(prec, az.E) &&
-               pspfft::wave_lds_bytes(prec, pspfft::Z_CONV, az.E, NB, 4) <= 160 * 1024;
-    const bool nb_ok = NB == 32 || NB == 64 || (NB == 16 && pspfft::wave_z_lds_bytes(prec, az.E, NB) > 80 * 1024);
-    return az.nst == 3 && az.R[1] == M && nb_ok && M * az.R[2] == NB &&
-           pspfft::wave_tile(prec, pspfft::Z_CONV, az.E, NB) * NB <= pspfft::max_block_for(prec, az.E) &&
-           pspfft::wave_lds_bytes(prec, pspfft::Z_CONV, az.E, NB) <= 160 * 1024 &&
-           pspfft::pass_tile(prec, pspfft::Y_FWD, az.E, NB) * NB <= pspfft::max_block_for(prec, az.E);
+    return p->prec == PSPFFT_FP32 && az.E == pspfft::kWaveE && az.nst == 4 && (az.NB == 32 || az.NB == 64) &&
+           !arrays_below_4gb(p) && z_block_below_4gb(p);
 }
 
 // Lines (main, Nyquist) that a pass processes for one problem.
@@ -691,19 +664,17 @@ pspfft_status launch_lines(int mode, const std::vector<int> &all_in, const pspff
         const pspfft_status st = launch_generic_lines(mode, gen, plans, ws, S, Phi, whole, stream);
         if (st != PSPFFT_OK) return st;
     }
-    // One kernel per (precision, radix family E, last-stage radix K, spectrum
-    // layout); a kz-fastest z group also shares its lines' stage count (the
-    // wavefront-owned kernel's tile depends on it).
-    std::map<std::tuple<int, int, int, int>, std::vector<int>> groups;
+    // One kernel per (precision, radix family E, last-stage radix K, spectrum layout).
+    std::map<std::tuple<int, int, int, bool>, std::vector<int>> groups;
     for (int i : all) {
         const AxisPlan &ax = plans[i]->host.ax[axis];
         const int K = ax.nst == 1 ? 1 : ax.R[ax.nst - 1];
-        const int gz = mode == pspfft::Z_CONV && plans[i]->host.gz ? ax.nst : 0;
+        const bool gz = mode == pspfft::Z_CONV && plans[i]->host.gz;
         groups[{static_cast<int>(plans[i]->prec), ax.E, K, gz}].push_back(i);
     }
     for (auto &kv : groups) {
         const int prec = std::get<0>(kv.first), E = std::get<1>(kv.first), K = std::get<2>(kv.first);
-        const bool gz = std::get<3>(kv.first) != 0;
+        const bool gz = std::get<3>(kv.first);
         std::vector<int> idx = kv.second;
         // problems of one plan next to each other: they form a segment sharing spectrum reads
         std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) {
@@ -718,8 +689,7 @@ pspfft_status launch_lines(int mode, const std::vector<int> &all_in, const pspff
             int block = 0, nbmax = 1;
             for (size_t j = c0; j < c1; ++j) nbmax = std::max(nbmax, plans[idx[j]]->host.ax[axis].NB);
             // (a kz-fastest spectrum needs the compile-time tile: no override)
-            const int gst = gz ? plans[idx[c0]]->host.ax[axis].nst : 0;
-            const int tile_target = gz ? pspfft::wave_tile(prec, mode, E, nbmax, gst)
+            const int tile_target = gz ? pspfft::wave_tile(nbmax)
                                        : line_tile(mode, pspfft::pass_tile(prec, mode, E, nbmax));
             for (size_t j = c0; j < c1; ++j) block = std::max(block, tile_target * plans[idx[j]]->host.ax[axis].NB);
             block = std::min(std::max(block, 64), bmax);
@@ -792,7 +762,7 @@ pspfft_status launch_lines(int mode, const std::vector<int> &all_in, const pspff
                 else if (a0.nst == 4 && a0.R[1] == M && a0.R[2] == M && M < E && E * M * M * K <= 4096) fix = 4;
                 const int cnb = pspfft::fix_nb(fix, E, K);
                 if (fix && !gz && block != pspfft::pass_tile(prec, mode, E, cnb) * cnb) fix = 0;
-                if (fix && gz && block != pspfft::wave_tile(prec, mode, E, cnb, fix) * cnb) fix = 0;
+                if (fix && gz && block != pspfft::wave_tile(cnb) * cnb) fix = 0;
                 if (fix >= 3 && pspfft::pass_tile(prec, pspfft::Y_FWD, E, cnb) * cnb > pspfft::max_block_for(prec, E))
                     fix = 0;
                 bool wide = false;
@@ -804,7 +774,7 @@ pspfft_status launch_lines(int mode, const std::vector<int> &all_in, const pspff
                 if (fix && wide) fix += pspfft::kFixWide;
             }
             // only wave_col_kernel reads that layout
-            if (gz && (fix & 7) != 3 && (fix & 7) != 4) return PSPFFT_ERR_UNSUPPORTED_SIZE;
+            if (gz && fix != 4 + pspfft::kFixWide) return PSPFFT_ERR_UNSUPPORTED_SIZE;
             // compile-time lines that keep their tables in global memory need only
             // their rows (or packed column positions) in LDS
             if (fix && row && pspfft::row_tables_global(prec, E, pspfft::fix_nb(fix, E, K))) {
@@ -996,11 +966,12 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
         if (!build_axis(a, p->n[a], prec, p->host.ax[a], tws[a]))
             return fail(PSPFFT_ERR_UNSUPPORTED_SIZE, vlevel, "%s: no stage plan for axis %d (n = %d)", who, a,
                         p->n[a]);
-        if (a == 2 && z32_enabled() && prec == PSPFFT_FP32 && p->host.ax[2].E == 16 && p->host.ax[2].L == 2048) {
-            // the 32-family's z lines, where the wavefront-owned z kernel takes them
+        if (a == 2 && prec == PSPFFT_FP32 && p->host.ax[2].E == 16 && p->host.ax[2].L == 2048) {
+            // stages 32 x 32 x 2 where a block of 64 positions fits 32-bit offsets: the stage plan that is reported for
+            // these lines, which half-length lines take wherever it applies
             const AxisPlan keep = p->host.ax[2];
             std::vector<std::complex<double>> tw32;
-            if (build_axis(2, p->n[2], prec, p->host.ax[2], tw32, 32) && z_wave_lines(p))
+            if (build_axis(2, p->n[2], prec, p->host.ax[2], tw32, 32) && z_block_below_4gb(p))
                 tws[2].swap(tw32);
             else
                 p->host.ax[2] = keep;
