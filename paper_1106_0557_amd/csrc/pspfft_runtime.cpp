@@ -121,13 +121,11 @@ pspfft_status fail(pspfft_status st, int plan_level, const char *fmt, ...) {
     return st;
 }
 
-// Workgroup renumbering for the XCDs, per pass (0 none, 1 contiguous eighths,
+// Workgroup renumbering for the XCDs, per pass of the family kernels (0 none, 1 contiguous eighths,
 // 2 runs of 8 within blocks of 64).  PSPFFT_XCD_REMAP="abcde" overrides the
-// five passes in order.  Measured: the row passes and the y passes gain from
-// contiguous eighths (y passes of one solve: FP64 768^3 8.0 / 8.9 -> 6.8 /
-// 7.0 ms, 256^3 0.156 / 0.160 -> 0.146 / 0.147 ms; FP32 1152^3, whose column
-// kernel keeps its twiddles in global memory, 32.7 / 21.3 -> 14.1 / 12.4 ms),
-// the z pass loses.
+// five passes in order.  The row passes and the y passes gain from contiguous eighths: an XCD finds in its L2 what it
+// wrote in the pass before (measured when they took these lengths, y passes of one FP64 256^3 solve 0.156 / 0.160 ->
+// 0.146 / 0.147 ms); the z pass loses.
 int xcd_remap_mode(int mode) {
     static int modes[5] = {-1, -1, -1, -1, -1};
     if (modes[0] < 0) {
@@ -513,10 +511,6 @@ int generic_tile(int L, size_t csz) {
     return t;
 }
 
-// Grouped launches of a pass on the generic line kernel: one per precision (and
-// per kMaxProblems problems).  The launch's tile follows its longest line; a
-// line's arithmetic does not depend on the tile (each butterfly reads only its
-// own line), so results are the same alone and in any batch.
 // The plan as the passes of whole solves and single passes read it.
 const DevPlan &layout(pspfft_plan_t p, bool whole) { return whole ? p->whole : p->host; }
 
@@ -538,15 +532,18 @@ void add_problems(LaunchArgs &args, const std::vector<int> &idx, size_t c0, size
     }
 }
 
-// Numbers the workgroups of a launch: `tile` lines each, main lines, then Nyquist lines.  False if
+// Numbers the workgroups of a launch: tile_of(plan) lines each, main lines, then Nyquist lines.  False if
 // there are too many.
-bool number_tiles(LaunchArgs &args, int mode, int tile, const std::vector<int> &idx, size_t c0,
+template <typename F>
+bool number_tiles(LaunchArgs &args, int mode, F &&tile_of, const std::vector<int> &idx, size_t c0,
                   const pspfft_plan_t *plans) {
     long wg = 0;
     for (int k = 0; k < args.nseg; ++k) {
         pspfft::Segment &sg = args.seg[k];
+        const pspfft_plan_t pl = plans[idx[c0 + sg.first]];
+        const int tile = tile_of(pl);
         long lm, ln;
-        pass_lines(mode, plans[idx[c0 + sg.first]]->n, lm, ln);
+        pass_lines(mode, pl->n, lm, ln);
         const long wm = (lm + tile - 1) / tile, wn = (ln + tile - 1) / tile;
         sg.wg_begin = static_cast<int>(wg);
         sg.wg_main = static_cast<int>(wm);
@@ -587,7 +584,7 @@ pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_pla
             const size_t c1 = std::min(idx.size(), c0 + pspfft::kMaxProblems);
             LaunchArgs args;
             add_problems(args, idx, c0, c1, plans, ws, S, Phi, whole);
-            if (!number_tiles(args, mode, tile, idx, c0, plans)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
+            if (!number_tiles(args, mode, [&](pspfft_plan_t) { return tile; }, idx, c0, plans)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
             bool slabs = false;
             for (size_t j = c0; j < c1; ++j) slabs |= layout(plans[idx[j]], whole).ks != pspfft::kNoSlabs;
             if (axis == 0) args.rounds = mix_rounds(info.rows, args.nwg, slabs);
@@ -605,6 +602,10 @@ pspfft_status launch_mix(int mode, const std::vector<int> &all, const pspfft_pla
     return PSPFFT_OK;
 }
 
+// Grouped launches of a pass on the generic line kernel: one per precision (and
+// per kMaxProblems problems).  The launch's tile follows its longest line; a
+// line's arithmetic does not depend on the tile (each butterfly reads only its
+// own line), so results are the same alone and in any batch.
 pspfft_status launch_generic_lines(int mode, const std::vector<int> &all, const pspfft_plan_t *plans,
                                    const pspfft_workspace_t *ws, const void *const *S, void *const *Phi, bool whole,
                                    hipStream_t stream) {
@@ -630,7 +631,8 @@ pspfft_status launch_generic_lines(int mode, const std::vector<int> &all, const 
             for (size_t j = c0; j < c1; ++j) ntw = std::max(ntw, plans[idx[j]]->host.ax[axis].ntw);
             const size_t bufs = static_cast<size_t>(2) * args.gtile * (lmax + 1) * csz;
             args.gtw = bufs + ntw * csz <= 160 * 1024 ? 1 : 0;
-            if (!number_tiles(args, mode, args.gtile, idx, c0, plans)) return PSPFFT_ERR_UNSUPPORTED_SIZE;
+            if (!number_tiles(args, mode, [&](pspfft_plan_t) { return args.gtile; }, idx, c0, plans))
+                return PSPFFT_ERR_UNSUPPORTED_SIZE;
             const size_t lds = bufs + (args.gtw ? ntw * csz : 0);
             PSPFFT_LOG(3, "pass %d prec %d generic: %d problems in %d segments, %ld workgroups of 256 threads, "
                           "%d lines each, %zu B LDS", mode, prec, args.count, args.nseg, static_cast<long>(args.nwg),
@@ -709,42 +711,11 @@ pspfft_status launch_lines(int mode, const std::vector<int> &all_in, const pspff
             if (block < nbmax || lds_need(block) > 160 * 1024) return PSPFFT_ERR_UNSUPPORTED_SIZE;
             size_t lds = lds_need(block);
             LaunchArgs args;
-            std::memset(&args, 0, sizeof(args));
-            args.count = static_cast<int>(c1 - c0);
+            add_problems(args, idx, c0, c1, plans, ws, S, Phi, whole);
             args.nt = streaming_launch(plans, idx, c0, c1) ? 1 : 0;
-            long wg = 0;
-            for (size_t j = c0; j < c1; ++j) {
-                const int i = idx[j];
-                const pspfft_plan_t pl = plans[i];
-                ProbArg &a = args.p[j - c0];
-                a.plan = pl->dev + (whole ? 1 : 0);
-                a.S = S ? S[i] : nullptr;
-                a.Phi = Phi ? Phi[i] : nullptr;
-                a.W = ws[i]->W;
-                a.Wn = ws[i]->Wn;
-                if (j > c0 && plans[idx[j - 1]] == pl) {
-                    pspfft::Segment &sg = args.seg[args.nseg - 1];
-                    sg.group += 1;
-                    continue;
-                }
-                pspfft::Segment &sg = args.seg[args.nseg++];
-                sg.first = static_cast<int>(j - c0);
-                sg.group = 1;
-            }
-            for (int k = 0; k < args.nseg; ++k) {
-                pspfft::Segment &sg = args.seg[k];
-                const pspfft_plan_t pl = plans[idx[c0 + sg.first]];
-                const int tile = block / pl->host.ax[axis].NB;
-                long lm, ln;
-                pass_lines(mode, pl->n, lm, ln);
-                const long wm = (lm + tile - 1) / tile, wn = (ln + tile - 1) / tile;
-                sg.wg_begin = static_cast<int>(wg);
-                sg.wg_main = static_cast<int>(wm);
-                wg += (wm + wn) * sg.group;
-            }
-            // grids are padded to a multiple of 8 (XCD renumbering) or 64 (chunked tile order)
-            if (wg + 64 > 0x7fffffffL) return PSPFFT_ERR_UNSUPPORTED_SIZE;
-            args.nwg = static_cast<int>(wg);
+            if (!number_tiles(args, mode, [&](pspfft_plan_t pl) { return block / pl->host.ax[axis].NB; }, idx, c0, plans))
+                return PSPFFT_ERR_UNSUPPORTED_SIZE;
+            const long wg = args.nwg;
             args.xcd_remap = xcd_remap_mode(mode);
             args.wave_z = gz ? 1 : 0;
             const long align = args.xcd_remap == 1 ? 8 : (args.xcd_remap == 2 ? 64 : 1);
