@@ -38,14 +38,17 @@
  * also reported as messages of level PSPFFT_CONSOLE_ERROR (see Messages).
  *
  * Supported sizes.  Each of nx, ny, nz may be any 2^a 3^b 5^c from 1 to 2048
- * (2n <= 4096 points per doubled line), in both precisions.  The sizes from 25
- * to 1152 outside the radix families, and of the others 80, 96 and 144 to 1152
- * (128 in part), run on half-length line kernels with radices of their own.
- * Sizes 2^a * o with o in {1, 3, 5, 9} and n >= 8, 10, 12, 18 (x: twice that, the
- * packed real transform having length n), up to 2048 (FP32) or 1152 (FP64) for y
- * and z and 4096 or 2304 for x, otherwise run on compile-time radix-family
- * kernels; the remaining sizes (15 and below, or above 1152) on a generic line
- * kernel (slower; a plan that uses it reports a warning).
+ * (2n <= 4096 points per doubled line), in both precisions.  The sizes 2^a * o with
+ * o in {1, 3, 5, 9} and n >= 8, 10, 12, 18 (x: twice that, the packed real
+ * transform having length n), up to 2048 (FP32) or 1152 (FP64) for y and z and
+ * 4096 or 2304 for x, are the radix families'.  Half-length line kernels with
+ * radices of their own run the sizes from 25 to 1152 outside the families
+ * (but FP64 625), and of the families' 80, 96 and 144 to 1152 (FP64: 128 along x
+ * and y), and the x and y transforms of square planes down to n = 16 (see
+ * pspfft_plan_create_ex); compile-time family kernels the families' other sizes;
+ * a generic line kernel the rest (x: 24 and below but 16, 20 and 24, y and z: 15 and
+ * below but 8, 10 and 12; FP64 625; above 1152 outside the families): it is slower,
+ * and a plan that uses it reports a warning.
  * Rows nx of 2560, 3072 and 4096 (FP32) or 2304 (FP64) are also accepted.
  * Other sizes return PSPFFT_ERR_UNSUPPORTED_SIZE.
  * S and Phi must be aligned to two reals (8 bytes FP32, 16 bytes FP64).
@@ -157,11 +160,10 @@ typedef enum {
  * As pspfft_plan_create, with options (a bitwise or of pspfft_plan_flags and
  * at most one PSPFFT_PLAN_VERBOSITY; unknown bits return
  * PSPFFT_ERR_INVALID_ARGUMENT).  By default a plan fuses
- * the x and y transforms of each z plane when nx == ny = E*K (E in
- * {16, 20, 24, 36}, K a power of two dividing the power-of-two part of E, so at
- * most two stages) and the plane of x spectra fits in the 160 KB of LDS: FP32
- * up to n = 128, FP64 up to n = 80, and for the other sizes nx == ny from 25 to
- * 120 (FP32) or 81 (FP64).  Both forms compute the same potential to
+ * the x and y transforms of each z plane for nx == ny = 16, 18, 20, 24, 25, 27, 30,
+ * 32, 36, 40, 45, 48, 50, 54, 60, 64, 72, 75 and 81, and in FP32 80, 90, 96, 100, 108,
+ * 120 and 128, where the plane of x spectra fits in the 160 KB of LDS and its
+ * transforms in the registers.  Both forms compute the same potential to
  * rounding; the fused one moves 2ny nz (nx+1) fewer complex values per solve.
  */
 pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], pspfft_precision prec,
@@ -171,17 +173,12 @@ pspfft_status pspfft_plan_create_ex(int nx, int ny, int nz, const double h[3], p
 int pspfft_plan_fused(pspfft_plan_t plan);
 
 /*
- * 1 if the plan keeps its spectrum kz-fastest, 0 otherwise (and for NULL).
- * That is the case for half-length z lines (in blocks of 8 kx, even kz before odd
- * ones, but for nz = 80, 96, 128, 144, 160 and 192 and in FP64 320, 576, 640, 1024
- * and 1152), and where the z pass keeps each line within one wavefront,
- * which reads its spectrum values in contiguous runs: z lines of three stages
- * E, M, K with 16, 32 or 64 threads per line (2 nz = 16*16*2, 36*4*4, 24*8*4,
- * 16*16*4 or 24*8*8, that is nz = 256, 288, 384, 512 or 768), four-stage FP32
- * lines of 32 or 64 threads (nz = 576, 1152, 320, 640), the FP32 32-family's
- * 2048-point lines (nz = 1024), each where a z line's block of NB*2ny*nx
- * positions stays below 4 GB; and z lines on the generic kernel (nz outside
- * the radix families), whose lanes of a line walk consecutive kz.
+ * 1 if the plan keeps the spectrum values of a z line together, 0 if it keeps the
+ * spectrum kx-fastest (and for NULL).  1 for half-length z lines (in blocks of 8 kx,
+ * even kz before odd ones) but of nz = 80, 96, 144, 160 and 192 and in FP64
+ * 320, 576, 640, 1024 and 1152; for z lines on the generic kernel, whose lanes of a
+ * line walk consecutive kz (kz-fastest); and for FP32 z lines of nz = 576 and 1152 in
+ * planes too large for half-length lines, kept within one wavefront (kz-fastest).
  * pspfft_plan_green exports the same octant either way.
  */
 int pspfft_plan_spectrum_kz_fastest(pspfft_plan_t plan);

@@ -5,11 +5,12 @@
 //                                            (rows of nx values, aligned)
 //   Wn : [z < nz][ky < 2ny]                  the kx = nx (Nyquist) column, split
 //                                            off so that every row of W is aligned
-// B (DevPlan::zb, a power of two up to 16 that divides the z lines' threads per
-// line; 1 unless a z plane spans 4 MB or more) keeps the z lines of the z pass
+// B (DevPlan::zb, a power of two up to 16 that divides nz; 1 but for planes of 4 MB
+// or more, half-length z lines: 1 MB) keeps the z lines of the z pass
 // within nz/B regions of B rows instead of nz planes far apart, which the address
 // translation caches cannot hold for large meshes.  Row (z, ky) starts at element
-// ((z/B)*2ny + ky)*B*nx + (z%B)*nx.
+// ((z/B)*2ny + ky)*B*nx + (z%B)*nx.  Whole solves of large meshes keep W in slabs of kx, each
+// laid out like that with its own width in place of nx (w_slab below).
 // The x pass writes rows ky = y < ny of every z plane; the y pass fills all 2ny
 // rows; the z pass works in place on z < nz; the inverse y pass leaves rows
 // y < ny; the inverse x pass reads them.  The upper z half of the doubled mesh
@@ -97,9 +98,10 @@ struct Segment {
     int wg_main;      // tiles of main lines per problem; the rest are Nyquist lines
 };
 
-// Workspace bytes of a launch above which its line data is streamed with
-// nontemporal accesses: about the device's Infinity Cache (256 MB), which a
-// smaller launch's workspaces can stay in between passes.
+// Workspace bytes of a launch above which family kernels stream their line data with
+// nontemporal accesses and half-length x and y passes take the chunked tile order: about
+// the device's Infinity Cache (256 MB), which a
+// smaller launch's workspaces can stay in between passes.  Half-length lines take no nontemporal accesses.
 constexpr size_t kStreamBytes = size_t(256) << 20;
 
 struct LaunchArgs {
@@ -275,8 +277,8 @@ __host__ __device__ constexpr int col_ldsw(int prec, int mode, int E, int NB) {
     return col_tables_global(prec, mode, E, NB) ? tile : col_stride(E * NB, tile, prec == 0 ? 8 : 16);
 }
 
-// The wavefront-owned z kernel: FP32 lines of kWaveE*NB points, NB = 32 or 64 threads, in four stages with radices 36, 4,
-// 4 and K (1152 and 2304 points).  Threads per line:
+// The wavefront-owned z kernel: FP32 lines of kWaveE*NB points, NB = 32 or 64 threads, in four stages with
+// radices 36, 4, 4 and K (1152 and 2304 points).  Threads per line:
 constexpr int kWaveE = 36;
 __host__ __device__ constexpr int wave_nb(int K) { return 16 * K; }
 
@@ -407,12 +409,14 @@ inline hipError_t launch_plane(bool fwd, int prec, int E, int K, const LaunchArg
 hipError_t launch_generic(int mode, int prec, const LaunchArgs &args, int grid, size_t lds, hipStream_t stream);
 
 
-// Spectrum layout of a plan whose z lines of n cells are half-length lines:
-// blocked, or kx-fastest for the lengths of the radix families whose plans have
-// always kept it so.
+// Spectrum layout of a plan whose z lines of n cells are half-length lines: blocked, but kx-fastest for the lengths
+// for which pspfft_plan_spectrum_kz_fastest has always answered 0.  That answer is what the list keeps, not
+// speed: measured, z passes with the blocked layout take 0.95 of the time at 96 (thirteen FP32 96^3), 144 and 160
+// (sixteen), 0.93 at 192 (nine), 0.97 in FP32 288 x 144 x 144, and in FP64 0.92 at 144 and 192 (eight), 0.88 at 320
+// (two), 0.83 at 576, 0.94 at 640, 0.88 at 1024 and 1152 (512 x 512 planes); 80 and single small solves within 1 %.
 __host__ __device__ constexpr int mix_spectrum(int prec, int n) {
     const bool fp32_only = n == 320 || n == 576 || n == 640 || n == 1024 || n == 1152;
-    return n == 80 || n == 96 || n == 128 || n == 144 || n == 160 || n == 192 || (prec != 0 && fp32_only) ? 0 : 2;
+    return n == 80 || n == 96 || n == 144 || n == 160 || n == 192 || (prec != 0 && fp32_only) ? 0 : 2;
 }
 
 // Stage radices of length n on the half-length line kernels (radix[2] = 1: two

@@ -7,8 +7,8 @@
 // and the inverse of a doubled line of which only the first half is kept is
 // the sum of their adjoints.  s = 1 shifts the frequency by one half: in a
 // decimation-in-time transform that only replaces k by k + s/2 in the stage
-// twiddles exp(-2 pi i r (k + s/2) / (Ns R)), so the first stage (k = 0)
-// multiplies by constants and the others read a table of their own.  One half
+// twiddles exp(-2 pi i r (k + s/2) / (Ns R)), so the first stage (k = 0) is a
+// shifted DFT (dft_half) and the others read a table of their own.  One half
 // of the line is in LDS at a time, half of what the doubled line takes, so a
 // compute unit holds two or more workgroups (one's memory traffic runs under
 // another's transforms) with whole 64- or 128-byte row segments.

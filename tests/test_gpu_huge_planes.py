@@ -22,6 +22,7 @@ def test_fp32_planes_of_huge_meshes(n):
         pytest.skip("no GPU")
     from paper_1106_0557_amd import Plan
 
+    torch.cuda.empty_cache()  # (what earlier tests' tensors left with the allocator)
     nx, ny, nz = n
     h = np.array((0.011, 0.009, 0.013))
     rng = np.random.default_rng(sum(n))

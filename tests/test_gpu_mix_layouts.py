@@ -181,3 +181,19 @@ def test_persistent_z_lines_of_several_tiles(n):
         w.close()
     for p in plans.values():
         p.close()
+
+
+def test_lengths_of_fused_planes():
+    """The sizes nx == ny that pspfft_plan_create_ex lists."""
+    import paper_1106_0557_amd as ps
+
+    both = {16, 18, 20, 24, 25, 27, 30, 32, 36, 40, 45, 48, 50, 54, 60, 64, 72, 75, 81}
+    want = {torch.float32: both | {80, 90, 96, 100, 108, 120, 128}, torch.float64: both}
+    for dt in want:
+        got = set()
+        for n in range(1, 145):
+            if ps.workspace_bytes(n, n, 3, dt):
+                plan = ps.Plan(n, n, 3, h=0.1, dtype=dt)
+                got |= {n} if plan.fused else set()
+                plan.close()
+        assert got == want[dt], got ^ want[dt]
