@@ -266,7 +266,9 @@ __device__ __forceinline__ void mirror_partners(const cx<T> *v, cx<T> *p, int t,
         const int addr = (lane - t + ((NB - t) & (NB - 1))) << 2;
 #pragma unroll
         for (int m = 0; m < E; ++m) {
-            const cx<T> d = t == 0 ? v[(E - m) % E] : v[E - 1 - m];  // what this lane sends
+            // what this lane sends (a choice of values: one of addresses can leave v in memory)
+            const cx<T> own = v[(E - m) % E], other = v[E - 1 - m];
+            const cx<T> d = {t == 0 ? own.x : other.x, t == 0 ? own.y : other.y};
             p[m] = cx<T>{lane_read(addr, d.x), lane_read(addr, d.y)};
         }
     }
@@ -509,7 +511,7 @@ __global__ void __launch_bounds__((max_block_for(sizeof(T) == 4 ? 0 : 1, E))) pa
             for (int m = 0; m < E; ++m) {
                 const int k = t + NB * m;
                 const cx<T> a = v[m];
-                const cx<T> b = k == 0 ? xn : wp[m];
+                const cx<T> b = {k == 0 ? xn.x : wp[m].x, k == 0 ? xn.y : wp[m].y};
                 const cx<T> sm = {a.x + b.x, a.y - b.y};
                 const cx<T> df = {a.x - b.x, a.y + b.y};
                 const cx<T> ed = cmulc(df, tw_at(post, k));
